@@ -114,8 +114,7 @@ struct TailParams {
 // DoFs (mode 2); with `partials` != NULL every block also writes the sum of squares of
 // its y entries to partials[block] (spmv_grid(A) entries).  xk / yk: vector kinds.
 hipError_t launch_spmv(const SellDev& A, const void* b, const void* x, void* y, const uint8_t* mask,
-                       int xk, int yk, int mode, double* partials, hipStream_t s,
-                       const double* dotv = nullptr);
+                       int xk, int yk, int mode, double* partials, hipStream_t s);
 int spmv_grid(const SellDev& A);
 // x_out = x + omega S (b - A x); S in lane layout, same kind as the vectors.  pmode 1:
 // also + beta (x - x_prev) with x_prev read from xo before it is overwritten (three-term
@@ -153,17 +152,22 @@ hipError_t launch_scale_div(int64_t n, double* y, const double* x, const double*
 int reduction_grid(int64_t n);
 hipError_t launch_dot_partials(int64_t n, const double* a, const double* b, double* partials, hipStream_t s);
 hipError_t launch_finish(const double* partials, int g, double* out, int sqrt_out, hipStream_t s);
-// MGS step: h = sum(pin) -> *hout; w -= h vi; partials of (w, vnext) (vnext NULL: (w, w));
-// gin = number of partials in pin (0: reduction_grid(n))
-hipError_t launch_mgs_step(int64_t n, double* w, const double* vi, const double* vnext, const double* pin,
-                           double* pout, double* hout, hipStream_t s, int gin = 0);
-// nrm = sqrt(sum(pin)) -> *hout; w /= nrm unless nrm == 0.  With H given, Givens step gj
+// Gram-Schmidt of FGMRES step j (modified Gram-Schmidt with its dot products formed in one
+// pass): w -= sum_{i<=j} h_i v_i, v_i = V + i * n, h stored in h[0..j]; gram: kWave * kWave
+// doubles that hold the basis's Gram entries from step to step (row 0 first, any content
+// before step 0); partials: gs_partials_size(m) doubles for up to m vectors; pnorm receives
+// *gnorm <= kMaxRedBlocks partial sums of the new (w, w).
+constexpr int kGsGroup = 10;          // vectors per pass
+int64_t gs_partials_size(int m);
+hipError_t launch_gram_schmidt(int64_t n, int j, double* w, const double* V, double* partials, double* gram,
+                               double* h, double* pnorm, int* gnorm, hipStream_t s);
+// nrm = sqrt(sum of the gin partials pin) -> *hout; w /= nrm unless nrm == 0.  With H given, Givens step gj
 // of GMRES on the (m+1) x m Hessenberg H (column-major, ld = m+1) follows in the same
 // kernel: rotate column gj by the previous rotations, form rotation gj, update g;
 // st[0] = |g[gj+1]|, st[1] = 1 if H[gj+1][gj] was 0 before the rotation.  With wc given,
 // w is also written there in FP32.
-hipError_t launch_mgs_normalize(int64_t n, double* w, const double* pin, double* hout, hipStream_t s, int gj = 0,
-                                int gm = 0, double* H = nullptr, double* cs = nullptr, double* sn = nullptr,
+hipError_t launch_mgs_normalize(int64_t n, double* w, const double* pin, int gin, double* hout, hipStream_t s,
+                                int gj = 0, int gm = 0, double* H = nullptr, double* cs = nullptr, double* sn = nullptr,
                                 double* gg = nullptr, double* st = nullptr, float* wc = nullptr);
 // x += sum_{i<k} y[i] Z_i, Z_i = Z + i*ldz of kind zk
 hipError_t launch_update_x(int64_t n, double* x, const void* Z, int zk, int64_t ldz, const double* y,

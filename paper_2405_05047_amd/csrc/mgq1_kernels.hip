@@ -46,18 +46,18 @@ namespace mgq1 {
 namespace {
 
 // ------------------------------------------------------------------ grid kernels
-// NORM: per-block partial sums of out * out, or of out * dotv[row] when dotv is given
+// NORM: per-block partial sums of out * out
 template <int B, int K, class XI, class XO, class T, int MODE, bool NORM, int KB, bool C16>
 __global__ __launch_bounds__(kThreads) void k_spmv(SellDev A, const XO* __restrict__ b, const XI* __restrict__ x,
                                                    XO* __restrict__ y, const uint8_t* __restrict__ mask,
-                                                   double* __restrict__ partials, const double* __restrict__ dotv) {
+                                                   double* __restrict__ partials) {
   dict_stage<K>(A);
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
   const SliceLane s = slice_lane<B, 1>(A, bid * kSliceWaves + threadIdx.x / kWave, threadIdx.x % kWave);
   const T out = spmv_slice<B, 1, K, XI, XO, T, MODE, KB, C16>(A, b, x, y, mask, s);
   if (NORM) {
     __shared__ double lds[kMaxWaves + 1];
-    const double p = block_allsum(double(out) * (dotv ? (s.valid ? dotv[s.dof] : 0.0) : double(out)), lds);
+    const double p = block_allsum(double(out) * double(out), lds);
     if (threadIdx.x == 0) partials[blockIdx.x] = p;
   }
 }
@@ -398,48 +398,6 @@ __global__ __launch_bounds__(1024) void k_finish(const double* __restrict__ p, i
   if (threadIdx.x == 0) *out = sq ? sqrt(s) : s;
 }
 
-// modified Gram-Schmidt step: h = sum(pin) (= (w, v_i)), stored by block 0;
-// w -= h v_i; partial sums of (w, vnext) or, for vnext == nullptr, of (w, w)
-__global__ __launch_bounds__(kRedThreads) void k_mgs_step(int64_t n, double* __restrict__ w,
-                                                          const double* __restrict__ vi,
-                                                          const double* __restrict__ vnext,
-                                                          const double* __restrict__ pin, int gin,
-                                                          double* __restrict__ pout, double* __restrict__ hout) {
-  __shared__ double lds[kMaxWaves + 1];
-  constexpr int U = 4;
-  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-  double wv[U], vv[U], nv[U];
-  auto load = [&](int64_t i0) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t i = i0 + u * stride;
-      const bool ok = i < n;
-      wv[u] = ok ? w[i] : 0.0;
-      vv[u] = ok ? vi[i] : 0.0;
-      nv[u] = (ok && vnext) ? vnext[i] : 0.0;
-    }
-  };
-  // the first chunk's loads do not depend on h: issue them before the partial sums are
-  // combined, so the two latencies overlap
-  const int64_t first = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  load(first);
-  const double h = sum_partials(pin, gin, lds);
-  if (blockIdx.x == 0 && threadIdx.x == 0) *hout = h;
-  double t = 0.0;
-  for (int64_t i0 = first; i0 < n; i0 += stride * U) {
-    if (i0 != first) load(i0);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t i = i0 + u * stride;
-      const double v = wv[u] - h * vv[u];
-      if (i < n) w[i] = v;
-      t += v * (vnext ? nv[u] : v);
-    }
-  }
-  const double s = block_allsum(t, lds);
-  if (threadIdx.x == 0) pout[blockIdx.x] = s;
-}
-
 // Givens rotation j of the Hessenberg column j (applies the previous rotations, forms the
 // new one, rotates g); st receives |g_{j+1}| and the breakdown flag
 __device__ __forceinline__ void givens_column(int j, int m, double* H, double* cs, double* sn, double* g,
@@ -546,7 +504,7 @@ __global__ void k_init_g(int m, double* g, const double* beta) {
 
 template <int B, int K, class XI, class XO, class T>
 hipError_t spmv_t(const SellDev& A, const void* b, const void* x, void* y, const uint8_t* mask, int mode,
-                  double* partials, const double* dotv, hipStream_t s) {
+                  double* partials, hipStream_t s) {
   const unsigned g = slice_grid(A.nslices);
   if (g == 0) return hipSuccess;
   const XO* bb = static_cast<const XO*>(b);
@@ -554,8 +512,7 @@ hipError_t spmv_t(const SellDev& A, const void* b, const void* x, void* y, const
   XO* yy = static_cast<XO*>(y);
   // slot batch and column format are runtime properties of the operator
 #define MGQ1_SPMV4(MODE, NORM, KB, C16)                                                                     \
-  hipLaunchKernelGGL((k_spmv<B, K, XI, XO, T, MODE, NORM, KB, C16>), g, kThreads, dict_lds_bytes<K>(A), s, A, bb, xx, yy, mask, partials, \
-                     dotv)
+  hipLaunchKernelGGL((k_spmv<B, K, XI, XO, T, MODE, NORM, KB, C16>), g, kThreads, dict_lds_bytes<K>(A), s, A, bb, xx, yy, mask, partials)
 #define MGQ1_SPMV(MODE, NORM)                                                             \
   if (A.col16) {                                                                          \
     if (A.kb == kb_alt<B>()) MGQ1_SPMV4(MODE, NORM, kb_alt<B>(), true);                   \
@@ -567,8 +524,7 @@ hipError_t spmv_t(const SellDev& A, const void* b, const void* x, void* y, const
   // the combinations the library uses: y = Ax, b - Ax with or without norm partials,
   // masked defect
   if (mode == 0 && !partials) MGQ1_SPMV(0, false)
-  else if (mode == 0 && dotv) MGQ1_SPMV(0, true)
-  else if (mode == 1 && partials && !dotv) MGQ1_SPMV(1, true)
+  else if (mode == 1 && partials) MGQ1_SPMV(1, true)
   else if (mode == 1) MGQ1_SPMV(1, false)
   else if (mode == 2 && !partials) MGQ1_SPMV(2, false)
   else return hipErrorInvalidValue;
@@ -579,21 +535,21 @@ hipError_t spmv_t(const SellDev& A, const void* b, const void* x, void* y, const
 
 template <int B>
 hipError_t spmv_b(const SellDev& A, const void* b, const void* x, void* y, const uint8_t* mask, int xk, int yk,
-                  int mode, double* partials, const double* dotv, hipStream_t s) {
+                  int mode, double* partials, hipStream_t s) {
   if (A.kind == VK_DICT) {
-    if (xk == X_F64 && yk == X_F64) return spmv_t<B, VK_DICT, double, double, double>(A, b, x, y, mask, mode, partials, dotv, s);
+    if (xk == X_F64 && yk == X_F64) return spmv_t<B, VK_DICT, double, double, double>(A, b, x, y, mask, mode, partials, s);
     return hipErrorInvalidValue;
   }
   if (A.kind == VK_F64) {
-    if (xk == X_F64 && yk == X_F64) return spmv_t<B, VK_F64, double, double, double>(A, b, x, y, mask, mode, partials, dotv, s);
-    if (xk == X_F32 && yk == X_F64) return spmv_t<B, VK_F64, float, double, double>(A, b, x, y, mask, mode, partials, dotv, s);
+    if (xk == X_F64 && yk == X_F64) return spmv_t<B, VK_F64, double, double, double>(A, b, x, y, mask, mode, partials, s);
+    if (xk == X_F32 && yk == X_F64) return spmv_t<B, VK_F64, float, double, double>(A, b, x, y, mask, mode, partials, s);
     return hipErrorInvalidValue;
   }
   if (xk != X_F32 || yk != X_F32) return hipErrorInvalidValue;
   switch (A.kind) {
-    case VK_F32: return spmv_t<B, VK_F32, float, float, float>(A, b, x, y, mask, mode, partials, dotv, s);
-    case VK_F16: return spmv_t<B, VK_F16, float, float, float>(A, b, x, y, mask, mode, partials, dotv, s);
-    case VK_BF16: return spmv_t<B, VK_BF16, float, float, float>(A, b, x, y, mask, mode, partials, dotv, s);
+    case VK_F32: return spmv_t<B, VK_F32, float, float, float>(A, b, x, y, mask, mode, partials, s);
+    case VK_F16: return spmv_t<B, VK_F16, float, float, float>(A, b, x, y, mask, mode, partials, s);
+    case VK_BF16: return spmv_t<B, VK_BF16, float, float, float>(A, b, x, y, mask, mode, partials, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -679,12 +635,12 @@ void slot_batch_choices(int B, int* kb_def, int* kb_other) {
 int spmv_grid(const SellDev& A) { return int(slice_grid(A.nslices)); }
 
 hipError_t launch_spmv(const SellDev& A, const void* b, const void* x, void* y, const uint8_t* mask, int xk, int yk,
-                       int mode, double* partials, hipStream_t s, const double* dotv) {
+                       int mode, double* partials, hipStream_t s) {
   switch (A.B) {
-    case 1: return spmv_b<1>(A, b, x, y, mask, xk, yk, mode, partials, dotv, s);
-    case 2: return spmv_b<2>(A, b, x, y, mask, xk, yk, mode, partials, dotv, s);
-    case 3: return spmv_b<3>(A, b, x, y, mask, xk, yk, mode, partials, dotv, s);
-    case 4: return spmv_b<4>(A, b, x, y, mask, xk, yk, mode, partials, dotv, s);
+    case 1: return spmv_b<1>(A, b, x, y, mask, xk, yk, mode, partials, s);
+    case 2: return spmv_b<2>(A, b, x, y, mask, xk, yk, mode, partials, s);
+    case 3: return spmv_b<3>(A, b, x, y, mask, xk, yk, mode, partials, s);
+    case 4: return spmv_b<4>(A, b, x, y, mask, xk, yk, mode, partials, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -954,18 +910,11 @@ hipError_t launch_finish(const double* partials, int g, double* out, int sqrt_ou
   return hipGetLastError();
 }
 
-hipError_t launch_mgs_step(int64_t n, double* w, const double* vi, const double* vnext, const double* pin,
-                           double* pout, double* hout, hipStream_t s, int gin) {
-  const unsigned g = vec_grid(n);
-  hipLaunchKernelGGL(k_mgs_step, g, kRedThreads, 0, s, n, w, vi, vnext, pin, gin > 0 ? gin : int(g), pout, hout);
-  return hipGetLastError();
-}
-
-hipError_t launch_mgs_normalize(int64_t n, double* w, const double* pin, double* hout, hipStream_t s, int gj,
-                                int gm, double* H, double* cs, double* sn, double* gg, double* st, float* wc) {
+hipError_t launch_mgs_normalize(int64_t n, double* w, const double* pin, int gin, double* hout, hipStream_t s,
+                                int gj, int gm, double* H, double* cs, double* sn, double* gg, double* st, float* wc) {
   const unsigned g = vec_grid(n);
   GivensArgs gv{gj, gm, H, cs, sn, gg, st};
-  hipLaunchKernelGGL(k_mgs_normalize, g, kRedThreads, 0, s, n, w, pin, int(g), hout, gv, wc);
+  hipLaunchKernelGGL(k_mgs_normalize, g, kRedThreads, 0, s, n, w, pin, gin, hout, gv, wc);
   return hipGetLastError();
 }
 

@@ -522,7 +522,9 @@ struct mg_handle : DevOwner {
   double* pbig = nullptr; // per-block partials of the outer defect norm
   double* scratch_dev = nullptr;  // this device's copy of `scratch` (device address)
   int scratch_cap = kScratchDoubles;
-  double* pv[2] = {nullptr, nullptr};   // per-block partials of the vector reductions
+  double* pv = nullptr;   // per-block partials of the vector reductions
+  double* pgs = nullptr;  // per-block partials of the Gram-Schmidt dot products
+  double* gram = nullptr; // Gram entries of the Krylov basis (launch_gram_schmidt)
   int* dflag = nullptr;
   bool fuse2z = true;     // fused first two pre-sweeps for block size 1 (MGQ1_NO_FUSE=1: off)
   // Chebyshev smoother (levels >= 1): estimated largest eigenvalue of S A per level and
@@ -1077,22 +1079,15 @@ int enqueue_fgmres_step(mg_handle* h, int j, hipStream_t s) {
   int rc;
   // the cycle-precision copy of v_j was written by the kernel that produced v_j
   if ((rc = precond(h, vj, zj, s, true))) return rc;
-  // w = A z_j together with the partial sums of (w, v_0) for the first Gram-Schmidt step
-  MG_HIP(launch_spmv(T.A64, nullptr, zj, w, nullptr, h->xk, X_F64, 0, h->pbig, s, h->V));
+  MG_HIP(launch_spmv(T.A64, nullptr, zj, w, nullptr, h->xk, X_F64, 0, nullptr, s));
   double* Hj = h->H + int64_t(j) * (m + 1);
-  // each step subtracts the projection on v_i and forms the partial dot products with
-  // v_{i+1} (or with w itself after the last step)
-  for (int i = 0; i <= j; ++i) {
-    const double* vi = h->V + int64_t(i) * N;
-    const double* vn = (i < j) ? h->V + int64_t(i + 1) * N : nullptr;
-    const double* pin = (i == 0) ? h->pbig : h->pv[i & 1];
-    MG_HIP(launch_mgs_step(N, w, vi, vn, pin, h->pv[(i + 1) & 1], Hj + i, s, i == 0 ? spmv_grid(T.A64) : 0));
-  }
+  int gn = 0;
+  MG_HIP(launch_gram_schmidt(N, j, w, h->V, h->pgs, h->gram, Hj, h->pv, &gn, s));
   // v_{j+1} = w / ||w|| (and its cycle-precision copy for step j+1), then Givens rotation
   // j, whose |g_{j+1}| and breakdown flag go straight to pinned host memory (slot j) so the
   // host can read them while step j+1 is already queued
   float* wc = h->xk == X_F64 ? nullptr : static_cast<float*>(h->bcyc);
-  MG_HIP(launch_mgs_normalize(N, w, h->pv[(j + 1) & 1], Hj + j + 1, s, j, m, h->H, h->cs, h->sn, h->g,
+  MG_HIP(launch_mgs_normalize(N, w, h->pv, gn, Hj + j + 1, s, j, m, h->H, h->cs, h->sn, h->g,
                               h->hst_dev + 2 * j, wc));
   return MG_OK;
 }
@@ -1138,8 +1133,8 @@ int solve_impl(mg_handle* h, const double* b, double* x, mg_solve_stats* st, voi
   int rc;
   // ||b|| (to dsc[4]) and the initial defect r = b - A x with ||r|| (to dsc[0]), read
   // back with one synchronisation
-  MG_HIP(launch_dot_partials(N, b, nullptr, h->pv[0], s));
-  MG_HIP(launch_finish(h->pv[0], reduction_grid(N), h->dsc + 4, 1, s));
+  MG_HIP(launch_dot_partials(N, b, nullptr, h->pv, s));
+  MG_HIP(launch_finish(h->pv, reduction_grid(N), h->dsc + 4, 1, s));
   MG_HIP(launch_spmv(T.A64, b, x, h->rout, nullptr, X_F64, X_F64, 1, h->pbig, s));
   MG_HIP(launch_finish(h->pbig, spmv_grid(T.A64), h->dsc + 0, 1, s));
   if ((rc = read_scalars(h, h->dsc, 5, s))) return rc;
@@ -1256,14 +1251,14 @@ int setup_chebyshev(mg_handle* h, hipStream_t s) {
     LevelDev& Lv = h->lv[l];
     const int64_t n = Lv.N;
     MG_HIP(launch_weyl(n, Lv.t, h->xk, s));
-    MG_HIP(launch_sumsq_partials(n, Lv.t, h->xk, h->pv[0], s));
-    MG_HIP(launch_finish(h->pv[0], reduction_grid(n), h->dsc + 6, 1, s));
+    MG_HIP(launch_sumsq_partials(n, Lv.t, h->xk, h->pv, s));
+    MG_HIP(launch_finish(h->pv, reduction_grid(n), h->dsc + 6, 1, s));
     MG_HIP(launch_scale_inv(n, Lv.x, Lv.t, h->xk, h->dsc + 6, s));
     for (int it = 0; it < c.power_its; ++it) {
       MG_HIP(launch_spmv(Lv.Ac, nullptr, Lv.x, Lv.r, nullptr, h->xk, h->xk, 0, nullptr, s));
       MG_HIP(launch_sweep0(Lv.Ac, Lv.S, Lv.r, Lv.t, 1.0, h->xk, s));
-      MG_HIP(launch_sumsq_partials(n, Lv.t, h->xk, h->pv[0], s));
-      MG_HIP(launch_finish(h->pv[0], reduction_grid(n), h->dsc + 6, 1, s));
+      MG_HIP(launch_sumsq_partials(n, Lv.t, h->xk, h->pv, s));
+      MG_HIP(launch_finish(h->pv, reduction_grid(n), h->dsc + 6, 1, s));
       MG_HIP(launch_scale_inv(n, Lv.x, Lv.t, h->xk, h->dsc + 6, s));
     }
     double lam = 0.0;
@@ -1579,8 +1574,11 @@ int setup_handle(mg_handle* h, const std::vector<HostLevel>& H, hipStream_t s) {
   int64_t maxgrid = 1;
   for (const LevelDev& D : h->lv) maxgrid = std::max<int64_t>(maxgrid, spmv_grid(D.A64));
   if ((rc = dalloc(h, &h->pbig, size_t(maxgrid)))) return rc;
-  for (int q = 0; q < 2; ++q)
-    if ((rc = dalloc(h, &h->pv[q], size_t(kMaxRedBlocks)))) return rc;
+  if ((rc = dalloc(h, &h->pv, size_t(kMaxRedBlocks)))) return rc;
+  if (c.outer == MG_OUTER_FGMRES) {
+    if ((rc = dalloc(h, &h->pgs, size_t(gs_partials_size(m))))) return rc;
+    if ((rc = dalloc(h, &h->gram, size_t(kWave) * kWave))) return rc;
+  }
   pt.mark("outer-loop storage");
   if (c.smoother == MG_SMOOTH_CHEBYSHEV && (rc = setup_chebyshev(h, s))) return rc;
   if ((rc = tune_levels(h, s))) return rc;
