@@ -82,11 +82,11 @@ def sweep_bytes(n, b, nnzb, col_bytes=4):
     return nnzb * (b * b * 8 + col_bytes) + 4 * (n + 1) + 3 * n * b * 8 + n * b * b * 8
 
 
-def dict_sweep_bytes(n, b, nnzb, col_bytes, ndict):
-    """The same sweep with the operator in the dictionary form: a 16-bit block index and
-    the column index per stored block, the distinct blocks once, vectors and smoother
-    blocks as in sweep_bytes."""
-    return nnzb * (2 + col_bytes) + ndict * b * b * 8 + 4 * (n + 1) + 3 * n * b * 8 + n * b * b * 8
+def node_sweep_bytes(n, b):
+    """The same sweep on a level that stores its distinct blocks once: x and b read, x_out
+    written, the row positions (int32) and smoother numbers (uint16).  Slices whose rows
+    do not repeat read up to 4 B per block more, which is not counted."""
+    return 3 * n * b * 8 + 6 * n
 
 
 def time_solves(torch, h, b, x, steps, warmup):
@@ -155,11 +155,13 @@ def sweep_roofline(torch, h, name, bound):
     L = h.n_levels - 1
     n, bs, nnzb = h.sizes[L]
     ksec = kernel_time(torch, h, L, n * bs)
-    kbytes = sweep_bytes(n, bs, nnzb, h.col_bytes(L))
+    node = h.dictionary_blocks(L) > 0
+    kbytes = node_sweep_bytes(n, bs) if node else sweep_bytes(n, bs, nnzb, h.col_bytes(L))
     achieved = kbytes / ksec / 1e9
     return {"bound": bound, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": counter_traffic(name),
-            "kernel": "k_sweep<B=%d,FP64> finest level" % bs, "bytes_per_launch": kbytes,
+            "kernel": "%s<B=%d,FP64> finest level" % ("k_node_sweep" if node else "k_sweep", bs),
+            "bytes_per_launch": kbytes,
             "us_per_launch": round(ksec * 1e6, 2)}
 
 
@@ -510,14 +512,14 @@ def main():
                          "setup_s": round(t_setup, 3),
                          "slot_batch_per_level": [h.tuning(l)[0] for l in range(h.n_levels)]}
         if base_prec == "fp64dict":
-            # lossless: the distinct FP64 blocks once per level, a 16-bit index per stored block
+            # lossless: the distinct FP64 blocks stored once on every level that can
             Ld = h.n_levels - 1
             nd, bsd, nnzbd = h.sizes[Ld]
             ndict = h.dictionary_blocks(Ld)
             results[prec]["dictionary_blocks_per_level"] = [h.dictionary_blocks(l) for l in range(h.n_levels)]
             if ndict:
                 ksec = kernel_time(torch, h, Ld, nd * bsd)
-                kbytes = dict_sweep_bytes(nd, bsd, nnzbd, h.col_bytes(Ld), ndict)
+                kbytes = node_sweep_bytes(nd, bsd)
                 results[prec]["finest_sweep"] = {"us_per_launch": round(ksec * 1e6, 2), "bytes_per_launch": kbytes,
                                                  "achieved_gbs": round(kbytes / ksec / 1e9, 1)}
         if sm == "cheb":
@@ -541,7 +543,7 @@ def main():
     h64 = handles["fp64"]
     L = h64.n_levels - 1
     n, bs, nnzb = h64.sizes[L]
-    op_bytes = nnzb * (bs * bs * 8 + h64.col_bytes(L))
+    op_bytes = node_sweep_bytes(n, bs) if h64.dictionary_blocks(L) else nnzb * (bs * bs * 8 + h64.col_bytes(L))
     roof = sweep_roofline(torch, h64, wl.name, "hbm" if op_bytes > CACHED_STREAM_BYTES else "mall")
     roof["copy_gbs_measured"] = round(copy_gbs, 1)
     roof["frac_of_copy"] = round(roof["achieved"] / copy_gbs, 4)

@@ -50,10 +50,12 @@ enum { MG_OUTER_IR = 0, MG_OUTER_FGMRES = 1 };
 /* smoother on levels >= 1 (the coarse MG_COARSE_SMOOTH variant always uses damped sweeps) */
 enum { MG_SMOOTH_JACOBI = 0, MG_SMOOTH_CHEBYSHEV = 1 };
 /* precision of the V-cycle; the outer defect, the update and the coarse solve are FP64.
- * MG_PREC_FP64_DICT: FP64 throughout with every level's stored blocks kept as a
- * dictionary (the distinct b x b FP64 blocks once, a 16-bit index per stored block) where
- * a level has at most 65,535 distinct blocks, else as plain FP64 values; lossless, so
- * every result is bitwise that of MG_PREC_FP64 (single-problem handles only). */
+ * Every precision stores a level's distinct blocks once (lossless: the same bits in every
+ * step, V-cycle and solve) where the level's FP64 blocks fill 16 MiB and more, at most 65,535 of
+ * them are distinct and most rows repeat whole rows (single-problem handles).
+ * MG_PREC_FP64_DICT: FP64 throughout with that form on every level of at most 65,535
+ * distinct blocks, whatever its size and repetition; every result is bitwise that of
+ * MG_PREC_FP64 (single-problem handles only). */
 enum { MG_PREC_FP64 = 0, MG_PREC_FP32 = 1, MG_PREC_FP32_F16VAL = 2, MG_PREC_FP32_BF16VAL = 3,
        MG_PREC_FP64_DICT = 4 };
 
@@ -221,7 +223,8 @@ int32_t mg_num_levels(const mg_handle* h);
  * slots each span less than 2^16 columns, the others, at most 1/8 of the slots, reading
  * 32-bit indices; else 4), and the sweep times (microseconds per
  * launch) that the setup measured for the default and the other slot batch (0 when
- * slot_batch was fixed).  Any output pointer may be NULL. */
+ * slot_batch was fixed, and on levels that store their distinct blocks once, whose kernels
+ * have one batch size).  Any output pointer may be NULL. */
 int mg_level_tuning(const mg_handle* h, int32_t level, int32_t* slot_batch, int32_t* col_bytes,
                     double* us_default, double* us_other);
 
@@ -237,8 +240,9 @@ int mg_level_tuning(const mg_handle* h, int32_t level, int32_t* slot_batch, int3
 int mg_level_transfer_format(const mg_handle* h, int32_t level, int32_t* p_col_bytes, int32_t* r_col_bytes,
                              int32_t* weight_bytes);
 
-/* Distinct blocks of level `level`'s operator in the dictionary form (MG_PREC_FP64_DICT
- * handles), or 0 when its values are stored plainly. */
+/* Distinct blocks of level `level`'s operator where they are stored once (the zero block of
+ * the padding included; 16-bit values: blocks distinct with their row exponents), or 0 when
+ * its values are stored plainly. */
 int mg_level_dictionary(const mg_handle* h, int32_t level, int32_t* n_blocks);
 
 /* Host-only structural validation of one level (and its coarser neighbour for P~);

@@ -19,8 +19,10 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB_GEN = os.path.join(HERE, "libmggen.so")
 LIB_MG = os.path.join(HERE, "libmgq1.so")
 
-HIP_SOURCES = ["mgq1_kernels.hip", "mgq1_batch.hip", "mgq1_runtime.hip", "mgq1_time.hip", "mgq1_cheb.hip",
-               "mgq1_ns.hip", "mgq1_asm.hip", "mgq1_gs.hip"]
+# (source, object, extra flags); the slice kernels are one object per block size
+HIP_UNITS = [("mgq1_slices.hip", f"mgq1_slices_b{b}", [f"-DMGQ1_B={b}"]) for b in (4, 3, 2, 1)] + \
+            [(f"mgq1_{u}.hip", f"mgq1_{u}", []) for u in ("kernels", "node", "batch", "runtime", "gs", "time", "cheb",
+                                                          "ns", "asm")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
@@ -44,9 +46,9 @@ def build_hip():
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
              "-ffp-contract=on", "-Wall", "-I", INCLUDE]
     procs, objs = [], []
-    for src in HIP_SOURCES:
-        obj = os.path.join(objdir, os.path.splitext(src)[0] + ".o")
-        cmd = [HIPCC] + flags + ["-c", os.path.join(CSRC, src), "-o", obj]
+    for src, name, extra in HIP_UNITS:
+        obj = os.path.join(objdir, name + ".o")
+        cmd = [HIPCC] + flags + extra + ["-c", os.path.join(CSRC, src), "-o", obj]
         print("+", " ".join(cmd), flush=True)
         procs.append(subprocess.Popen(cmd))
         objs.append(obj)

@@ -63,11 +63,6 @@ template <> struct Val<VK_F16> {
   }
   __device__ __forceinline__ static float dec(raw u) { return __half2float(__ushort_as_half(u)); }
 };
-// FP64 blocks from the level's dictionary (loaded in sell_batch, not through load())
-template <> struct Val<VK_DICT> {
-  using raw = double;
-  __device__ __forceinline__ static double dec(raw u) { return u; }
-};
 template <> struct Val<VK_BF16> {
   using raw = unsigned short;
   template <bool NT>
@@ -119,40 +114,15 @@ __device__ __forceinline__ void sell_batch(const SellDev& A, int k, int r, int n
   unsigned js[NB];                         // unsigned: widening needs no sign extension
   VR av[NB][B];
   XI xv[NB][B];
-  if constexpr (K == VK_DICT) {
-    // the dictionary form: column and block index first, then the block's row from the
-    // (cached) dictionary together with the x gathers
-    static_assert(NR == 1, "the dictionary form has one right-hand side");
-    unsigned short di[NB];
 #pragma unroll
-    for (int qq = 0; qq < NB; ++qq) js[qq] = slot_col<C16, NT>(A, k + qq, int64_t(k + qq) * R + r);
+  for (int qq = 0; qq < NB; ++qq) js[qq] = slot_col<C16, NT>(A, k + qq, int64_t(k + qq) * R + r);
 #pragma unroll
-    for (int qq = 0; qq < NB; ++qq) di[qq] = stream_load<NT>(A.didx + int64_t(k + qq) * R + r);
-    __builtin_amdgcn_sched_barrier(0);
-    const int c = rl % B;
-    if (A.dlds) {
-      extern __shared__ double dict_lds[];
+  for (int qq = 0; qq < NB; ++qq) {
+    const int64_t vb = int64_t(k + qq) * B * W + rl;
 #pragma unroll
-      for (int qq = 0; qq < NB; ++qq)
-#pragma unroll
-        for (int cc = 0; cc < B; ++cc) av[qq][cc] = dict_lds[(int(di[qq]) * B + c) * B + cc];
-    } else {
-#pragma unroll
-      for (int qq = 0; qq < NB; ++qq)
-#pragma unroll
-        for (int cc = 0; cc < B; ++cc) av[qq][cc] = A.dtab[(int64_t(di[qq]) * B + c) * B + cc];
-    }
-  } else {
-#pragma unroll
-    for (int qq = 0; qq < NB; ++qq) js[qq] = slot_col<C16, NT>(A, k + qq, int64_t(k + qq) * R + r);
-#pragma unroll
-    for (int qq = 0; qq < NB; ++qq) {
-      const int64_t vb = int64_t(k + qq) * B * W + rl;
-#pragma unroll
-      for (int cc = 0; cc < B; ++cc) av[qq][cc] = Val<K>::template load<NT>(A.val, vb + cc * W);
-    }
-    __builtin_amdgcn_sched_barrier(0);
+    for (int cc = 0; cc < B; ++cc) av[qq][cc] = Val<K>::template load<NT>(A.val, vb + cc * W);
   }
+  __builtin_amdgcn_sched_barrier(0);
   if constexpr (B > 1 && NR == 1) {
     // each lane gathers only its own component of the neighbour node (the B lanes of a
     // node read one contiguous B-vector together) and takes the others from its node's
@@ -179,26 +149,6 @@ __device__ __forceinline__ void sell_batch(const SellDev& A, int k, int r, int n
   for (int qq = 0; qq < NB; ++qq)
 #pragma unroll
     for (int cc = 0; cc < B; ++cc) acc += T(Val<K>::dec(av[qq][cc])) * T(xv[qq][cc]);
-}
-
-// dictionary form with dlds set: the workgroup copies the dictionary into LDS before any
-// slice work (all threads reach the barrier); launched with ndict * B * B doubles of
-// dynamic shared memory
-template <int K>
-__device__ __forceinline__ void dict_stage(const SellDev& A) {
-  if constexpr (K == VK_DICT) {
-    if (A.dlds) {
-      extern __shared__ double dict_lds[];
-      const int n = A.ndict * A.B * A.B;
-      for (int i = int(threadIdx.x); i < n; i += int(blockDim.x)) dict_lds[i] = A.dtab[i];
-      __syncthreads();
-    }
-  }
-}
-
-template <int K>
-inline size_t dict_lds_bytes(const SellDev& A) {
-  return (K == VK_DICT && A.dlds) ? size_t(A.ndict) * A.B * A.B * sizeof(double) : 0;
 }
 
 // The same batch for the second of two sweeps from x = 0 with b = 1: the iterate after the
@@ -650,6 +600,27 @@ template <int B, class X, class T, bool MC, int MODE>
 __global__ __launch_bounds__(kThreads) void k_tnode(TSellDev M, const X* __restrict__ in, X* __restrict__ out) {
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
   tnode_lane<B, X, T, MC, MODE>(M, bid * kSliceWaves + threadIdx.x / kWave, threadIdx.x % kWave, in, out);
+}
+
+// Gauss-Jordan with row pivoting on [M | I]; the right half becomes the inverse.  false: singular
+template <int B>
+__device__ __forceinline__ bool invert_augmented(double (&m)[B][2 * B]) {
+  for (int k = 0; k < B; ++k) {
+    int p = k;
+    for (int i = k + 1; i < B; ++i)
+      if (fabs(m[i][k]) > fabs(m[p][k])) p = i;
+    if (m[p][k] == 0.0) return false;
+    if (p != k)
+      for (int c = 0; c < 2 * B; ++c) { const double t = m[k][c]; m[k][c] = m[p][c]; m[p][c] = t; }
+    const double inv = 1.0 / m[k][k];
+    for (int c = 0; c < 2 * B; ++c) m[k][c] *= inv;
+    for (int i = 0; i < B; ++i) {
+      if (i == k) continue;
+      const double f = m[i][k];
+      for (int c = 0; c < 2 * B; ++c) m[i][c] -= f * m[k][c];
+    }
+  }
+  return true;
 }
 
 inline unsigned grid_for(int64_t n, int threads) { return unsigned((n + threads - 1) / threads); }

@@ -8,7 +8,7 @@
 namespace mgq1 {
 
 // storage kind of matrix values
-enum ValKind { VK_F64 = 0, VK_F32 = 1, VK_F16 = 2, VK_BF16 = 3, VK_DICT = 4 };
+enum ValKind { VK_F64 = 0, VK_F32 = 1, VK_F16 = 2, VK_BF16 = 3 };
 // storage kind of vectors
 enum VecKind { X_F64 = 0, X_F32 = 1 };
 
@@ -16,6 +16,8 @@ constexpr int kWave = 64;             // wavefront width on CDNA
 constexpr int kSliceWaves = 4;        // slices (one per wave) per 256-thread workgroup
 constexpr int kRedThreads = 1024;
 constexpr int kMaxRedBlocks = 2048;   // grid (= partial count) of the vector reductions
+
+struct NodeDev;
 
 // Sliced ELL of a block matrix: one slice = 64 lanes = R = 64/B nodes x B components;
 // lane = r*B + c handles scalar row (node slice*R + r, component c).  For block slot k of
@@ -40,12 +42,37 @@ struct SellDev {
   const int32_t* perm = nullptr;    // node at row position slice*R + r (NULL: the position
                                     // itself); rows sorted by length inside windows of slices
   int nt = 1;                       // 1: values and indices read with non-temporal loads
-  // kind VK_DICT: the block of node row r in slot k is dtab[didx[k * R + r]] (ndict
-  // distinct B x B FP64 blocks, row-major); val is not read
+  const NodeDev* node = nullptr;    // host: the level is stored in the node form instead (the
+                                    // sliced arrays above are then absent)
+};
+
+// Node form of an operator whose rows repeat: slices of 64 nodes, lane = node, the distinct
+// B x B blocks stored once.  A slice's descriptor is {width, flags, iv, ic}:
+//   kNodeValUniform  every row of the slice has the same blocks, those of slots iv .. of vtab
+//                    (B * B values each); else didx[(iv + k) * 64 + lane] names the block of
+//                    slot k in dtab
+//   kNodeColUniform  the column of slot k is the row's node + opat[ic + k]; else it is
+//                    base[ic + k] + col16[(ic + k) * 64 + lane], or (kNodeCol32)
+//                    col32[(ic + k) * 64 + lane]
+// Rows past the end repeat the last row's node.  Padding slots of a shorter row hold the zero
+// block (number 0) and the row's own node.
+enum { kNodeValUniform = 1, kNodeColUniform = 2, kNodeCol32 = 4 };
+struct NodeDev {
+  int32_t n = 0, B = 1, nslices = 0;
+  int tk = X_F64;                   // type of the block tables: that of the row sums
+  const int32_t* desc = nullptr;    // nslices * 4
+  const int32_t* perm = nullptr;    // node at each row position (NULL: the position itself)
+  const void* vtab = nullptr;       // blocks of the distinct uniform rows, row after row
+  const void* dtab = nullptr;       // the distinct blocks, row-major
+  const int32_t* opat = nullptr;
   const uint16_t* didx = nullptr;
-  const double* dtab = nullptr;
-  int32_t ndict = 0;
-  int dlds = 0;                     // VK_DICT: every workgroup first copies dtab into LDS
+  const uint16_t* col16 = nullptr;
+  const int32_t* base = nullptr;
+  const int32_t* col32 = nullptr;
+  const int8_t* rexp = nullptr;     // n * B power-of-two row exponents by row position, or NULL
+  const uint16_t* sidx = nullptr;   // smoother block of each row position in stab (NULL: sfull)
+  const void* stab = nullptr;       // the distinct smoother blocks, cycle type
+  const void* sfull = nullptr;      // smoother block of every node (B = 1 always; else with no sidx)
 };
 
 // the two slot-batch sizes the slice kernels are built for (default, alternative)
@@ -110,12 +137,36 @@ struct TailParams {
 };
 
 // ------------------------------------------------------------------ launchers
+// operators in the node form; arguments as launch_spmv, launch_sweep, launch_sweep0 and
+// launch_sweep2z (which call these for an operator with A.node set)
+hipError_t launch_node_spmv(const NodeDev& A, const void* b, const void* x, void* y, const uint8_t* mask, int xk,
+                            int yk, int mode, double* partials, hipStream_t s);
+hipError_t launch_node_sweep(const NodeDev& A, const void* b, const void* x, void* xo, double omega, int xk,
+                             hipStream_t s, double beta, int pmode);
+hipError_t launch_node_sweep0(const NodeDev& A, const void* b, void* xo, double omega, int xk, hipStream_t s);
+hipError_t launch_node_sweep2z(const NodeDev& A, const void* b, void* xo, double omega, int xk, hipStream_t s);
+// inverses of nb FP64 B x B blocks in double or float (sk); *flag = 1 if one is singular
+hipError_t launch_invert_blocks(int nb, int B, const double* blocks, void* out, int sk, int* flag, hipStream_t s);
+// S[node] = stab[sidx[pos]], node = perm[pos] (perm NULL: pos)
+hipError_t launch_expand_smoother(int n, int B, const int32_t* perm, const uint16_t* sidx, const void* stab, void* S,
+                                  int sk, hipStream_t s);
 // y = A x (mode 0), y = b - A x (mode 1), y = M (b - A x) with M zeroing constrained
 // DoFs (mode 2); with `partials` != NULL every block also writes the sum of squares of
 // its y entries to partials[block] (spmv_grid(A) entries).  xk / yk: vector kinds.
 hipError_t launch_spmv(const SellDev& A, const void* b, const void* x, void* y, const uint8_t* mask,
                        int xk, int yk, int mode, double* partials, hipStream_t s);
 int spmv_grid(const SellDev& A);
+// the sliced-ELL forms of launch_spmv, launch_sweep, launch_sweep0 and launch_sweep2z for one
+// block size
+template <int B>
+hipError_t spmv_block(const SellDev& A, const void* b, const void* x, void* y, const uint8_t* mask, int xk, int yk,
+                      int mode, double* partials, hipStream_t s);
+template <int B>
+hipError_t sweep_block(const SellDev& A, const void* S, const void* b, const void* x, void* xo, double omega,
+                       double beta, int pmode, int xk, hipStream_t s);
+template <int B>
+hipError_t sweep0_block(const SellDev& A, const void* S, const void* b, void* xo, double omega, int xk, hipStream_t s);
+hipError_t sweep2z_block(const SellDev& A, const void* S, const void* b, void* xo, double omega, int xk, hipStream_t s);
 // x_out = x + omega S (b - A x); S in lane layout, same kind as the vectors.  pmode 1:
 // also + beta (x - x_prev) with x_prev read from xo before it is overwritten (three-term
 // Chebyshev step); pmode 2: + beta x (x_prev = 0)

@@ -9,6 +9,7 @@
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <numeric>
@@ -19,6 +20,7 @@
 
 #include "../../include/mgq1.h"
 #include "mgq1_internal.h"
+#include "mgq1_nodebuild.h"
 
 #include <cstdio>
 
@@ -243,6 +245,19 @@ uint16_t to_bf16_bits(double v) {
   uint32_t u;
   std::memcpy(&u, &f, 4);
   return uint16_t(u >> 16);
+}
+
+// the FP32 values of the stored 16-bit codes (exact)
+float f16_value(uint16_t u) {
+  const int e = (u >> 10) & 31, m = u & 0x3ff;
+  const float v = e == 31 ? (m ? NAN : INFINITY) : e ? std::ldexp(float(m | 0x400), e - 25) : std::ldexp(float(m), -24);
+  return (u & 0x8000) ? -v : v;
+}
+float bf16_value(uint16_t u) {
+  const uint32_t w = uint32_t(u) << 16;
+  float f;
+  std::memcpy(&f, &w, 4);
+  return f;
 }
 
 struct HostSell {
@@ -500,6 +515,11 @@ struct LevelDev {
   // host copies of the operator's geometry (single-problem handles): BSR row pointers,
   // slice pointers and row positions of the sliced layout, to map stored values back
   std::vector<int32_t> hrow, hsptr, hperm;
+  // node form (single-problem handles): host description, FP64 and cycle operators
+  std::unique_ptr<NodeHost> nh;
+  std::unique_ptr<NodeDev> n64, nc;
+  std::vector<int8_t> hexp;         // row exponents (FP16 / BF16 values)
+  std::vector<uint16_t> hcode;      // 16-bit codes of the distinct blocks (FP16 / BF16 values)
 };
 
 struct mg_handle : DevOwner {
@@ -688,103 +708,162 @@ int upload_sell(DevOwner* h, const HostSell& S, int kind, SellDev& D, hipStream_
   return MG_OK;
 }
 
-// Dictionary form of a level's FP64 blocks (MG_PREC_FP64_DICT): the distinct B x B blocks
-// of the sliced layout once (padding blocks are zero blocks), a 16-bit index per slot and
-// node row.  Applied when the level has at most 65,535 distinct blocks (blocks compare
-// bitwise); the kernels then read the same doubles, so every result has the same bits.
-struct BlockKey {
-  uint64_t w[16];
-  int n;
-  bool operator==(const BlockKey& o) const {
-    for (int i = 0; i < n; ++i)
-      if (w[i] != o.w[i]) return false;
-    return true;
-  }
-};
-struct BlockHash {
-  size_t operator()(const BlockKey& k) const {
-    uint64_t x = 1469598103934665603ull;
-    for (int i = 0; i < k.n; ++i) {
-      x ^= k.w[i] + 0x9e3779b97f4a7c15ull + (x << 6) + (x >> 2);
-      x *= 1099511628211ull;
-    }
-    return size_t(x ^ (x >> 29));
-  }
-};
+// Which levels take the node form (besides all that can on a MG_PREC_FP64_DICT handle): those
+// whose FP64 blocks would fill kNodeFormBytes and more.  Smaller levels wait for memory
+// latency, not bytes, and the node form's descriptor is one more dependent load in their
+// chain.  MGQ1_NODE_FORM=1 / =0: every level that can / none (tests; the V-cycle's bits are
+// the same).
+constexpr int64_t kNodeFormBytes = int64_t(16) << 20;
 
-int upload_dict(DevOwner* h, const HostSell& S, SellDev& D, hipStream_t s, bool* applied) {
+bool want_node(const HostLevel& L, int64_t tail_dofs, bool* must) {
+  if (int64_t(L.n) * L.B <= tail_dofs) return false;       // the single-workgroup tail reads sliced ELL
+  if (const char* e = std::getenv("MGQ1_NODE_FORM")) {
+    *must = std::atoi(e) != 0;
+    return *must;
+  }
+  return L.nnzb * L.B * L.B * 8 >= kNodeFormBytes;
+}
+
+// The node form of level L (NodeDev): D.A64 and D.Ac with their smoother blocks.  *applied
+// tells whether the operator qualified; must: a MG_PREC_FP64_DICT handle, which takes it with
+// any share of general slices.
+int setup_node(DevOwner* h, const HostLevel& L, int vkind, int xk, bool must, int* flag, hipStream_t s, LevelDev& D,
+               bool* applied) {
   *applied = false;
-  const int B = S.B, BB = B * B, W = S.W, R = S.R;
-  if (BB > 16 || W != kWave) return MG_OK;
-  const int64_t nblk = S.slots * R;
-  auto key_at = [&](int64_t e, BlockKey& key) {
-    const int64_t k = e / R, r = e % R;
-    key.n = BB;
-    for (int c = 0; c < B; ++c)
-      for (int cc = 0; cc < B; ++cc) {
-        const double v = S.val[size_t((k * B + cc) * W + r * B + c)];
-        std::memcpy(&key.w[c * B + cc], &v, 8);
-      }
-  };
-  constexpr size_t kMaxDict = 65535;
-  // pass 1: distinct blocks per chunk, in first-seen order
-  const int64_t nchunk = 64;
-  const int64_t per = (nblk + nchunk - 1) / nchunk;
-  std::vector<std::vector<BlockKey>> seen(static_cast<size_t>(nchunk));
-  std::vector<int> bad(size_t(nchunk), 0);
-  parallel_for(nchunk, 1, [&](int64_t c0, int64_t c1) {
-    for (int64_t c = c0; c < c1; ++c) {
-      try {
-        std::unordered_map<BlockKey, uint32_t, BlockHash> m;
-        BlockKey key;
-        for (int64_t e = c * per; e < std::min(nblk, (c + 1) * per); ++e) {
-          key_at(e, key);
-          if (m.emplace(key, uint32_t(m.size())).second) {
-            seen[size_t(c)].push_back(key);
-            if (m.size() > kMaxDict) { bad[size_t(c)] = 1; break; }
-          }
+  const int B = L.B, BB = B * B;
+  const bool coded = vkind == VK_F16 || vkind == VK_BF16;
+  std::vector<int8_t> rexp;
+  if (coded) {
+    rexp.assign(size_t(L.n) * B, 0);
+    parallel_for(L.n, 1 << 14, [&](int64_t a, int64_t b) {
+      for (int64_t i = a; i < b; ++i)
+        for (int c = 0; c < B; ++c) {
+          double mx = 0.0;
+          for (int64_t k = L.rowptr[i]; k < L.rowptr[i + 1]; ++k)
+            for (int cc = 0; cc < B; ++cc) mx = std::max(mx, std::fabs(L.val[size_t(k) * BB + c * B + cc]));
+          rexp[size_t(i) * B + c] = int8_t(row_exponent(mx));
         }
-      } catch (...) {
-        bad[size_t(c)] = 2;
-      }
-    }
-  });
-  for (int b : bad)
-    if (b == 2) return fail(MG_ENOMEM, "host allocation failed (block dictionary)");
-  for (int b : bad)
-    if (b) return MG_OK;                           // too many distinct blocks: plain values
-  std::unordered_map<BlockKey, uint32_t, BlockHash> dict;
-  std::vector<double> tab;
-  for (const auto& v : seen)
-    for (const BlockKey& key : v)
-      if (dict.emplace(key, uint32_t(dict.size())).second) {
-        if (dict.size() > kMaxDict) return MG_OK;
-        for (int i = 0; i < BB; ++i) {
-          double d;
-          std::memcpy(&d, &key.w[i], 8);
-          tab.push_back(d);
-        }
-      }
-  // pass 2: the index of every block (read-only lookups)
-  std::vector<uint16_t> idx(static_cast<size_t>(nblk));
-  parallel_for(nblk, 1 << 16, [&](int64_t a, int64_t b) {
-    BlockKey key;
-    for (int64_t e = a; e < b; ++e) {
-      key_at(e, key);
-      idx[size_t(e)] = uint16_t(dict.find(key)->second);
-    }
-  });
+    });
+  }
+  auto H = std::make_unique<NodeHost>();
+  const bool ok = build_node(L.n, B, L.rowptr.data(), L.col.data(), L.val.data(), coded ? rexp.data() : nullptr, must,
+                             [](int64_t n, int64_t c, auto&& f) { parallel_for(n, c, f); }, *H);
+  if (!ok) return MG_OK;
+  NodeDev N;
+  N.n = L.n;
+  N.B = B;
+  N.nslices = H->nslices;
   int rc;
-  uint16_t* di;
-  double* dt;
-  if ((rc = upload(h, &di, idx, s)) || (rc = upload(h, &dt, tab, s))) return rc;
+  auto put = [&](auto& dst, const auto& src) -> int {
+    using T = std::remove_const_t<std::remove_pointer_t<std::remove_reference_t<decltype(dst)>>>;
+    T* p = nullptr;
+    const int e = src.empty() ? MG_OK : upload(h, &p, src, s);
+    dst = p;
+    return e;
+  };
+  if ((rc = put(N.desc, H->desc)) || (rc = put(N.perm, H->perm)) || (rc = put(N.opat, H->opat)) ||
+      (rc = put(N.didx, H->didx)) || (rc = put(N.col16, H->col16)) || (rc = put(N.base, H->base)) ||
+      (rc = put(N.col32, H->col32)))
+    return rc;
+  // block tables: FP64, and in the cycle's type the values the reduced formats decode to
+  auto rows_of = [&](const auto& tab) {
+    std::remove_cv_t<std::remove_reference_t<decltype(tab)>> v(H->vlist.size() * size_t(BB));
+    for (size_t q = 0; q < H->vlist.size(); ++q)
+      for (int z = 0; z < BB; ++z) v[q * BB + z] = tab[size_t(H->vlist[q]) * BB + z];
+    return v;
+  };
+  auto tables = [&](NodeDev& M, const auto& tab) -> int {
+    using T = std::remove_cv_t<std::remove_reference_t<decltype(tab[0])>>;
+    T *dt, *vt;
+    const auto rows = rows_of(tab);
+    int e;
+    if ((e = upload(h, &dt, tab, s)) || (e = upload(h, &vt, rows, s))) return e;
+    MG_HIP(hipStreamSynchronize(s));
+    M.dtab = dt;
+    M.vtab = vt;
+    M.tk = sizeof(T) == 8 ? X_F64 : X_F32;
+    return MG_OK;
+  };
+  D.n64 = std::make_unique<NodeDev>(N);
+  D.nc = std::make_unique<NodeDev>(N);
+  if ((rc = tables(*D.n64, H->dict))) return rc;
+  if (vkind == VK_F64) {
+    *D.nc = *D.n64;
+  } else {
+    std::vector<float> f(H->dict.size());
+    if (coded) D.hcode.assign(H->dict.size(), 0);
+    for (size_t q = 0; q < f.size(); ++q) {
+      if (!coded) {
+        f[q] = float(H->dict[q]);
+        continue;
+      }
+      const double sc = std::ldexp(H->dict[q], -int(H->dexp[q / BB * B + q % BB / B]));
+      const uint16_t u = vkind == VK_F16 ? to_f16_bits(sc) : to_bf16_bits(sc);
+      D.hcode[q] = u;
+      f[q] = vkind == VK_F16 ? f16_value(u) : bf16_value(u);
+    }
+    if ((rc = tables(*D.nc, f))) return rc;
+    if (coded) {
+      std::vector<int8_t> pe(size_t(L.n) * B);
+      for (int64_t pos = 0; pos < L.n; ++pos)
+        for (int c = 0; c < B; ++c) pe[size_t(pos) * B + c] = rexp[size_t(H->node_at(pos)) * B + c];
+      int8_t* p;
+      if ((rc = upload(h, &p, pe, s))) return rc;
+      MG_HIP(hipStreamSynchronize(s));
+      D.nc->rexp = p;
+      D.hexp = std::move(rexp);
+    }
+  }
+  // smoother blocks in the cycle's type: the caller's per node; the inverses of the distinct
+  // diagonal blocks, looked up per row (one component: spread over the nodes, so that the
+  // fused first sweeps can gather them)
+  char* st = nullptr;
+  if (!L.sblk.empty()) {
+    if (xk == X_F64) {
+      double* p;
+      if ((rc = upload(h, &p, L.sblk, s))) return rc;
+      D.nc->sfull = p;
+    } else {
+      const std::vector<float> f(L.sblk.begin(), L.sblk.end());
+      float* p;
+      if ((rc = upload(h, &p, f, s))) return rc;
+      MG_HIP(hipStreamSynchronize(s));
+      D.nc->sfull = p;
+    }
+  } else {
+    const int nb = int(H->sblock.size());
+    std::vector<double> blocks(size_t(nb) * BB);
+    for (int q = 0; q < nb; ++q)
+      for (int z = 0; z < BB; ++z) blocks[size_t(q) * BB + z] = H->dict[size_t(H->sblock[size_t(q)]) * BB + z];
+    double* bl;
+    uint16_t* si;
+    if ((rc = upload(h, &bl, blocks, s)) || (rc = upload(h, &si, H->sidx, s))) return rc;
+    if ((rc = dalloc(h, &st, size_t(nb) * BB * xsize(xk)))) return rc;
+    MG_HIP(launch_invert_blocks(nb, B, bl, st, xk, flag, s));
+    if (B == 1) {
+      char* sf;
+      if ((rc = dalloc(h, &sf, size_t(L.n) * xsize(xk)))) return rc;
+      MG_HIP(launch_expand_smoother(L.n, B, N.perm, si, st, sf, xk, s));
+      D.nc->sfull = sf;
+    } else {
+      D.nc->sidx = si;
+      D.nc->stab = st;
+    }
+    MG_HIP(hipStreamSynchronize(s));
+  }
   MG_HIP(hipStreamSynchronize(s));
-  D.kind = VK_DICT;
-  D.didx = di;
-  D.dtab = dt;
-  D.ndict = int32_t(dict.size());
-  D.dlds = tab.size() * sizeof(double) <= 16384 ? 1 : 0;     // small tables: one LDS copy per workgroup
-  D.nt = stream_nt(int64_t(S.col.size()) * (D.col16 ? 2 : 4) + nblk * 2);
+  for (SellDev* A : {&D.A64, &D.Ac}) {
+    A->n = L.n;
+    A->B = B;
+    A->R = kWave / B;
+    A->nslices = (L.n + A->R - 1) / A->R;
+  }
+  D.A64.kind = VK_F64;
+  D.Ac.kind = vkind;
+  D.A64.node = D.n64.get();
+  D.Ac.node = D.nc.get();
+  D.hperm = H->perm;
+  D.nh = std::move(H);
   *applied = true;
   return MG_OK;
 }
@@ -1059,12 +1138,25 @@ int read_scalars(mg_handle* h, const double* d, int k, hipStream_t s) {
   return MG_OK;
 }
 
-// r = b - A x, h->hs[0] = ||r||
-int outer_defect(mg_handle* h, const double* b, const double* x, hipStream_t s) {
+// r = b - A x, dsc[0] = ||r||.  FGMRES divides by the norm: there it is summed over the
+// vector in an order that does not depend on the operator's storage, so that every form of
+// the operator gives the solve the same bits; the MG iteration only compares it.
+int enqueue_defect(mg_handle* h, const double* b, const double* x, hipStream_t s) {
   LevelDev& T = h->lv[h->L];
-  MG_HIP(launch_spmv(T.A64, b, x, h->rout, nullptr, X_F64, X_F64, 1, h->pbig, s));
-  MG_HIP(launch_finish(h->pbig, spmv_grid(T.A64), h->dsc + 0, 1, s));
-  return read_scalars(h, h->dsc, 1, s);
+  if (h->cfg.outer == MG_OUTER_FGMRES) {
+    MG_HIP(launch_spmv(T.A64, b, x, h->rout, nullptr, X_F64, X_F64, 1, nullptr, s));
+    MG_HIP(launch_dot_partials(T.N, h->rout, nullptr, h->pv, s));
+    MG_HIP(launch_finish(h->pv, reduction_grid(T.N), h->dsc + 0, 1, s));
+  } else {
+    MG_HIP(launch_spmv(T.A64, b, x, h->rout, nullptr, X_F64, X_F64, 1, h->pbig, s));
+    MG_HIP(launch_finish(h->pbig, spmv_grid(T.A64), h->dsc + 0, 1, s));
+  }
+  return MG_OK;
+}
+
+int outer_defect(mg_handle* h, const double* b, const double* x, hipStream_t s) {
+  const int rc = enqueue_defect(h, b, x, s);
+  return rc ? rc : read_scalars(h, h->dsc, 1, s);
 }
 
 // One FGMRES step j on internal buffers: z_j = V(v_j), w = A z_j, modified Gram-Schmidt
@@ -1135,9 +1227,7 @@ int solve_impl(mg_handle* h, const double* b, double* x, mg_solve_stats* st, voi
   // back with one synchronisation
   MG_HIP(launch_dot_partials(N, b, nullptr, h->pv, s));
   MG_HIP(launch_finish(h->pv, reduction_grid(N), h->dsc + 4, 1, s));
-  MG_HIP(launch_spmv(T.A64, b, x, h->rout, nullptr, X_F64, X_F64, 1, h->pbig, s));
-  MG_HIP(launch_finish(h->pbig, spmv_grid(T.A64), h->dsc + 0, 1, s));
-  if ((rc = read_scalars(h, h->dsc, 5, s))) return rc;
+  if ((rc = enqueue_defect(h, b, x, s)) || (rc = read_scalars(h, h->dsc, 5, s))) return rc;
   const double bn = h->hs[4];
   const double tol = c.rtol * bn;
   const int limit = fixed > 0 ? fixed : c.maxit;
@@ -1326,7 +1416,7 @@ struct PhaseTimer {
 // per-DoF form
 int setup_level(DevOwner* h, const HostLevel& L, bool has_p, int NR, int vkind, int xk, bool vectors, int* flag,
                 hipStream_t s, LevelDev& D, bool single = false, const HostLevel* coarser = nullptr,
-                bool dict = false) {
+                bool dict = false, int64_t tail_dofs = 0) {
   const bool keep_host = single;
   int rc;
   D.n = L.n;
@@ -1334,6 +1424,13 @@ int setup_level(DevOwner* h, const HostLevel& L, bool has_p, int NR, int vkind, 
   D.N = int64_t(L.n) * L.B;
   D.nnzb = L.nnzb;
   PhaseTimer pt;
+  bool node = false;
+  bool must = dict;
+  if (single && NR == 1 && (dict || want_node(L, tail_dofs, &must))) {
+    if ((rc = setup_node(h, L, vkind, xk, must, flag, s, D, &node))) return rc;
+    pt.mark("  node form");
+  }
+  if (!node) {
   HostSell S = build_sell(L, NR);
   pt.mark("  sliced layout");
   if ((rc = upload_sell(h, S, VK_F64, D.A64, s))) return rc;
@@ -1369,21 +1466,13 @@ int setup_level(DevOwner* h, const HostLevel& L, bool has_p, int NR, int vkind, 
     }
   }
   if (keep_host) {
-    D.hrow = L.rowptr;
     D.hsptr = S.sptr;
     D.hperm = S.perm;
   }
-  if ((rc = upload(h, &D.mask, L.mask, s))) return rc;
-  pt.mark("  smoother blocks and mask");
-  if (dict && NR == 1) {
-    // the smoother blocks above were computed from the plain FP64 values; from here on the
-    // level's kernels read the dictionary form of the same values
-    MG_HIP(hipStreamSynchronize(s));
-    bool ok = false;
-    if ((rc = upload_dict(h, S, D.A64, s, &ok))) return rc;
-    if (ok) D.Ac = D.A64;
-    pt.mark("  block dictionary");
+  pt.mark("  smoother blocks");
   }
+  if (keep_host) D.hrow = L.rowptr;
+  if ((rc = upload(h, &D.mask, L.mask, s))) return rc;
   if (has_p) {
     CsrHost P;
     P.nrows = L.n;
@@ -1457,10 +1546,7 @@ int tune_levels(mg_handle* h, hipStream_t s) {
     slot_batch_choices(D.B, &kd, &ko);
     if (req != 0 && req != kd && req != ko)
       return fail(MG_EINVAL, "slot_batch must be 0 or one of the two batch sizes built for this block size");
-    if (req != 0) {
-      D.Ac.kb = D.A64.kb = req;
-      continue;
-    }
+    D.Ac.kb = D.A64.kb = req != 0 ? req : kd;
   }
   if (req != 0) return MG_OK;
   hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -1478,6 +1564,7 @@ int tune_levels(mg_handle* h, hipStream_t s) {
   const double omega = h->cfg.omega;
   for (size_t l = 0; l < h->lv.size() && rc == MG_OK; ++l) {
     LevelDev& D = h->lv[l];
+    if (D.Ac.node) continue;             // one batch size
     int kb[2];
     slot_batch_choices(D.B, &kb[0], &kb[1]);
     if ((rc = launch_fill(D.N, D.x, h->xk, 1.0, s) == hipSuccess ? MG_OK : MG_EDEVICE)) break;
@@ -1499,7 +1586,7 @@ int tune_levels(mg_handle* h, hipStream_t s) {
     D.us_def = 100.0 * best[0];          // ms per 10 launches -> us per launch
     D.us_alt = 100.0 * best[1];
   }
-  if (rc == MG_OK && h->xk != X_F64) {
+  if (rc == MG_OK && h->xk != X_F64 && !h->lv[h->L].A64.node) {
     // FP64 outer defect of a mixed-precision handle: r = b - A x with norm partials
     LevelDev& T = h->lv[h->L];
     int kb[2];
@@ -1539,9 +1626,11 @@ int setup_handle(mg_handle* h, const std::vector<HostLevel>& H, hipStream_t s) {
   h->dflag = flag;
   MG_HIP(hipMemsetAsync(flag, 0, sizeof(int), s));
   const int vkind = value_kind(c.precision);
+  int64_t tail_dofs = 0;
+  if (const char* e = std::getenv("MGQ1_TAIL_DOFS")) tail_dofs = std::atoll(e);
   for (int l = 0; l < n_levels; ++l) {
     if ((rc = setup_level(h, H[l], l > 0, 1, vkind, h->xk, true, flag, s, h->lv[l], true,
-                          l > 0 ? &H[l - 1] : nullptr, c.precision == MG_PREC_FP64_DICT)))
+                          l > 0 ? &H[l - 1] : nullptr, c.precision == MG_PREC_FP64_DICT, tail_dofs)))
       return rc;
     if (pt.on) MG_HIP(hipStreamSynchronize(s));
     pt.mark("level", l);
@@ -1585,12 +1674,9 @@ int setup_handle(mg_handle* h, const std::vector<HostLevel>& H, hipStream_t s) {
   pt.mark("Chebyshev bounds and slot-batch timing");
   if (const char* e = std::getenv("MGQ1_NO_FUSE")) h->fuse2z = std::atoi(e) == 0;
   if (c.smoother == MG_SMOOTH_CHEBYSHEV) h->fuse2z = false;   // the fused pair is two Jacobi sweeps
-  if (c.precision == MG_PREC_FP64_DICT) h->fuse2z = false;     // the fused pair reads plain values
   // tail: every level up to the largest one with at most tail_dofs unknowns.  Default off:
   // on MI355X one workgroup walking several levels was measured slower (dependent-load
   // latency serialises) than separate grid launches per step.
-  int64_t tail_dofs = 0;
-  if (const char* e = std::getenv("MGQ1_TAIL_DOFS")) tail_dofs = std::atoll(e);
   int top = 0;
   for (int l = 1; l <= h->L; ++l)
     if (h->lv[l].N <= tail_dofs) top = l;
@@ -2691,9 +2777,10 @@ int mg_outer_defect_noalloc(mg_handle* h, const double* b, const double* x, doub
   if (static_cast<const void*>(r) == static_cast<const void*>(x) || static_cast<const void*>(r) == static_cast<const void*>(b))
     return fail(MG_EINVAL, "r must not alias b or x");
   LevelDev& T = h->lv[h->L];
-  const int g = spmv_grid(T.A64);
-  if (g > h->scratch_cap)
-    return fail(MG_EUNSUPPORTED, "the finest level needs " + std::to_string(g) + " partial sums; the static scratch array holds " +
+  // the limit is that of the sliced-ELL form whatever the level's storage
+  const int need = (T.A64.nslices + kSliceWaves - 1) / kSliceWaves, g = spmv_grid(T.A64);
+  if (need > h->scratch_cap)
+    return fail(MG_EUNSUPPORTED, "the finest level needs " + std::to_string(need) + " partial sums; the static scratch array holds " +
                                      std::to_string(h->scratch_cap));
   hipStream_t s = static_cast<hipStream_t>(stream);
   // every workgroup writes its own partial and the finish kernel reads exactly g of them,
@@ -2813,10 +2900,29 @@ int mg_level_export(const mg_handle* h, int32_t level, void* values, int8_t* row
   const LevelDev& L = h->lv[level];
   const SellDev& A = L.Ac;
   if (L.hrow.empty()) return fail(MG_EUNSUPPORTED, "no host geometry kept for this level");
-  if (A.kind == VK_DICT) return fail(MG_EUNSUPPORTED, "the level's values are stored as a block dictionary");
+  if (A.node && h->cfg.precision == MG_PREC_FP64_DICT)
+    return fail(MG_EUNSUPPORTED, "the level's values are stored as a block dictionary");
   if ((A.kind == VK_F16 || A.kind == VK_BF16) && !row_exp) return fail(MG_EINVAL, "row_exp is required for 16-bit values");
   const int B = L.B, W = kWave, R = A.R;
   const int vb = A.kind == VK_F64 ? 8 : A.kind == VK_F32 ? 4 : 2;
+  if (A.node) {
+    const NodeHost& H = *L.nh;
+    const int BB = B * B;
+    for (int64_t pos = 0; pos < L.n; ++pos) {
+      const int32_t node = H.node_at(pos);
+      for (int32_t k = 0; k < L.hrow[size_t(node) + 1] - L.hrow[size_t(node)]; ++k) {
+        const size_t src = size_t(H.block_at(pos / kWave, k, int32_t(pos % kWave))) * BB;
+        const size_t dst = (size_t(L.hrow[size_t(node)]) + k) * BB;
+        for (int z = 0; z < BB; ++z) {
+          if (vb == 8) static_cast<double*>(values)[dst + z] = H.dict[src + z];
+          else if (vb == 4) static_cast<float*>(values)[dst + z] = float(H.dict[src + z]);
+          else static_cast<uint16_t*>(values)[dst + z] = L.hcode[src + z];
+        }
+      }
+    }
+    if (vb == 2) std::copy(L.hexp.begin(), L.hexp.end(), row_exp);
+    return MG_OK;
+  }
   const int64_t slots = L.hsptr.back();
   std::vector<char> dv(size_t(slots) * B * W * vb);
   MG_HIP(hipMemcpy(dv.data(), A.val, dv.size(), hipMemcpyDeviceToHost));
@@ -2860,7 +2966,7 @@ int mg_level_tuning(const mg_handle* h, int32_t level, int32_t* slot_batch, int3
   int kd, ko;
   slot_batch_choices(L.B, &kd, &ko);
   if (slot_batch) *slot_batch = L.Ac.kb ? L.Ac.kb : kd;
-  if (col_bytes) *col_bytes = L.A64.col16 ? 2 : 4;
+  if (col_bytes) *col_bytes = L.A64.col16 || L.A64.node ? 2 : 4;
   if (us_default) *us_default = L.us_def;
   if (us_other) *us_other = L.us_alt;
   return MG_OK;
@@ -2879,8 +2985,8 @@ int mg_level_transfer_format(const mg_handle* h, int32_t level, int32_t* p_col_b
 
 int mg_level_dictionary(const mg_handle* h, int32_t level, int32_t* n_blocks) {
   if (!h || !n_blocks || level < 0 || level > h->L) return fail(MG_EINVAL, "bad handle, level or output");
-  const SellDev& A = h->lv[level].A64;
-  *n_blocks = A.kind == VK_DICT ? A.ndict : 0;
+  const LevelDev& D = h->lv[level];
+  *n_blocks = D.nh ? D.nh->nblocks() : 0;
   return MG_OK;
 }
 
