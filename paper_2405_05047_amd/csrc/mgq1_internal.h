@@ -286,6 +286,12 @@ hipError_t launch_asm_table(const AsmCoef& c, int dim, int B, int nd, const doub
 hipError_t launch_asm_gather(int64_t nnzb, int dim, int B, int nd, const int32_t* brow, const int32_t* bcol,
                              const uint32_t* cptr, const uint16_t* code, const double* table, const uint8_t* mask,
                              double* val, hipStream_t s);
+// the same blocks from nl distinct contribution lists: list l has the codes
+// code[lptr[l] .. lptr[l + 1]) and lmask[l] = row's constraint bits | column's << 4 |
+// diagonal << 8; block k has list lid[k]; lut: nl * B * B doubles of scratch
+hipError_t launch_asm_lists(int64_t nnzb, int dim, int B, int nl, const uint32_t* lptr, const uint16_t* code,
+                            const uint16_t* lmask, const uint16_t* lid, const double* table, double* lut, double* val,
+                            hipStream_t s);
 
 // ------------------------------------------------------------------ batched form
 // Many independent problems (same block size) with NR right-hand sides each.  Vectors

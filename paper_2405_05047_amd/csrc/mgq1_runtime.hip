@@ -2550,7 +2550,94 @@ struct AsmDev : DevOwner {
   const double* sizes = nullptr;
   const uint8_t* mask = nullptr;
   double* table = nullptr;
+  // distinct contribution lists (nl > 0: the arrays above per block are then absent)
+  int nl = 0;
+  const uint32_t* lptr = nullptr;
+  const uint16_t *lcode = nullptr, *lmask = nullptr, *lid = nullptr;
+  double* lut = nullptr;
 };
+
+// Numbers of the distinct contribution lists (with the constraint bits that apply to their
+// blocks): lid[k] of every block, rep[l] = the first block with list l.  Chunks of blocks on
+// the host threads, merged in chunk order; lists are compared entry by entry.  false: more
+// than 65,535.  Throws std::bad_alloc.
+bool distinct_lists(int64_t nnzb, const std::vector<uint32_t>& cptr, const std::vector<uint16_t>& code,
+                    const std::vector<uint16_t>& bits, std::vector<uint16_t>& lid, std::vector<int64_t>& rep) {
+  struct Set {
+    std::vector<int64_t> rep;
+    std::vector<int32_t> slot = std::vector<int32_t>(1024, 0);
+    uint64_t mask = 1023;
+  };
+  auto hash = [&](int64_t k) {
+    uint64_t h = bits[size_t(k)] * 0x9e3779b97f4a7c15ull + (cptr[size_t(k) + 1] - cptr[size_t(k)]);
+    for (uint32_t u = cptr[size_t(k)]; u < cptr[size_t(k) + 1]; ++u) h = (h ^ code[u]) * 0xff51afd7ed558ccdull + (h >> 31);
+    return nodebuild::mix(h);
+  };
+  auto same = [&](int64_t a, int64_t b) {
+    const uint32_t la = cptr[size_t(a) + 1] - cptr[size_t(a)];
+    return la == cptr[size_t(b) + 1] - cptr[size_t(b)] && bits[size_t(a)] == bits[size_t(b)] &&
+           std::equal(code.begin() + cptr[size_t(a)], code.begin() + cptr[size_t(a) + 1], code.begin() + cptr[size_t(b)]);
+  };
+  auto find_or_add = [&](Set& S, int64_t k) {
+    uint64_t p = hash(k) & S.mask;
+    while (S.slot[p]) {
+      const int32_t e = S.slot[p] - 1;
+      if (same(S.rep[size_t(e)], k)) return e;
+      p = (p + 1) & S.mask;
+    }
+    const int32_t e = int32_t(S.rep.size());
+    S.rep.push_back(k);
+    S.slot[p] = e + 1;
+    if (uint64_t(e) * 2 >= S.mask) {
+      S.mask = S.mask * 2 + 1;
+      S.slot.assign(size_t(S.mask) + 1, 0);
+      for (size_t q = 0; q < S.rep.size(); ++q) {
+        uint64_t z = hash(S.rep[q]) & S.mask;
+        while (S.slot[z]) z = (z + 1) & S.mask;
+        S.slot[z] = int32_t(q) + 1;
+      }
+    }
+    return e;
+  };
+  constexpr int32_t kMax = 65535;
+  const int64_t nchunk = 64, per = (nnzb + nchunk - 1) / nchunk;
+  std::vector<Set> sets(static_cast<size_t>(nchunk));
+  std::vector<int> bad(size_t(nchunk), 0);
+  lid.assign(size_t(nnzb), 0);
+  parallel_for(nchunk, 1, [&](int64_t c0, int64_t c1) {
+    for (int64_t c = c0; c < c1; ++c) {
+      try {
+        for (int64_t k = c * per; k < std::min(nnzb, (c + 1) * per); ++k) {
+          const int32_t e = find_or_add(sets[size_t(c)], k);
+          if (e >= kMax) { bad[size_t(c)] = 1; break; }
+          lid[size_t(k)] = uint16_t(e);
+        }
+      } catch (...) {
+        bad[size_t(c)] = 2;
+      }
+    }
+  });
+  for (int b : bad)
+    if (b == 2) throw std::bad_alloc();
+  for (int b : bad)
+    if (b) return false;
+  Set all;
+  std::vector<std::vector<uint16_t>> map(static_cast<size_t>(nchunk));
+  for (size_t c = 0; c < sets.size(); ++c) {
+    map[c].resize(sets[c].rep.size());
+    for (size_t q = 0; q < sets[c].rep.size(); ++q) {
+      const int32_t e = find_or_add(all, sets[c].rep[q]);
+      if (e >= kMax) return false;
+      map[c][q] = uint16_t(e);
+    }
+  }
+  parallel_for(nchunk, 1, [&](int64_t c0, int64_t c1) {
+    for (int64_t c = c0; c < c1; ++c)
+      for (int64_t k = c * per; k < std::min(nnzb, (c + 1) * per); ++k) lid[size_t(k)] = map[size_t(c)][lid[size_t(k)]];
+  });
+  rep = std::move(all.rep);
+  return true;
+}
 
 // exponent e with w = 2^-e (0 <= e <= 7), or -1
 int dyadic_exponent(double w) {
@@ -2661,18 +2748,58 @@ int asm_setup(AsmDev* A, const mg_asm_in& in, hipStream_t s) {
   uint16_t* p16;
   double* pd;
   uint8_t* p8;
-  if ((rc = upload(A, &p32, brow, s))) return rc;
-  A->brow = p32;
-  if ((rc = upload(A, &p32, bcol, s))) return rc;
-  A->bcol = p32;
-  if ((rc = upload(A, &pu, cptr, s))) return rc;
-  A->cptr = pu;
-  if ((rc = upload(A, &p16, code, s))) return rc;
-  A->code = p16;
+  // Where the distinct lists are at most a quarter of the blocks (and at most 65,535), each is
+  // summed once and spread over its blocks; a mesh so irregular (or so small) that they are
+  // more is summed block by block.  MGQ1_ASM_LISTS=0 keeps that everywhere (tests; the values
+  // are the same bits).
+  std::vector<uint16_t> lid, bits(size_t(in.nnzb), 0);
+  std::vector<int64_t> rep;
+  parallel_for(in.nnzb, 1 << 16, [&](int64_t k0, int64_t k1) {
+    for (int64_t k = k0; k < k1; ++k) {
+      unsigned m = brow[size_t(k)] == bcol[size_t(k)] ? 256u : 0u;
+      for (int c = 0; c < B; ++c) {
+        if (mask[size_t(brow[size_t(k)]) * B + c]) m |= 1u << c;
+        if (mask[size_t(bcol[size_t(k)]) * B + c]) m |= 16u << c;
+      }
+      bits[size_t(k)] = uint16_t(m);
+    }
+  });
+  const char* off = std::getenv("MGQ1_ASM_LISTS");
+  const bool lists = !(off && std::atoi(off) == 0) && distinct_lists(in.nnzb, cptr, code, bits, lid, rep) &&
+                     int64_t(rep.size()) * 4 <= in.nnzb;
+  if (lists) {
+    std::vector<uint32_t> lptr(1, 0);
+    std::vector<uint16_t> lcode, lmask;
+    for (int64_t k : rep) {
+      lcode.insert(lcode.end(), code.begin() + cptr[size_t(k)], code.begin() + cptr[size_t(k) + 1]);
+      lptr.push_back(uint32_t(lcode.size()));
+      lmask.push_back(bits[size_t(k)]);
+    }
+    if ((rc = upload(A, &pu, lptr, s))) return rc;
+    A->lptr = pu;
+    if ((rc = upload(A, &p16, lcode, s))) return rc;
+    A->lcode = p16;
+    if ((rc = upload(A, &p16, lmask, s))) return rc;
+    A->lmask = p16;
+    if ((rc = upload(A, &p16, lid, s))) return rc;
+    A->lid = p16;
+    if ((rc = dalloc(A, &A->lut, rep.size() * size_t(B) * B))) return rc;
+    A->nl = int(rep.size());
+    MG_HIP(hipStreamSynchronize(s));
+  } else {
+    if ((rc = upload(A, &p32, brow, s))) return rc;
+    A->brow = p32;
+    if ((rc = upload(A, &p32, bcol, s))) return rc;
+    A->bcol = p32;
+    if ((rc = upload(A, &pu, cptr, s))) return rc;
+    A->cptr = pu;
+    if ((rc = upload(A, &p16, code, s))) return rc;
+    A->code = p16;
+    if ((rc = upload(A, &p8, mask, s))) return rc;
+    A->mask = p8;
+  }
   if ((rc = upload(A, &pd, sizes, s))) return rc;
   A->sizes = pd;
-  if ((rc = upload(A, &p8, mask, s))) return rc;
-  A->mask = p8;
   A->nd = int(sizes.size());
   if ((rc = dalloc(A, &A->table, size_t(A->nd) * nb * nb * B * B))) return rc;
   MG_HIP(hipStreamSynchronize(s));   // the host vectors are freed on return
@@ -3254,6 +3381,10 @@ int mg_asm_values(mg_asm* a, const mg_asm_coef* coef, double* val, void* stream)
   c.mass_coef = coef->mass_coef;
   hipStream_t s = static_cast<hipStream_t>(stream);
   MG_HIP(launch_asm_table(c, a->dim, a->B, a->nd, a->sizes, a->table, s));
+  if (a->nl > 0) {
+    MG_HIP(launch_asm_lists(a->nnzb, a->dim, a->B, a->nl, a->lptr, a->lcode, a->lmask, a->lid, a->table, a->lut, val, s));
+    return MG_OK;
+  }
   MG_HIP(launch_asm_gather(a->nnzb, a->dim, a->B, a->nd, a->brow, a->bcol, a->cptr, a->code, a->table, a->mask, val,
                            s));
   return MG_OK;

@@ -115,3 +115,18 @@ def test_invalid_assembly_input_refused():
     val = torch.empty(top.nnzb, dtype=torch.float64, device="cuda")
     with pytest.raises(mg.MGError):
         a.values(mg.asm_coef(W.c3_elasticity(1)), val)     # elasticity on a scalar pattern
+
+
+@pytest.mark.parametrize("name", ["poisson33", "td_band", "elast17", "edge4", "face3", "td_time33"])
+def test_distinct_lists_bitwise_equal(name, monkeypatch):
+    """Summing each distinct contribution list once and spreading it over its blocks gives the
+    bits of the block-by-block sums, on every level (workgroups of 256 blocks with every kind
+    of remainder), also next to hanging nodes and constrained unknowns."""
+    from paper_2405_05047_amd import gen
+    wl = CASES[name]
+    p = gen.build(wl)
+    got = []
+    for lists in ("0", "1"):
+        monkeypatch.setenv("MGQ1_ASM_LISTS", lists)
+        got.append([host(val) for _, val in _assemble(p, wl)])
+    assert all(np.array_equal(a, b) for a, b in zip(*got))
