@@ -178,14 +178,20 @@ hipError_t launch_sweep2z(const SellDev& A, const void* S, const void* b, void* 
                           hipStream_t s);
 hipError_t launch_sweep0(const SellDev& A, const void* S, const void* b, void* xo, double omega,
                          int xk, hipStream_t s);
-// x = Ainv b with the FP64 inverse stored row-major; b / x of kind xk
-hipError_t launch_coarse_gemv(int n, const double* Ainv, const void* b, void* x, int xk, hipStream_t s);
+// x = Ainv b, or x += Ainv b (add), with the FP64 matrix stored row-major; b / x of kind xk
+hipError_t launch_coarse_gemv(int n, const double* Ainv, const void* b, void* x, int xk, hipStream_t s,
+                              bool add = false);
 // Gauss-Jordan with partial pivoting on the n x 2n augmented matrix M = [A | I]
 // (row-major, FP64); writes the inverse (row-major) to Ainv; flag != 0 if singular
 hipError_t launch_coarse_invert(int n, double* M, double* Ainv, double* pivbuf, int* flag,
                                 hipStream_t s);
-// levels p.top .. 1 and the coarse solve of one V-cycle in one workgroup
-hipError_t launch_tail(const TailLevel* lv, int B, int kind, int xk, const TailParams& p, hipStream_t s);
+// levels p.top .. 1 and the coarse solve of one V-cycle in one workgroup, for each of
+// `columns` right-hand sides (the levels' vectors hold that many, one after the other)
+hipError_t launch_tail(const TailLevel* lv, int B, int kind, int xk, const TailParams& p, hipStream_t s,
+                       int columns = 1);
+// v = columns c0 .. c0 + cols - 1 of the n x n unit matrix; M[i][c0 + c] = v[c * n + i]
+hipError_t launch_unit_columns(int n, int c0, int cols, double* v, hipStream_t s);
+hipError_t launch_columns_to_rows(int n, int c0, int cols, const double* v, double* M, hipStream_t s);
 // nodal block inverses of the diagonal blocks of A (FP64 SELL) into S (lane layout,
 // double or float per sk); flag != 0 if a block is singular
 hipError_t launch_block_invert(const SellDev& A, void* S, int sk, int* flag, int NR, hipStream_t s);
@@ -202,7 +208,8 @@ hipError_t launch_scale_div(int64_t n, double* y, const double* x, const double*
 // (reduction_grid(n) of them); consumers re-sum them in a fixed order
 int reduction_grid(int64_t n);
 hipError_t launch_dot_partials(int64_t n, const double* a, const double* b, double* partials, hipStream_t s);
-hipError_t launch_finish(const double* partials, int g, double* out, int sqrt_out, hipStream_t s);
+hipError_t launch_finish(const double* partials, int g, double* out, int sqrt_out, hipStream_t s,
+                         double* host = nullptr);
 // Gram-Schmidt of FGMRES step j (modified Gram-Schmidt with its dot products formed in one
 // pass): w -= sum_{i<=j} h_i v_i, v_i = V + i * n, h stored in h[0..j]; gram: kWave * kWave
 // doubles that hold the basis's Gram entries from step to step (row 0 first, any content

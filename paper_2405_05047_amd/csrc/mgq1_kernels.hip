@@ -45,12 +45,12 @@
 namespace mgq1 {
 namespace {
 
-// x = Ainv b, one wavefront per row (Ainv row-major, FP64)
+// x = Ainv b or (add) x += Ainv b, one wavefront per row (Ainv row-major, FP64)
 // U row chunks of 64 elements have their loads issued together; every lane sums its
 // elements in increasing column order whatever U is, so U does not change the result
 template <class XI, class XO, int U = 8>
 __device__ __forceinline__ void gemv_row(int n, const double* __restrict__ Ainv, const XI* __restrict__ b,
-                                         XO* __restrict__ x, int i, int lane) {
+                                         XO* __restrict__ x, int i, int lane, bool add = false) {
   double acc = 0.0;
   const double* row = Ainv + int64_t(i) * n;
   for (int k0 = lane; k0 < n; k0 += kWave * U) {
@@ -66,14 +66,14 @@ __device__ __forceinline__ void gemv_row(int n, const double* __restrict__ Ainv,
     for (int u = 0; u < U; ++u) acc += av[u] * double(bv[u]);
   }
   acc = wave_sum(acc);
-  if (lane == 0) x[i] = XO(acc);
+  if (lane == 0) x[i] = add ? XO(double(x[i]) + acc) : XO(acc);
 }
 
 template <class XI, class XO>
 __global__ __launch_bounds__(kThreads) void k_coarse_gemv(int n, const double* __restrict__ Ainv,
-                                                          const XI* __restrict__ b, XO* __restrict__ x) {
+                                                          const XI* __restrict__ b, XO* __restrict__ x, bool add) {
   const int i = blockIdx.x * kSliceWaves + threadIdx.x / kWave;
-  if (i < n) gemv_row<XI, XO, 32>(n, Ainv, b, x, i, threadIdx.x % kWave);   // rows up to 2048 in one pass
+  if (i < n) gemv_row<XI, XO, 32>(n, Ainv, b, x, i, threadIdx.x % kWave, add);   // rows up to 2048 in one pass
 }
 
 // ------------------------------------------------------------------ tail kernel
@@ -88,21 +88,24 @@ __device__ void tail_sweep(const TailLevel& L, const X* b, const X* x, X* xo, T 
 
 // Levels top .. 1 and the coarse solve of one V-cycle in a single workgroup.  Level top
 // reads its right-hand side from lv[top].b and leaves its result in lv[top].x, exactly
-// like the grid-kernel path of the host driver (same ping-pong order).
+// like the grid-kernel path of the host driver (same ping-pong order).  Workgroup c of a
+// launch works on column c of the levels' vectors (each column contiguous).
 template <int B, int K, class X, class T>
 __global__ __launch_bounds__(kTailThreads) void k_tail(const TailLevel* __restrict__ lv, TailParams p) {
   const int nw = blockDim.x / kWave, w = threadIdx.x / kWave, ln = threadIdx.x % kWave;
   const T omega = T(p.omega);
   const int pre_pp = p.nu1 >= 1 ? p.nu1 - 1 : 0;
   const int pp = pre_pp + p.nu2;
+  // this workgroup's column of a level vector
+  auto column = [&](void* v, const TailLevel& L) { return static_cast<X*>(v) + int64_t(blockIdx.x) * L.A.n * B; };
   // descent
   for (int l = p.top; l >= 1; --l) {
     const TailLevel& L = lv[l];
-    X* own = static_cast<X*>(L.x);
-    X* tmp = static_cast<X*>(L.t);
+    X* own = column(L.x, L);
+    X* tmp = column(L.t, L);
     X* cur = (pp % 2 == 0) ? own : tmp;
     X* oth = (pp % 2 == 0) ? tmp : own;
-    const X* b = static_cast<const X*>(L.b);
+    const X* b = column(L.b, L);
     if (p.nu1 >= 1) {
       for (int sl = w; sl < L.A.nslices; sl += nw)
         sweep0_slice<B, 1, X, T>(static_cast<const X*>(L.S), b, cur, omega, slice_lane<B, 1>(L.A, sl, ln));
@@ -116,25 +119,25 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(const TailLevel* __restri
       __syncthreads();
     }
     for (int sl = w; sl < L.A.nslices; sl += nw)
-      spmv_slice<B, 1, K, X, X, T, 2, kb_default<B>(), false, 2>(L.A, b, cur, static_cast<X*>(L.r), L.mask,
+      spmv_slice<B, 1, K, X, X, T, 2, kb_default<B>(), false, 2>(L.A, b, cur, column(L.r, L), L.mask,
                                                                  slice_lane<B, 1>(L.A, sl, ln));
     __syncthreads();
     const TailLevel& C = lv[l - 1];
     for (int64_t t = threadIdx.x; t < int64_t(C.A.n) * B; t += blockDim.x)
-      restrict_dof<B, 1, X, T>(L.R, static_cast<const X*>(L.r), static_cast<X*>(C.b), C.mask, nullptr, t);
+      restrict_dof<B, 1, X, T>(L.R, column(L.r, L), column(C.b, C), C.mask, nullptr, t);
     __syncthreads();
   }
   // coarse solve on level 0
   {
     const TailLevel& C = lv[0];
-    X* x0 = static_cast<X*>(C.x);
-    const X* b0 = static_cast<const X*>(C.b);
+    X* x0 = column(C.x, C);
+    const X* b0 = column(C.b, C);
     if (p.coarse_mode == 0) {
       for (int i = w; i < p.n0; i += nw) gemv_row<X, X>(p.n0, p.Ainv, b0, x0, i, ln);
       __syncthreads();
     } else {
       const int k = p.coarse_sweeps > 1 ? p.coarse_sweeps : 1;
-      X* tmp = static_cast<X*>(C.t);
+      X* tmp = column(C.t, C);
       X* cur = ((k - 1) % 2 == 0) ? x0 : tmp;
       X* oth = ((k - 1) % 2 == 0) ? tmp : x0;
       for (int sl = w; sl < C.A.nslices; sl += nw)
@@ -150,16 +153,16 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(const TailLevel* __restri
   for (int l = 1; l <= p.top; ++l) {
     const TailLevel& L = lv[l];
     const TailLevel& C = lv[l - 1];
-    X* own = static_cast<X*>(L.x);
-    X* tmp = static_cast<X*>(L.t);
+    X* own = column(L.x, L);
+    X* tmp = column(L.t, L);
     X* cur = (pp % 2 == 0) ? own : tmp;
     X* oth = (pp % 2 == 0) ? tmp : own;
     if (pre_pp % 2 == 1) { X* t = cur; cur = oth; oth = t; }
     for (int64_t t = threadIdx.x; t < int64_t(L.A.n) * B; t += blockDim.x)
-      prolong_dof<B, 1, X, T>(L.P, static_cast<const X*>(C.x), cur, L.mask, C.mask, t);
+      prolong_dof<B, 1, X, T>(L.P, column(C.x, C), cur, L.mask, C.mask, t);
     __syncthreads();
     for (int q = 0; q < p.nu2; ++q) {
-      tail_sweep<B, K, X, T>(L, static_cast<const X*>(L.b), cur, oth, omega);
+      tail_sweep<B, K, X, T>(L, column(L.b, L), cur, oth, omega);
       X* t = cur; cur = oth; oth = t;
     }
   }
@@ -257,6 +260,25 @@ __global__ __launch_bounds__(256) void k_block_invert(SellDev A, ST* __restrict_
     for (int cc = 0; cc < B; ++cc) S[(int64_t(slice) * B + cc) * W + r * B + c] = ST(m[c][B + cc]);
 }
 
+// columns c0 .. c0 + cols - 1 of the n x n unit matrix, one after the other
+__global__ __launch_bounds__(256) void k_unit_columns(int n, int c0, int64_t total, double* __restrict__ v) {
+  const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
+  if (t < total) v[t] = t % n == c0 + t / n ? 1.0 : 0.0;
+}
+
+// B[i][c0 + c] = v[c * n + i]: columns into a row-major matrix, 32 x 32 entries through LDS
+__global__ __launch_bounds__(256) void k_columns_to_rows(int n, int c0, int cols, const double* __restrict__ v,
+                                                         double* __restrict__ M) {
+  __shared__ double tile[32][33];
+  const int tx = int(threadIdx.x) % 32, ty = int(threadIdx.x) / 32;
+  const int i0 = int(blockIdx.x) * 32, k0 = int(blockIdx.y) * 32;
+  for (int q = ty; q < 32; q += 8)
+    if (i0 + tx < n && k0 + q < cols) tile[q][tx] = v[int64_t(k0 + q) * n + i0 + tx];
+  __syncthreads();
+  for (int q = ty; q < 32; q += 8)
+    if (i0 + q < n && k0 + tx < cols) M[int64_t(i0 + q) * n + c0 + k0 + tx] = tile[tx][q];
+}
+
 // ------------------------------------------------------------------ vector kernels
 template <class Y>
 __global__ void k_fill(int64_t n, Y* y, double v) {
@@ -311,11 +333,20 @@ __global__ __launch_bounds__(kRedThreads) void k_dot_partials(int64_t n, const d
   if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
-// out = sum (or sqrt of the sum) of partials, one workgroup
-__global__ __launch_bounds__(1024) void k_finish(const double* __restrict__ p, int g, double* out, int sq) {
+// out = sum (or sqrt of the sum) of partials, one workgroup; host: the same to memory that the
+// host reads after the stream has been waited for
+__global__ __launch_bounds__(1024) void k_finish(const double* __restrict__ p, int g, double* out, int sq,
+                                                 double* host) {
   __shared__ double lds[kMaxWaves + 1];
   const double s = sum_partials(p, g, lds);
-  if (threadIdx.x == 0) *out = sq ? sqrt(s) : s;
+  if (threadIdx.x == 0) {
+    const double v = sq ? sqrt(s) : s;
+    *out = v;
+    if (host) {
+      *host = v;
+      __threadfence_system();
+    }
+  }
 }
 
 // Givens rotation j of the Hessenberg column j (applies the previous rotations, forms the
@@ -423,21 +454,21 @@ __global__ void k_init_g(int m, double* g, const double* beta) {
 // ------------------------------------------------------------------ launch helpers
 
 template <int B, int K, class X, class T>
-hipError_t tail_t(const TailLevel* lv, const TailParams& p, hipStream_t s) {
-  hipLaunchKernelGGL((k_tail<B, K, X, T>), 1, kTailThreads, 0, s, lv, p);
+hipError_t tail_t(const TailLevel* lv, const TailParams& p, int columns, hipStream_t s) {
+  hipLaunchKernelGGL((k_tail<B, K, X, T>), columns, kTailThreads, 0, s, lv, p);
   return hipGetLastError();
 }
 
 template <int B>
-hipError_t tail_b(const TailLevel* lv, int kind, int xk, const TailParams& p, hipStream_t s) {
+hipError_t tail_b(const TailLevel* lv, int kind, int xk, const TailParams& p, int columns, hipStream_t s) {
   if (xk == X_F64) {
     if (kind != VK_F64) return hipErrorInvalidValue;
-    return tail_t<B, VK_F64, double, double>(lv, p, s);
+    return tail_t<B, VK_F64, double, double>(lv, p, columns, s);
   }
   switch (kind) {
-    case VK_F32: return tail_t<B, VK_F32, float, float>(lv, p, s);
-    case VK_F16: return tail_t<B, VK_F16, float, float>(lv, p, s);
-    case VK_BF16: return tail_t<B, VK_BF16, float, float>(lv, p, s);
+    case VK_F32: return tail_t<B, VK_F32, float, float>(lv, p, columns, s);
+    case VK_F16: return tail_t<B, VK_F16, float, float>(lv, p, columns, s);
+    case VK_BF16: return tail_t<B, VK_BF16, float, float>(lv, p, columns, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -588,25 +619,25 @@ hipError_t launch_prolong_s(const TSellDev& P, int B, const void* y, void* x, co
 }
 
 
-hipError_t launch_tail(const TailLevel* lv, int B, int kind, int xk, const TailParams& p, hipStream_t s) {
+hipError_t launch_tail(const TailLevel* lv, int B, int kind, int xk, const TailParams& p, hipStream_t s, int columns) {
   switch (B) {
-    case 1: return tail_b<1>(lv, kind, xk, p, s);
-    case 2: return tail_b<2>(lv, kind, xk, p, s);
-    case 3: return tail_b<3>(lv, kind, xk, p, s);
-    case 4: return tail_b<4>(lv, kind, xk, p, s);
+    case 1: return tail_b<1>(lv, kind, xk, p, columns, s);
+    case 2: return tail_b<2>(lv, kind, xk, p, columns, s);
+    case 3: return tail_b<3>(lv, kind, xk, p, columns, s);
+    case 4: return tail_b<4>(lv, kind, xk, p, columns, s);
     default: return hipErrorInvalidValue;
   }
 }
 
-hipError_t launch_coarse_gemv(int n, const double* Ainv, const void* b, void* x, int xk, hipStream_t s) {
+hipError_t launch_coarse_gemv(int n, const double* Ainv, const void* b, void* x, int xk, hipStream_t s, bool add) {
   if (n == 0) return hipSuccess;
   const unsigned g = grid_for(n, kSliceWaves);
   if (xk == X_F64)
     hipLaunchKernelGGL((k_coarse_gemv<double, double>), g, kThreads, 0, s, n, Ainv, static_cast<const double*>(b),
-                       static_cast<double*>(x));
+                       static_cast<double*>(x), add);
   else
     hipLaunchKernelGGL((k_coarse_gemv<float, float>), g, kThreads, 0, s, n, Ainv, static_cast<const float*>(b),
-                       static_cast<float*>(x));
+                       static_cast<float*>(x), add);
   return hipGetLastError();
 }
 
@@ -618,6 +649,16 @@ hipError_t launch_coarse_invert(int n, double* M, double* Ainv, double* pivbuf, 
     hipLaunchKernelGGL(k_gj_clear, grid_for(n, 256), 256, 0, s, n, k, M);
   }
   hipLaunchKernelGGL(k_gj_extract, grid_for(int64_t(n) * n, 256), 256, 0, s, n, M, Ainv);
+  return hipGetLastError();
+}
+
+hipError_t launch_unit_columns(int n, int c0, int cols, double* v, hipStream_t s) {
+  hipLaunchKernelGGL(k_unit_columns, grid_for(int64_t(n) * cols, 256), 256, 0, s, n, c0, int64_t(n) * cols, v);
+  return hipGetLastError();
+}
+
+hipError_t launch_columns_to_rows(int n, int c0, int cols, const double* v, double* M, hipStream_t s) {
+  hipLaunchKernelGGL(k_columns_to_rows, dim3(grid_for(n, 32), grid_for(cols, 32)), 256, 0, s, n, c0, cols, v, M);
   return hipGetLastError();
 }
 
@@ -688,8 +729,8 @@ hipError_t launch_dot_partials(int64_t n, const double* a, const double* b, doub
   return hipGetLastError();
 }
 
-hipError_t launch_finish(const double* partials, int g, double* out, int sqrt_out, hipStream_t s) {
-  hipLaunchKernelGGL(k_finish, 1, 1024, 0, s, partials, g, out, sqrt_out);
+hipError_t launch_finish(const double* partials, int g, double* out, int sqrt_out, hipStream_t s, double* host) {
+  hipLaunchKernelGGL(k_finish, 1, 1024, 0, s, partials, g, out, sqrt_out, host);
   return hipGetLastError();
 }
 

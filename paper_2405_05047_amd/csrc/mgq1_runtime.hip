@@ -530,6 +530,8 @@ struct mg_handle : DevOwner {
   double* Ainv = nullptr; // coarse inverse, row-major
   int n0 = 0;
   int tail_top = -1;      // levels 0..tail_top run in the single-workgroup tail kernel
+  int dense_top = -1;     // >= 1: levels 0..dense_top are one product with `dense`
+  double* dense = nullptr;  // matrix of the V-cycle on level dense_top, row-major
   TailLevel* dtail = nullptr;
   // outer loop
   double* V = nullptr;    // (m+1) x N_L FP64
@@ -551,9 +553,9 @@ struct mg_handle : DevOwner {
   // the step coefficients x_{k+1} = x_k + alpha_k S r_k + beta_k (x_k - x_{k-1})
   std::vector<double> lam;
   std::vector<std::vector<double>> cheb_alpha, cheb_beta;
-  double* hs = nullptr;   // pinned host scalars
   double* hst = nullptr;  // pinned, device-mapped: Givens output of step j at [2j], [2j+1]
   double* hst_dev = nullptr;             // the same memory as the kernels address it
+  double *norm = nullptr, *norm_dev = nullptr;   // behind it: ||r|| and ||b|| of a solve
   std::vector<hipEvent_t> step_done;     // recorded after FGMRES step j
   hipStream_t cap = nullptr;             // private stream used only to capture graphs
   std::vector<hipGraphExec_t> step_graph; // FGMRES step j (V-cycle, SpMV, MGS, Givens)
@@ -563,7 +565,6 @@ struct mg_handle : DevOwner {
     for (hipEvent_t e : step_done)
       if (e) (void)hipEventDestroy(e);
     if (cap) (void)hipStreamDestroy(cap);
-    if (hs) (void)hipHostFree(hs);
     if (hst) (void)hipHostFree(hst);
   }
 };
@@ -1033,7 +1034,9 @@ int smooth_level(mg_handle* h, int l, const void* b, void*& cur, void*& other, i
 int vcycle_cycle(mg_handle* h, const void* bL, void* xL, hipStream_t s, bool xinit = false) {
   const int L = h->L;
   const mg_config& c = h->cfg;
-  const int top = h->tail_top;
+  // the dense V-cycle starts from x = 0; from a given iterate the finest level runs its steps
+  const bool dense = h->dense_top >= 1 && !(xinit && h->dense_top == L);
+  const int top = dense ? h->dense_top : h->tail_top;
   std::vector<const void*> bb(L + 1);
   std::vector<void*> cur(L + 1), oth(L + 1);
   for (int l = 0; l <= L; ++l) bb[l] = h->lv[l].b;
@@ -1081,7 +1084,10 @@ int vcycle_cycle(mg_handle* h, const void* bL, void* xL, hipStream_t s, bool xin
     MG_HIP(launch_spmv(Lv.Ac, bb[l], cur[l], Lv.r, Lv.mask, h->xk, h->xk, 2, nullptr, s));
     MG_HIP(launch_restrict_s(Lv.Rs, Lv.B, Lv.r, h->lv[l - 1].b, h->lv[l - 1].mask, nullptr, h->xk, s));
   }
-  if (top == 0) {
+  if (dense) {
+    MG_HIP(launch_coarse_gemv(int(h->lv[top].N), h->dense, bb[top], top == L ? xL : h->lv[top].x, h->xk, s));
+    if (top == L) return MG_OK;
+  } else if (top == 0) {
     // coarse solve with grid-wide kernels: one wavefront per row of the dense inverse
     LevelDev& C0 = h->lv[0];
     void* x0 = (L == 0) ? xL : C0.x;
@@ -1132,31 +1138,28 @@ int precond(mg_handle* h, const double* v, void* z, hipStream_t s, bool converte
   return vcycle_cycle(h, h->bcyc, z, s);
 }
 
-int read_scalars(mg_handle* h, const double* d, int k, hipStream_t s) {
-  MG_HIP(hipMemcpyAsync(h->hs, d, sizeof(double) * k, hipMemcpyDeviceToHost, s));
-  MG_HIP(hipStreamSynchronize(s));
-  return MG_OK;
-}
-
-// r = b - A x, dsc[0] = ||r||.  FGMRES divides by the norm: there it is summed over the
-// vector in an order that does not depend on the operator's storage, so that every form of
-// the operator gives the solve the same bits; the MG iteration only compares it.
+// r = b - A x, ||r|| to dsc[0] and to the host's norm[0].  FGMRES divides by the norm: there
+// it is summed over the vector in an order that does not depend on the operator's storage, so
+// that every form of the operator gives the solve the same bits; the MG iteration only
+// compares it.
 int enqueue_defect(mg_handle* h, const double* b, const double* x, hipStream_t s) {
   LevelDev& T = h->lv[h->L];
   if (h->cfg.outer == MG_OUTER_FGMRES) {
     MG_HIP(launch_spmv(T.A64, b, x, h->rout, nullptr, X_F64, X_F64, 1, nullptr, s));
     MG_HIP(launch_dot_partials(T.N, h->rout, nullptr, h->pv, s));
-    MG_HIP(launch_finish(h->pv, reduction_grid(T.N), h->dsc + 0, 1, s));
+    MG_HIP(launch_finish(h->pv, reduction_grid(T.N), h->dsc + 0, 1, s, h->norm_dev));
   } else {
     MG_HIP(launch_spmv(T.A64, b, x, h->rout, nullptr, X_F64, X_F64, 1, h->pbig, s));
-    MG_HIP(launch_finish(h->pbig, spmv_grid(T.A64), h->dsc + 0, 1, s));
+    MG_HIP(launch_finish(h->pbig, spmv_grid(T.A64), h->dsc + 0, 1, s, h->norm_dev));
   }
   return MG_OK;
 }
 
 int outer_defect(mg_handle* h, const double* b, const double* x, hipStream_t s) {
   const int rc = enqueue_defect(h, b, x, s);
-  return rc ? rc : read_scalars(h, h->dsc, 1, s);
+  if (rc) return rc;
+  MG_HIP(hipStreamSynchronize(s));
+  return MG_OK;
 }
 
 // One FGMRES step j on internal buffers: z_j = V(v_j), w = A z_j, modified Gram-Schmidt
@@ -1226,12 +1229,12 @@ int solve_impl(mg_handle* h, const double* b, double* x, mg_solve_stats* st, voi
   // ||b|| (to dsc[4]) and the initial defect r = b - A x with ||r|| (to dsc[0]), read
   // back with one synchronisation
   MG_HIP(launch_dot_partials(N, b, nullptr, h->pv, s));
-  MG_HIP(launch_finish(h->pv, reduction_grid(N), h->dsc + 4, 1, s));
-  if ((rc = enqueue_defect(h, b, x, s)) || (rc = read_scalars(h, h->dsc, 5, s))) return rc;
-  const double bn = h->hs[4];
+  MG_HIP(launch_finish(h->pv, reduction_grid(N), h->dsc + 4, 1, s, h->norm_dev + 1));
+  if ((rc = outer_defect(h, b, x, s))) return rc;
+  const double bn = h->norm[1];
   const double tol = c.rtol * bn;
   const int limit = fixed > 0 ? fixed : c.maxit;
-  double beta = h->hs[0];
+  double beta = h->norm[0];
   S.res0 = beta;
   int status = MG_OK;
   if (c.outer == MG_OUTER_IR) {
@@ -1239,11 +1242,15 @@ int solve_impl(mg_handle* h, const double* b, double* x, mg_solve_stats* st, voi
       if (!std::isfinite(beta) || beta > 1e6 * std::max(S.res0, 1e-300)) { status = MG_ENUMERIC; break; }
       if (fixed <= 0 && beta <= tol) { S.converged = 1; break; }
       if (S.iters >= limit) { status = fixed > 0 ? MG_OK : MG_ENOCONV; break; }
-      if ((rc = precond(h, h->rout, h->e, s))) return rc;
-      MG_HIP(launch_axpy(N, x, X_F64, h->e, h->xk, 1.0, h->dsc + 1, s));
+      if (h->dense_top == h->L && h->L > 0) {
+        MG_HIP(launch_coarse_gemv(int(N), h->dense, h->rout, x, X_F64, s, true));   // x += V(r)
+      } else {
+        if ((rc = precond(h, h->rout, h->e, s))) return rc;
+        MG_HIP(launch_axpy(N, x, X_F64, h->e, h->xk, 1.0, h->dsc + 1, s));
+      }
       ++S.iters;
       if ((rc = outer_defect(h, b, x, s))) return rc;
-      beta = h->hs[0];
+      beta = h->norm[0];
     }
   } else {
     const int m = c.gmres_m;
@@ -1281,7 +1288,7 @@ int solve_impl(mg_handle* h, const double* b, double* x, mg_solve_stats* st, voi
       MG_HIP(launch_update_x(N, x, h->Z, h->xk, N, h->y, k, s));
       ++S.restarts;
       if ((rc = outer_defect(h, b, x, s))) return rc;
-      beta = h->hs[0];
+      beta = h->norm[0];
     }
     if (status == MG_OK && fixed <= 0 && beta > tol) status = MG_ENOCONV;
   }
@@ -1616,6 +1623,68 @@ int tune_levels(mg_handle* h, hipStream_t s) {
   return rc;
 }
 
+// The V-cycle from x = 0 is a fixed linear map of its right-hand side, so on the small levels
+// (up to kDenseRows unknowns above the coarsest level) the whole recursion below is one
+// dense product: its matrix comes from the V-cycle of every unit vector (one workgroup
+// each, all at once).  A level there costs 6 to 7 launches of 3 to 5 us each; the product
+// reads 8 n^2 bytes.  Solve of the 33^2 Poisson problem (5 levels, 9.5 MB matrix, MG
+// iteration): 1290 -> 226 us; 1,761-unknown transport-diffusion (FGMRES): 1775 -> 838 us.  2048
+// rows (34 MB, 8 us) still take less than the launches that they replace.  FP64 cycles of
+// damped sweeps only: reduced cycles keep their rounding.  MGQ1_NO_DENSE=1: off (tests).
+constexpr int64_t kDenseRows = 2048;
+
+int setup_dense(mg_handle* h, const std::vector<HostLevel>& H, hipStream_t s) {
+  const mg_config& c = h->cfg;
+  const char* off = std::getenv("MGQ1_NO_DENSE");
+  if (h->xk != X_F64 || c.smoother != MG_SMOOTH_JACOBI || h->tail_top > 0 || (off && std::atoi(off) != 0)) return MG_OK;
+  int top = 0;
+  for (int l = 1; l <= h->L && h->lv[l].N <= kDenseRows; ++l) top = l;
+  if (top < 1) return MG_OK;
+  const int n = int(h->lv[top].N);
+  const int cols = std::min(n, 512);             // two workgroups per CU at a time
+  DevOwner tmp;                                  // sliced-ELL copies and vectors, freed on return
+  std::vector<LevelDev> lv(static_cast<size_t>(top) + 1);
+  std::vector<TailLevel> tl(size_t(top) + 1);
+  int rc;
+  for (int l = 0; l <= top; ++l) {
+    LevelDev& D = lv[size_t(l)];
+    if ((rc = setup_level(&tmp, H[size_t(l)], l > 0, 1, VK_F64, X_F64, false, h->dflag, s, D))) return rc;
+    TailLevel& T = tl[size_t(l)];
+    T.A = D.Ac;
+    T.S = D.S;
+    T.mask = D.mask;
+    T.P = D.P;
+    T.R = D.R;
+    for (void** v : {&T.x, &T.b, &T.r, &T.t}) {
+      double* p;
+      if ((rc = dalloc(&tmp, &p, size_t(D.N) * cols))) return rc;
+      *v = p;
+    }
+  }
+  TailLevel* dt;
+  if ((rc = upload(&tmp, &dt, tl, s))) return rc;
+  if ((rc = dalloc(h, &h->dense, size_t(n) * n))) return rc;
+  TailParams tp;
+  tp.top = top;
+  tp.nu1 = c.nu1;
+  tp.nu2 = c.nu2;
+  tp.omega = c.omega;
+  tp.Ainv = h->Ainv;
+  tp.n0 = h->n0;
+  tp.coarse_mode = c.coarse_mode;
+  tp.coarse_sweeps = c.coarse_sweeps;
+  TailLevel& T = tl[size_t(top)];
+  for (int c0 = 0; c0 < n; c0 += cols) {
+    const int k = std::min(cols, n - c0);
+    MG_HIP(launch_unit_columns(n, c0, k, static_cast<double*>(T.b), s));
+    MG_HIP(launch_tail(dt, h->lv[0].B, VK_F64, X_F64, tp, s, k));
+    MG_HIP(launch_columns_to_rows(n, c0, k, static_cast<double*>(T.x), h->dense, s));
+  }
+  MG_HIP(hipStreamSynchronize(s));
+  h->dense_top = top;
+  return MG_OK;
+}
+
 int setup_handle(mg_handle* h, const std::vector<HostLevel>& H, hipStream_t s) {
   PhaseTimer pt;
   const mg_config& c = h->cfg;
@@ -1685,6 +1754,8 @@ int setup_handle(mg_handle* h, const std::vector<HostLevel>& H, hipStream_t s) {
   if (top >= 1 && c.smoother == MG_SMOOTH_CHEBYSHEV)
     return fail(MG_EUNSUPPORTED, "the single-workgroup tail runs damped Jacobi sweeps only");
   h->tail_top = top;
+  if ((rc = setup_dense(h, H, s))) return rc;
+  pt.mark("dense V-cycle of the small levels");
   std::vector<TailLevel> tl(top + 1);
   for (int l = 0; l <= top; ++l) {
     const LevelDev& D = h->lv[l];
@@ -1700,10 +1771,11 @@ int setup_handle(mg_handle* h, const std::vector<HostLevel>& H, hipStream_t s) {
   }
   if ((rc = dalloc(h, &h->dtail, tl.size()))) return rc;
   MG_HIP(hipMemcpyAsync(h->dtail, tl.data(), tl.size() * sizeof(TailLevel), hipMemcpyHostToDevice, s));
-  MG_HIP(hipHostMalloc(reinterpret_cast<void**>(&h->hs), 16 * sizeof(double), hipHostMallocDefault));
-  MG_HIP(hipHostMalloc(reinterpret_cast<void**>(&h->hst), 2 * size_t(m) * sizeof(double),
+  MG_HIP(hipHostMalloc(reinterpret_cast<void**>(&h->hst), (2 * size_t(m) + 2) * sizeof(double),
                        hipHostMallocMapped | hipHostMallocCoherent));
   MG_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&h->hst_dev), h->hst, 0));
+  h->norm = h->hst + 2 * size_t(m);
+  h->norm_dev = h->hst_dev + 2 * size_t(m);
   h->step_done.assign(size_t(m), nullptr);
   for (hipEvent_t& e : h->step_done) MG_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   h->step_graph.assign(size_t(m), nullptr);
