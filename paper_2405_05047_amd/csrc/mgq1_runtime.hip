@@ -1642,23 +1642,30 @@ int setup_dense(mg_handle* h, const std::vector<HostLevel>& H, hipStream_t s) {
   if (top < 1) return MG_OK;
   const int n = int(h->lv[top].N);
   const int cols = std::min(n, 512);             // two workgroups per CU at a time
-  DevOwner tmp;                                  // sliced-ELL copies and vectors, freed on return
-  std::vector<LevelDev> lv(static_cast<size_t>(top) + 1);
+  DevOwner tmp;                                  // work vectors (and copies), freed on return
+  std::vector<LevelDev> copy(static_cast<size_t>(top) + 1);
   std::vector<TailLevel> tl(size_t(top) + 1);
   int rc;
+  int64_t total = 0;
+  for (int l = 0; l <= top; ++l) total += h->lv[l].N;
+  double* work;
+  if ((rc = dalloc(&tmp, &work, size_t(total) * 4 * cols))) return rc;
   for (int l = 0; l <= top; ++l) {
-    LevelDev& D = lv[size_t(l)];
-    if ((rc = setup_level(&tmp, H[size_t(l)], l > 0, 1, VK_F64, X_F64, false, h->dflag, s, D))) return rc;
+    // the workgroup's cycle reads sliced ELL: a level in the node form gets a copy in it
+    LevelDev* D = &h->lv[l];
+    if (D->Ac.node) {
+      D = &copy[size_t(l)];
+      if ((rc = setup_level(&tmp, H[size_t(l)], l > 0, 1, VK_F64, X_F64, false, h->dflag, s, *D))) return rc;
+    }
     TailLevel& T = tl[size_t(l)];
-    T.A = D.Ac;
-    T.S = D.S;
-    T.mask = D.mask;
-    T.P = D.P;
-    T.R = D.R;
+    T.A = D->Ac;
+    T.S = D->S;
+    T.mask = D->mask;
+    T.P = D->P;
+    T.R = D->R;
     for (void** v : {&T.x, &T.b, &T.r, &T.t}) {
-      double* p;
-      if ((rc = dalloc(&tmp, &p, size_t(D.N) * cols))) return rc;
-      *v = p;
+      *v = work;
+      work += size_t(D->N) * cols;
     }
   }
   TailLevel* dt;
