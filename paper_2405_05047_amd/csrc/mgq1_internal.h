@@ -54,17 +54,27 @@ struct SellDev {
 //   kNodeColUniform  the column of slot k is the row's node + opat[ic + k]; else it is
 //                    base[ic + k] + col16[(ic + k) * 64 + lane], or (kNodeCol32)
 //                    col32[(ic + k) * 64 + lane]
+//   kNodeRuns        (B >= 2, with both uniform flags) the slice's nodes lie within kRunSpan
+//                    and its offsets in runs of at most kRunWidth: ic is the start of a record
+//                    in rpat: {phases, then per phase {end of its slots, start and width of up
+//                    to kPhaseRuns runs (width 0: none), 0}, then per slot the place of its
+//                    column in the phase's staging area, in nodes from the slice's first}; run q
+//                    of a phase is staged at node q * kRunStride
 // Rows past the end repeat the last row's node.  Padding slots of a shorter row hold the zero
 // block (number 0) and the row's own node.
-enum { kNodeValUniform = 1, kNodeColUniform = 2, kNodeCol32 = 4 };
+enum { kNodeValUniform = 1, kNodeColUniform = 2, kNodeCol32 = 4, kNodeRuns = 8 };
+constexpr int kRunSpan = 76, kRunWidth = 5, kRunStride = kRunSpan + kRunWidth - 1, kPhaseRuns = 3;
+constexpr int kPhaseInts = 2 + 2 * kPhaseRuns;
 struct NodeDev {
   int32_t n = 0, B = 1, nslices = 0;
   int tk = X_F64;                   // type of the block tables: that of the row sums
+  int shallow = 0;                  // more than half of the slices read staged runs
   const int32_t* desc = nullptr;    // nslices * 4
   const int32_t* perm = nullptr;    // node at each row position (NULL: the position itself)
   const void* vtab = nullptr;       // blocks of the distinct uniform rows, row after row
   const void* dtab = nullptr;       // the distinct blocks, row-major
   const int32_t* opat = nullptr;
+  const int32_t* rpat = nullptr;
   const uint16_t* didx = nullptr;
   const uint16_t* col16 = nullptr;
   const int32_t* base = nullptr;

@@ -10,7 +10,11 @@
 //                      enter the multiply-adds as scalar operands
 //            general   a 16-bit block number per row and slot, the block read per lane
 //   columns  uniform   all rows have the same column offsets: nothing is stored per row, the
-//                      64 lanes read the neighbours' vector as one run
+//                      64 lanes read the neighbours' vector as one run.  With several
+//                      components the runs are staged in LDS: a lane's B values lie B apart, so
+//                      reading them slot by slot touches every cache line several times (64 tag
+//                      accesses per slot and wave on 129^3 elasticity, 87% of that sweep's
+//                      cycles), and the 3 slots of a mesh line read almost the same run
 //            16-bit    offsets from the slot's smallest column (32-bit where they do not fit)
 //
 // The sliced-ELL form of the same operator streams 8 B^2 + 2 bytes per block; here a block
@@ -20,12 +24,11 @@
 // slots run in the row's order and the B products of a block in component order with the
 // sliced-ELL kernels' expressions, so every result has the same bits.
 //
-// Measured, finest-level FP64 sweep, sliced ELL and node form: 129^3 elasticity (98% of the
-// slots in fully uniform slices) 838 and 103 us, 1.0M-node 2D annulus mesh (89%) 18.7 and
-// 12.7 us, uniform 1025^2 mesh 18.8 and 11.3 us; FP16-value sweep of the face-refined
-// elasticity mesh (84% uniform values, mostly 16-bit columns) 96 and 39 us.  The 129^3 sweep
-// moves 170 MB of vectors: what bounds it now is the waves' instruction issue and cached vector
-// reads (27 slots x 3 reads per lane), not HBM.
+// Measured, finest-level FP64 sweep, sliced ELL and node form: 129^3 elasticity (staged runs)
+// 838 and 66 us, face-refined elasticity (43% of the slices with 16-bit columns) 243 and 51 us
+// (FP16 values 96 and 32 us), 1.0M-node 2D annulus mesh 18.7 and 12.8 us, uniform 1025^2 mesh
+// 18.8 and 11.3 us.  The 129^3 sweep moves 170 MB of vectors (31 us at the copy rate); the rest
+// is the chain of a wave's dependent reads (descriptor, positions, runs, three phases).
 #include "mgq1_device.h"
 
 namespace mgq1 {
@@ -39,9 +42,14 @@ __device__ __forceinline__ ConstPtr<T> as_const(const void* p) {
   return (ConstPtr<T>)(reinterpret_cast<unsigned long long>(p));
 }
 
-// slots whose vector loads are issued together: a 9-point row in one batch, a 27-point row
-// in three (4 components: their 8 registers per slot allow fewer)
-template <int B> constexpr int node_batch_size() { return B == 4 ? 5 : 9; }
+// Slots whose vector loads are issued together.  Deep batches: a 9-point row in one, a 27-point
+// row in three.  Shallow ones leave registers for 6 instead of 4 waves per SIMD in the FP64
+// kernels of 2 and 3 components: better where most slices read staged runs from LDS
+// (129^3 elasticity sweep 66 us, deep 78 us), worse where they gather from memory (face-refined
+// elasticity 62 and 51 us); chosen per level by its slices (NodeDev::shallow).
+template <bool DEEP> constexpr int node_batch_size() { return DEEP ? 9 : 3; }
+template <bool DEEP> constexpr int node_min_waves() { return DEEP ? 1 : 6; }
+constexpr int kRunBatch = 3;          // slots read from LDS together
 // slots whose uniform blocks are read together: about 56 scalar registers of them
 template <int B, class T> constexpr int scalar_group() {
   constexpr int g = 56 / (B * B * int(sizeof(T)) / 4);
@@ -170,26 +178,130 @@ __device__ __forceinline__ void node_rest(int rem, const NodeDev& A, const NodeL
   }
 }
 
-template <int B, class T, class G, int NR, bool VU, int CK>
+template <int B, class T, class G, int NR, bool VU, int CK, bool DEEP>
 __device__ __forceinline__ void node_loop(const NodeDev& A, const NodeLane& s, int lane, const G& gx, T (&acc)[B]) {
-  constexpr int KB = node_batch_size<B>();
+  constexpr int KB = node_batch_size<DEEP>();
   int k = 0;
   for (; k + KB <= s.width; k += KB) node_batch<KB, B, T, G, NR, VU, CK>(A, s, lane, k, gx, acc);
   node_rest<KB - 1, B, T, G, NR, VU, CK>(s.width - k, A, s, lane, k, gx, acc);
 }
 
+// One slice whose offsets form runs: per phase up to three runs of consecutive columns are read
+// with full cache lines, put into the wave's LDS area, and the phase's slots read from there
+// (lane stride B elements: no bank conflicts for B = 3).  The next phase's reads are in flight
+// during a phase's products.
+template <class X, int B> constexpr int stage_elems() { return kPhaseRuns * kRunStride * B; }
+
+template <int NB, int B, class T, class X>
+__device__ __forceinline__ void run_batch(const NodeDev& A, const NodeLane& s, int k, ConstPtr<int> place,
+                                          const X* stage, int rel, T (&acc)[B]) {
+  X v[NB][B];
+#pragma unroll
+  for (int q = 0; q < NB; ++q)
+#pragma unroll
+    for (int c = 0; c < B; ++c) v[q][c] = stage[place[k + q] * B + rel + c];
+  const ConstPtr<T> a = as_const<T>(A.vtab) + (int64_t(s.iv) + k) * (B * B);
+  constexpr int G0 = scalar_group<B, T>();
+#pragma unroll
+  for (int q0 = 0; q0 < NB; q0 += G0) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = q0; q < (q0 + G0 < NB ? q0 + G0 : NB); ++q)
+#pragma unroll
+      for (int c = 0; c < B; ++c)
+#pragma unroll
+        for (int cc = 0; cc < B; ++cc) acc[c] += a[q * B * B + c * B + cc] * T(v[q][cc]);
+  }
+}
+
+template <int N, int B, class T, class X>
+__device__ __forceinline__ void run_rest(int rem, const NodeDev& A, const NodeLane& s, int k, ConstPtr<int> place,
+                                         const X* stage, int rel, T (&acc)[B]) {
+  if constexpr (N >= 1) {
+    if (rem == N) run_batch<N, B, T, X>(A, s, k, place, stage, rel, acc);
+    else run_rest<N - 1, B, T, X>(rem, A, s, k, place, stage, rel, acc);
+  }
+}
+
+template <int B, class T, class X>
+__device__ __forceinline__ void node_runs(const NodeDev& A, const NodeLane& s, int lane, const X* __restrict__ x,
+                                          X* stage, T (&acc)[B]) {
+  constexpr int NLD = (kRunStride * B + kWave - 1) / kWave;
+  constexpr int KB = kRunBatch;
+  const ConstPtr<int> rec = as_const<int>(A.rpat) + s.ic;
+  const int nph = rec[0];
+  const ConstPtr<int> place = rec + 1 + nph * kPhaseInts;
+  const int node0 = __builtin_amdgcn_readlane(s.node, 0);
+  const int span = __builtin_amdgcn_readlane(s.node, kWave - 1) - node0 + 1;
+  const int rel = (s.node - node0) * B;
+  X v[kPhaseRuns][NLD];
+  auto load = [&](int p) {
+    const ConstPtr<int> ph = rec + 1 + p * kPhaseInts;
+#pragma unroll
+    for (int q = 0; q < kPhaseRuns; ++q) {
+      // columns node0 + start .. node0 + start + span + width - 2: the first is a column of
+      // the first row, the last one of the last row, so all are in range
+      const int w = ph[2 + 2 * q], cnt = w > 0 ? (span + w - 1) * B : 0;
+      const X* src = x + int64_t(node0 + ph[1 + 2 * q]) * B;
+#pragma unroll
+      for (int u = 0; u < NLD; ++u) {
+        const int e = lane + u * kWave;
+        if (e < cnt) v[q][u] = src[e];
+      }
+    }
+  };
+  load(0);
+  int k = 0;
+  for (int p = 0; p < nph; ++p) {
+    const ConstPtr<int> ph = rec + 1 + p * kPhaseInts;
+#pragma unroll
+    for (int q = 0; q < kPhaseRuns; ++q) {
+      const int w = ph[2 + 2 * q], cnt = w > 0 ? (span + w - 1) * B : 0;
+#pragma unroll
+      for (int u = 0; u < NLD; ++u) {
+        const int e = lane + u * kWave;
+        if (e < cnt) stage[q * kRunStride * B + e] = v[q][u];
+      }
+    }
+    // the wave's LDS accesses execute in order; the fences keep the compiler's order too
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (p + 1 < nph) load(p + 1);
+    const int k1 = ph[0];
+    for (; k + KB <= k1; k += KB) run_batch<KB, B, T, X>(A, s, k, place, stage, rel, acc);
+    run_rest<KB - 1, B, T, X>(k1 - k, A, s, k, place, stage, rel, acc);
+    k = k1;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// this wave's staging area (none for one component)
+template <class X, int B>
+__device__ __forceinline__ X* wave_stage() {
+  if constexpr (B == 1) {
+    return nullptr;
+  } else {
+    __shared__ X area[kSliceWaves][stage_elems<X, B>()];
+    return area[int(threadIdx.x) / kWave];
+  }
+}
+
 // the B row sums of the lane's node; T is also the type of the block tables
-template <int B, class T, class G, int NR>
-__device__ __forceinline__ void node_dot(const NodeDev& A, const NodeLane& s, int lane, const G& gx, T (&acc)[B]) {
+template <int B, class T, class G, int NR, bool DEEP>
+__device__ __forceinline__ void node_dot(const NodeDev& A, const NodeLane& s, int lane, const G& gx,
+                                         typename G::raw* stage, T (&acc)[B]) {
 #pragma unroll
   for (int c = 0; c < B; ++c) acc[c] = T(0);
   if (s.flags & kNodeValUniform) {
-    if (s.flags & kNodeColUniform) node_loop<B, T, G, NR, true, 0>(A, s, lane, gx, acc);
-    else if (s.flags & kNodeCol32) node_loop<B, T, G, NR, true, 2>(A, s, lane, gx, acc);
-    else node_loop<B, T, G, NR, true, 1>(A, s, lane, gx, acc);
+    if (B >= 2 && (s.flags & kNodeRuns)) {
+      if constexpr (B >= 2) node_runs<B, T, typename G::raw>(A, s, lane, gx.x, stage, acc);
+    } else if (s.flags & kNodeColUniform) node_loop<B, T, G, NR, true, 0, DEEP>(A, s, lane, gx, acc);
+    else if (s.flags & kNodeCol32) node_loop<B, T, G, NR, true, 2, DEEP>(A, s, lane, gx, acc);
+    else node_loop<B, T, G, NR, true, 1, DEEP>(A, s, lane, gx, acc);
   } else {
-    if (s.flags & kNodeCol32) node_loop<B, T, G, NR, false, 2>(A, s, lane, gx, acc);
-    else node_loop<B, T, G, NR, false, 1>(A, s, lane, gx, acc);
+    if (s.flags & kNodeCol32) node_loop<B, T, G, NR, false, 2, DEEP>(A, s, lane, gx, acc);
+    else node_loop<B, T, G, NR, false, 1, DEEP>(A, s, lane, gx, acc);
   }
   if (A.rexp) {
 #pragma unroll
@@ -223,10 +335,10 @@ __device__ __forceinline__ void node_smoother(const NodeDev& A, const NodeLane& 
 }
 
 // y = A x (MODE 0), b - A x (MODE 1), M (b - A x) (MODE 2); NORM: partial sums of squares
-template <int B, class XI, class XO, int MODE, bool NORM>
-__global__ __launch_bounds__(kThreads) void k_node_spmv(NodeDev A, const XO* __restrict__ b, const XI* __restrict__ x,
-                                                        XO* __restrict__ y, const uint8_t* __restrict__ mask,
-                                                        double* __restrict__ partials) {
+template <int B, class XI, class XO, int MODE, bool NORM, bool DEEP>
+__global__ __launch_bounds__(kThreads, node_min_waves<DEEP>()) void k_node_spmv(
+    NodeDev A, const XO* __restrict__ b, const XI* __restrict__ x, XO* __restrict__ y,
+    const uint8_t* __restrict__ mask, double* __restrict__ partials) {
   using T = XO;
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
   const int lane = int(threadIdx.x) % kWave;
@@ -244,7 +356,7 @@ __global__ __launch_bounds__(kThreads) void k_node_spmv(NodeDev A, const XO* __r
     }
     T acc[B];
     const GatherX<B, XI> gx{x};
-    node_dot<B, T, GatherX<B, XI>, B>(A, s, lane, gx, acc);
+    node_dot<B, T, GatherX<B, XI>, B, DEEP>(A, s, lane, gx, wave_stage<XI, B>(), acc);
     if (s.valid) {
 #pragma unroll
       for (int c = 0; c < B; ++c) {
@@ -263,9 +375,9 @@ __global__ __launch_bounds__(kThreads) void k_node_spmv(NodeDev A, const XO* __r
 }
 
 // x_out = x + omega S (b - A x), and the three-term (Chebyshev) form as in sweep_slice
-template <int B, class X>
-__global__ __launch_bounds__(kThreads) void k_node_sweep(NodeDev A, const X* __restrict__ b, const X* __restrict__ x,
-                                                         X* xo, X omega, X beta, int pmode) {
+template <int B, class X, bool DEEP>
+__global__ __launch_bounds__(kThreads, node_min_waves<DEEP>()) void k_node_sweep(
+    NodeDev A, const X* __restrict__ b, const X* __restrict__ x, X* xo, X omega, X beta, int pmode) {
   using T = X;
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
   const int lane = int(threadIdx.x) % kWave;
@@ -283,7 +395,7 @@ __global__ __launch_bounds__(kThreads) void k_node_sweep(NodeDev A, const X* __r
   }
   T acc[B];
   const GatherX<B, X> gx{x};
-  node_dot<B, T, GatherX<B, X>, B>(A, s, lane, gx, acc);
+  node_dot<B, T, GatherX<B, X>, B, DEEP>(A, s, lane, gx, wave_stage<X, B>(), acc);
   node_smoother<B, X>(A, s, sv);
   T res[B];
 #pragma unroll
@@ -337,7 +449,7 @@ __global__ __launch_bounds__(kThreads) void k_node_sweep2z(NodeDev A, const X* _
   const X si = S[s.node], bi = b[s.node];
   T acc[1];
   const GatherZ<X, T> gz{S, b, omega};
-  node_dot<1, T, GatherZ<X, T>, 2>(A, s, lane, gz, acc);
+  node_dot<1, T, GatherZ<X, T>, 2, true>(A, s, lane, gz, nullptr, acc);
   if (!s.valid) return;
   const X x1 = X(omega * (T(0) + T(si) * T(bi)));
   const T res = T(bi) - acc[0];
@@ -374,19 +486,34 @@ __global__ __launch_bounds__(256) void k_expand_smoother(int n, int bb, const in
   for (int z = 0; z < bb; ++z) S[node * bb + z] = stab[int64_t(sidx[pos]) * bb + z];
 }
 
-template <int B, class XI, class XO>
-hipError_t node_spmv_t(const NodeDev& A, const void* b, const void* x, void* y, const uint8_t* mask, int mode,
+// the kernels with a choice of batch: FP64 sums of 2 and 3 components (4 exceed the registers of
+// 6 waves either way)
+template <int B, class T> constexpr bool has_shallow() { return (B == 2 || B == 3) && sizeof(T) == 8; }
+
+template <int B, class XI, class XO, bool DEEP>
+hipError_t node_spmv_d(const NodeDev& A, const void* b, const void* x, void* y, const uint8_t* mask, int mode,
                        double* partials, hipStream_t s) {
   const unsigned g = slice_grid(A.nslices);
   const XO* bb = static_cast<const XO*>(b);
   const XI* xx = static_cast<const XI*>(x);
   XO* yy = static_cast<XO*>(y);
-  if (mode == 0 && !partials) hipLaunchKernelGGL((k_node_spmv<B, XI, XO, 0, false>), g, kThreads, 0, s, A, bb, xx, yy, mask, partials);
-  else if (mode == 1 && partials) hipLaunchKernelGGL((k_node_spmv<B, XI, XO, 1, true>), g, kThreads, 0, s, A, bb, xx, yy, mask, partials);
-  else if (mode == 1) hipLaunchKernelGGL((k_node_spmv<B, XI, XO, 1, false>), g, kThreads, 0, s, A, bb, xx, yy, mask, partials);
-  else if (mode == 2 && !partials) hipLaunchKernelGGL((k_node_spmv<B, XI, XO, 2, false>), g, kThreads, 0, s, A, bb, xx, yy, mask, partials);
+#define MGQ1_NS(MODE, NORM) \
+  hipLaunchKernelGGL((k_node_spmv<B, XI, XO, MODE, NORM, DEEP>), g, kThreads, 0, s, A, bb, xx, yy, mask, partials)
+  if (mode == 0 && !partials) MGQ1_NS(0, false);
+  else if (mode == 1 && partials) MGQ1_NS(1, true);
+  else if (mode == 1) MGQ1_NS(1, false);
+  else if (mode == 2 && !partials) MGQ1_NS(2, false);
   else return hipErrorInvalidValue;
+#undef MGQ1_NS
   return hipGetLastError();
+}
+
+template <int B, class XI, class XO>
+hipError_t node_spmv_t(const NodeDev& A, const void* b, const void* x, void* y, const uint8_t* mask, int mode,
+                       double* partials, hipStream_t s) {
+  if constexpr (has_shallow<B, XO>())
+    if (A.shallow) return node_spmv_d<B, XI, XO, false>(A, b, x, y, mask, mode, partials, s);
+  return node_spmv_d<B, XI, XO, true>(A, b, x, y, mask, mode, partials, s);
 }
 
 template <int B>
@@ -402,8 +529,16 @@ hipError_t node_spmv_b(const NodeDev& A, const void* b, const void* x, void* y, 
 template <int B, class X>
 hipError_t node_sweep_t(const NodeDev& A, const void* b, const void* x, void* xo, double omega, double beta, int pmode,
                         hipStream_t s) {
-  hipLaunchKernelGGL((k_node_sweep<B, X>), slice_grid(A.nslices), kThreads, 0, s, A, static_cast<const X*>(b),
-                     static_cast<const X*>(x), static_cast<X*>(xo), X(omega), X(beta), pmode);
+  const unsigned g = slice_grid(A.nslices);
+  const X *bb = static_cast<const X*>(b), *xx = static_cast<const X*>(x);
+  X* oo = static_cast<X*>(xo);
+  if constexpr (has_shallow<B, X>()) {
+    if (A.shallow) {
+      hipLaunchKernelGGL((k_node_sweep<B, X, false>), g, kThreads, 0, s, A, bb, xx, oo, X(omega), X(beta), pmode);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((k_node_sweep<B, X, true>), g, kThreads, 0, s, A, bb, xx, oo, X(omega), X(beta), pmode);
   return hipGetLastError();
 }
 

@@ -23,7 +23,7 @@ struct NodeHost {
   std::vector<double> dict;             // distinct blocks (number 0: the zero block)
   std::vector<int8_t> dexp;             // their rows' exponents (with_exp), B per block
   std::vector<int32_t> vlist;           // block numbers of the uniform rows, row after row
-  std::vector<int32_t> opat;
+  std::vector<int32_t> opat, rpat;
   std::vector<uint16_t> didx, col16, sidx;
   std::vector<int32_t> base, col32;
   std::vector<int32_t> sblock;          // block number behind each smoother table entry
@@ -86,10 +86,6 @@ struct BlockSet {
 };
 
 constexpr int32_t kMaxBlocks = 65535;
-// rows of a window are regrouped by content: large enough that a kind of row with 2% of the
-// rows still fills slices of its own, small enough that a slice's vector reads stay in L2
-// (129^3 elasticity: 1.6% of the slots in general slices)
-constexpr int64_t kWindow = 4096;
 
 }  // namespace nodebuild
 
@@ -234,78 +230,99 @@ bool build_node(int32_t n, int B, const int32_t* rowptr, const int32_t* col, con
   ho.clear();
   ho.shrink_to_fit();
   auto len_of = [&](int32_t i) { return rowptr[i + 1] - rowptr[i]; };
-  // bytes per slot row of 64 lanes that a slice of the rows pos[0 .. cnt) reads, times its width
-  auto slice_cost = [&](const int32_t* node, int cnt) {
-    int32_t w = 0;
-    bool vu = vn[size_t(node[0])] >= 0, ou = on[size_t(node[0])] >= 0;
-    for (int r = 0; r < cnt; ++r) {
-      w = std::max(w, len_of(node[r]));
-      vu = vu && vn[size_t(node[r])] == vn[size_t(node[0])];
-      ou = ou && on[size_t(node[r])] == on[size_t(node[0])];
-    }
-    return int64_t(w) * (vu ? (ou ? 8 : 128 + 8) : 256 + 128);
+  // bytes that the slices of 64 rows order[0 .. n) read per slot row of 64 lanes, times their
+  // widths (general values also cost a scattered block read per lane)
+  auto cost_of = [&](const std::vector<int32_t>& order) {
+    std::vector<int64_t> part(size_t(nchunk), 0);
+    const int64_t sper = (H.nslices + nchunk - 1) / nchunk;
+    parallel_for(nchunk, 1, [&](int64_t c0, int64_t c1) {
+      for (int64_t c = c0; c < c1; ++c)
+        for (int64_t s = c * sper; s < std::min<int64_t>(H.nslices, (c + 1) * sper); ++s) {
+          const int32_t* node = &order[size_t(s) * kWave];
+          const int cnt = int(std::min<int64_t>(kWave, n - s * kWave));
+          int32_t w = 0;
+          bool vu = vn[size_t(node[0])] >= 0, ou = on[size_t(node[0])] >= 0;
+          for (int r = 0; r < cnt; ++r) {
+            w = std::max(w, len_of(node[r]));
+            vu = vu && vn[size_t(node[r])] == vn[size_t(node[0])];
+            ou = ou && on[size_t(node[r])] == on[size_t(node[0])];
+          }
+          part[size_t(c)] += int64_t(w) * (vu ? (ou ? 8 : 128 + 8) : 256 + 64 * 8 * BB);
+        }
+    });
+    int64_t t = 0;
+    for (int64_t v : part) t += v;
+    return t;
   };
-  // ---- grouping: inside windows of rows, whole slices of equal values and offsets first, then
-  // of equal values, the rest by length; slices in the order of their first row
+  // ---- grouping: the rows of equal values and offsets in whole slices of 64, node order inside a
+  // group; then the rest of each kind of values in whole slices; what is left by length.  The
+  // whole slices follow each other in the order of their first row, so that neighbours in the
+  // mesh stay near each other in the launch.  Over the whole level: what is left is then less
+  // than a slice per kind of row.  (Inside windows of 4,096 rows 5% of the slots of the 65^3
+  // elasticity level were in general slices, whose scattered block reads took a third of the
+  // sweep: 23.6 us against 15.9 us with windows of 32,768.)
   std::vector<int32_t> order(static_cast<size_t>(n));
   for (int32_t i = 0; i < n; ++i) order[size_t(i)] = i;
-  const int64_t nwin = (int64_t(n) + kWindow - 1) / kWindow;
-  std::vector<int64_t> cost0(size_t(nwin), 0), cost1(size_t(nwin), 0);
-  parallel_for(nwin, 1, [&](int64_t w0, int64_t w1) {
-    int32_t rows[kWindow], left[kWindow], out[kWindow];
-    std::pair<int32_t, int32_t> first[kWindow / kWave + 1];
-    for (int64_t w = w0; w < w1; ++w) {
-      const int32_t a = int32_t(w * kWindow), cnt = int32_t(std::min<int64_t>(kWindow, n - int64_t(a)));
-      for (int32_t i = 0; i < cnt; ++i) rows[i] = a + i;
-      for (int32_t p = 0; p < cnt; p += kWave) cost0[size_t(w)] += slice_cost(rows + p, std::min(kWave, cnt - p));
-      int32_t nout = 0, nleft = cnt;
-      for (int pass = 0; pass < 2; ++pass) {
-        // runs of equal keys, longest rows first inside the sort only to keep it a total order
-        const bool both = pass == 0;
-        std::sort(rows, rows + nleft, [&](int32_t i, int32_t j) {
-          if (vn[size_t(i)] != vn[size_t(j)]) return vn[size_t(i)] < vn[size_t(j)];
-          if (both && on[size_t(i)] != on[size_t(j)]) return on[size_t(i)] < on[size_t(j)];
-          return i < j;
-        });
-        int32_t nl = 0;
-        for (int32_t p = 0; p < nleft;) {
-          int32_t q = p;
-          while (q < nleft && vn[size_t(rows[q])] == vn[size_t(rows[p])] &&
-                 (!both || on[size_t(rows[q])] == on[size_t(rows[p])]))
-            ++q;
-          const bool known = vn[size_t(rows[p])] >= 0 && (!both || on[size_t(rows[p])] >= 0);
-          const int32_t whole = known ? (q - p) / kWave * kWave : 0;
-          for (int32_t z = 0; z < whole; ++z) out[nout++] = rows[p + z];
-          for (int32_t z = p + whole; z < q; ++z) left[nl++] = rows[z];
-          p = q;
+  const int64_t cost0 = cost_of(order);
+  {
+    std::vector<int32_t> grouped, left, rows(order);
+    grouped.reserve(size_t(n));
+    for (int pass = 0; pass < 2; ++pass) {
+      // group number of every row: values and offsets, then values
+      std::unordered_map<uint64_t, int32_t> m;
+      std::vector<int32_t> count, gid(rows.size());
+      uint64_t lastk = 0;
+      int32_t last = -1;
+      for (size_t q = 0; q < rows.size(); ++q) {
+        const int32_t i = rows[q], v = vn[size_t(i)], o = on[size_t(i)];
+        if (v < 0 || (pass == 0 && o < 0)) {
+          gid[q] = -1;
+          continue;
         }
-        nleft = nl;
-        for (int32_t z = 0; z < nleft; ++z) rows[z] = left[z];
+        const uint64_t k = uint64_t(uint32_t(v)) << 32 | (pass == 0 ? uint32_t(o) : 0u);
+        if (last < 0 || k != lastk) {
+          const auto it = m.emplace(k, int32_t(count.size()));
+          if (it.second) count.push_back(0);
+          last = it.first->second;
+          lastk = k;
+        }
+        gid[q] = last;
+        ++count[size_t(last)];
       }
-      std::sort(rows, rows + nleft, [&](int32_t i, int32_t j) {
-        const int32_t li = len_of(i), lj = len_of(j);
-        return li != lj ? li > lj : i < j;
-      });
-      // the leftover rows follow the whole slices; whole slices in the order of their first row
-      const int32_t ns = nout / kWave;
-      for (int32_t z = 0; z < ns; ++z) first[z] = {out[z * kWave], z};
-      std::sort(first, first + ns);
-      for (int32_t z = 0; z < ns; ++z)
-        std::memcpy(&order[size_t(a) + size_t(z) * kWave], &out[first[z].second * kWave], kWave * sizeof(int32_t));
-      for (int32_t z = 0; z < nleft; ++z) order[size_t(a) + nout + z] = rows[z];
-      for (int32_t p = 0; p < cnt; p += kWave)
-        cost1[size_t(w)] += slice_cost(&order[size_t(a) + p], std::min(kWave, cnt - p));
+      std::vector<int64_t> at(count.size());
+      std::vector<int32_t> room(count.size());
+      int64_t fill = int64_t(grouped.size());
+      for (size_t g = 0; g < count.size(); ++g) {
+        at[g] = fill;
+        room[g] = count[g] / kWave * kWave;
+        fill += room[g];
+      }
+      grouped.resize(size_t(fill));
+      left.clear();
+      for (size_t q = 0; q < rows.size(); ++q) {
+        const int32_t g = gid[q];
+        if (g >= 0 && room[size_t(g)] > 0) {
+          grouped[size_t(at[size_t(g)]++)] = rows[q];
+          --room[size_t(g)];
+        } else {
+          left.push_back(rows[q]);
+        }
+      }
+      rows.swap(left);
     }
-  });
-  int64_t c0 = 0, c1 = 0;
-  for (int64_t w = 0; w < nwin; ++w) {
-    c0 += cost0[size_t(w)];
-    c1 += cost1[size_t(w)];
+    const int64_t ns = int64_t(grouped.size()) / kWave;
+    std::vector<std::pair<int32_t, int32_t>> first(static_cast<size_t>(ns));
+    for (int64_t z = 0; z < ns; ++z) first[size_t(z)] = {grouped[size_t(z) * kWave], int32_t(z)};
+    std::sort(first.begin(), first.end());
+    for (int64_t z = 0; z < ns; ++z)
+      std::memcpy(&order[size_t(z) * kWave], &grouped[size_t(first[size_t(z)].second) * kWave], kWave * sizeof(int32_t));
+    std::stable_sort(rows.begin(), rows.end(), [&](int32_t i, int32_t j) { return len_of(i) > len_of(j); });
+    std::copy(rows.begin(), rows.end(), order.begin() + ns * kWave);
   }
   // regroup when that saves 3% of what the kernels read (the vectors: about 24 B bytes per
   // row; the position list costs 4)
   const int64_t vec = int64_t(n) * 24 * B;
-  if ((c1 + 4 * int64_t(n) + vec) * 100 <= (c0 + vec) * 97) H.perm = std::move(order);
+  if ((cost_of(order) + 4 * int64_t(n) + vec) * 100 <= (cost0 + vec) * 97) H.perm = std::move(order);
   order.clear();
   order.shrink_to_fit();
   // ---- descriptors
@@ -339,8 +356,42 @@ bool build_node(int32_t n, int B, const int32_t* rowptr, const int32_t* col, con
       H.desc[size_t(s) * 4 + 1] = flags;
     }
   });
+  // the run record of a row's offsets (see NodeDev), appended to rpat; -1: it has none
+  auto run_record = [&](int32_t i) -> int32_t {
+    const int32_t len = len_of(i);
+    const int32_t* cl = col + rowptr[i];
+    std::vector<int32_t> start, end, run(static_cast<size_t>(len));   // runs, first and last slot + 1
+    for (int32_t k = 0; k < len; ++k) {
+      if (start.empty() || cl[k] - cl[start.back()] >= kRunWidth) {
+        start.push_back(k);
+        end.push_back(k);
+      }
+      end.back() = k + 1;
+      run[size_t(k)] = int32_t(start.size()) - 1;
+    }
+    const int32_t nrun = int32_t(start.size()), nph = (nrun + kPhaseRuns - 1) / kPhaseRuns;
+    // a run is worth staging when its columns are read more than once
+    if (nrun * 2 > len) return -1;
+    const int32_t at = int32_t(H.rpat.size());
+    H.rpat.push_back(nph);
+    for (int32_t p = 0; p < nph; ++p) {
+      const int32_t last = std::min(nrun, (p + 1) * kPhaseRuns) - 1;
+      H.rpat.push_back(end[size_t(last)]);
+      for (int32_t q = 0; q < kPhaseRuns; ++q) {
+        const int32_t r = p * kPhaseRuns + q;
+        H.rpat.push_back(r < nrun ? cl[start[size_t(r)]] - i : 0);
+        H.rpat.push_back(r < nrun ? cl[end[size_t(r)] - 1] - cl[start[size_t(r)]] + 1 : 0);
+      }
+      H.rpat.push_back(0);
+    }
+    for (int32_t k = 0; k < len; ++k) {
+      const int32_t r = run[size_t(k)];
+      H.rpat.push_back((r % kPhaseRuns) * kRunStride + cl[k] - cl[start[size_t(r)]]);
+    }
+    return at;
+  };
   // places in the arrays (sequential), the lists of the uniform rows
-  std::vector<int32_t> vstart(vrep.size(), -1), ostart(orep.size(), -1);
+  std::vector<int32_t> vstart(vrep.size(), -1), ostart(orep.size(), -1), rstart(orep.size(), -2);
   int64_t nd = 0, n16 = 0, n32 = 0;
   for (int64_t s = 0; s < H.nslices; ++s) {
     int32_t* d = &H.desc[size_t(s) * 4];
@@ -365,6 +416,15 @@ bool build_node(int32_t n, int B, const int32_t* rowptr, const int32_t* col, con
         for (int64_t k = rowptr[i0]; k < rowptr[i0 + 1]; ++k) H.opat.push_back(col[k] - i0);
       }
       d[3] = o;
+      const int32_t il = H.node_at(std::min<int64_t>(s * kWave + kWave, n) - 1);
+      if (B >= 2 && il - i0 < kRunSpan) {
+        int32_t& r = rstart[size_t(on[size_t(i0)])];
+        if (r == -2) r = run_record(i0);
+        if (r >= 0) {
+          d[1] |= kNodeRuns;
+          d[3] = r;
+        }
+      }
     } else if (d[1] & kNodeCol32) {
       d[3] = int32_t(n32);
       n32 += w;

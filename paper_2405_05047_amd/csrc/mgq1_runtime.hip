@@ -754,6 +754,9 @@ int setup_node(DevOwner* h, const HostLevel& L, int vkind, int xk, bool must, in
   N.n = L.n;
   N.B = B;
   N.nslices = H->nslices;
+  int64_t runs = 0;
+  for (int64_t q = 0; q < H->nslices; ++q) runs += (H->desc[size_t(q) * 4 + 1] & kNodeRuns) != 0;
+  N.shallow = runs * 2 > H->nslices ? 1 : 0;
   int rc;
   auto put = [&](auto& dst, const auto& src) -> int {
     using T = std::remove_const_t<std::remove_pointer_t<std::remove_reference_t<decltype(dst)>>>;
@@ -763,6 +766,7 @@ int setup_node(DevOwner* h, const HostLevel& L, int vkind, int xk, bool must, in
     return e;
   };
   if ((rc = put(N.desc, H->desc)) || (rc = put(N.perm, H->perm)) || (rc = put(N.opat, H->opat)) ||
+      (rc = put(N.rpat, H->rpat)) ||
       (rc = put(N.didx, H->didx)) || (rc = put(N.col16, H->col16)) || (rc = put(N.base, H->base)) ||
       (rc = put(N.col32, H->col32)))
     return rc;

@@ -28,14 +28,14 @@ def check(tmp_path_factory):
         rowptr, col = np.ascontiguousarray(rowptr, np.int32), np.ascontiguousarray(col, np.int32)
         val = np.ascontiguousarray(val, np.float64)
         x = W.rand_vec(77, n * B) if x is None else x
-        y, st = np.zeros(n * B), np.zeros(8, np.int64)
+        y, st = np.zeros(n * B), np.zeros(9, np.int64)
         p = lambda a: None if a is None else a.ctypes.data_as(C.c_void_p)  # noqa: E731
         rc = f(C.c_int32(n), C.c_int32(B), p(rowptr), p(col), p(val), p(exps), C.c_int32(int(must)), p(x), p(y),
                p(st))
         assert rc >= 0, rc
         if rc:
             assert np.array_equal(y, _product(rowptr, col, val, x))
-        return rc, dict(zip(("slices", "slots", "general", "vu", "cu", "c32", "blocks", "regrouped"), st.tolist()))
+        return rc, dict(zip(("slices", "slots", "general", "vu", "cu", "c32", "blocks", "regrouped", "runs"), st.tolist()))
 
     return run
 
@@ -64,7 +64,7 @@ def _fma(a, b, c):
 
 
 CASES = {
-    "poisson": W.c1_poisson(4), "td_band": W.c2_td(band_rounds=2, uniform_rounds=1), "elast9": W.c3_elasticity(2),
+    "poisson": W.c1_poisson(4), "td_band": W.c2_td(band_rounds=2, uniform_rounds=1), "elast9": W.c3_elasticity(2), "elast17": W.c3_elasticity(3),
     "oseen9": W.c4_oseen(2), "face3": W.c3_adaptive("face", 3).with_(coarse=(2, 2, 2), h0=0.5),
     "time": W.td_time(5),
 }
@@ -82,6 +82,12 @@ def test_walk_equals_product(check, name):
         assert rc == 1 and st["slots"] * 64 >= len(lv.col)
         exps = np.clip(np.round(3 * W.rand_vec(5, lv.n * lv.block)), -2, 2).astype(np.int8)
         assert check(lv.rowptr, lv.col, lv.val, exps=exps)[0] == 1
+
+
+def test_uniform_elasticity_stages_runs(check):
+    lv = _levels("elast17")[-1]                    # 17^3 nodes, 3 components
+    rc, st = check(lv.rowptr, lv.col, lv.val, must=False)
+    assert rc == 1 and st["cu"] >= 0.9 * st["slices"] and st["runs"] >= 20
 
 
 def test_uniform_mesh_is_mostly_uniform_slices(check):
