@@ -230,11 +230,11 @@ int mg_level_tuning(const mg_handle* h, int32_t level, int32_t* slot_batch, int3
 
 /* Storage of the transfers between level `level` - 1 and `level` (level >= 1) on a
  * single-problem handle: bytes per stored column index of P~ and of R = P~^T, and bytes
- * per weight of P~.  (2, 2, 1): the node form (one lane per node; 16-bit column offsets
- * from a per-slot base and the weight code w * 128 packed with the column mask bits into
- * 32 bits), used when every weight is a multiple of 1/128 up to 255/128 (the weights of
- * nested box meshes) and every slot's columns span less than 2^16; else, level by level,
- * 4-byte columns and FP32 (4) weights when FP32 holds every weight exactly, FP64 (8)
+ * per weight of P~.  Weight bytes 1: the node form (one lane per node; the weight code
+ * w * 128 with the column mask bits in 16 bits), used when every weight is a multiple of 1/128
+ * up to 255/128 (the weights of nested box meshes), with 2-byte columns (offsets from a
+ * per-slot base) where every slot's columns span less than 2^16, else 4; other weights, level
+ * by level, 4-byte columns and FP32 (4) weights when FP32 holds every weight exactly, FP64 (8)
  * otherwise.  Every form gives the same bits (Sec. 4.1:
  * prolongation and restriction as sparse products).  Any output pointer may be NULL. */
 int mg_level_transfer_format(const mg_handle* h, int32_t level, int32_t* p_col_bytes, int32_t* r_col_bytes,

@@ -524,48 +524,67 @@ __global__ __launch_bounds__(kThreads) void k_tsell(TSellDev M, const X* __restr
 // with the same operands as the per-DoF form, so the sums are the same bit for bit.  A
 // wave issues one entry load per slot for 64 nodes where the per-DoF form issues an index,
 // a weight and a mask load per slot for 64 / B nodes.
-template <int NB, int B, class X, class T, bool MC>
-__device__ __forceinline__ void tnode_batch(const TSellDev& M, int k, int lane, const X* __restrict__ in,
-                                            T (&acc)[B]) {
-  uint32_t e[NB];
-  int32_t base[NB];
+//
+// WIDE: levels with a slot whose columns span 2^16 and more (adaptive 3D meshes) keep the
+// column in 32 bits and weight code and mask bits in another 16: 6 bytes per entry.
+template <int NB, int B, class X, bool WIDE>
+__device__ __forceinline__ void tnode_load(const TSellDev& M, int k, int last, int lane, const X* __restrict__ in,
+                                           uint32_t (&e)[NB], X (&v)[NB][B]) {
+  uint32_t j[NB];
 #pragma unroll
   for (int qq = 0; qq < NB; ++qq) {
-    e[qq] = M.ent[int64_t(k + qq) * kWave + lane];
-    base[qq] = M.colbase[k + qq];
-  }
-  __builtin_amdgcn_sched_barrier(0);
-  X v[NB][B];
-#pragma unroll
-  for (int qq = 0; qq < NB; ++qq) {
-    const uint64_t j = uint64_t(uint32_t(base[qq]) + (e[qq] & 0xffffu));
-#pragma unroll
-    for (int c = 0; c < B; ++c) v[qq][c] = in[j * B + c];
-  }
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int qq = 0; qq < NB; ++qq) {
-    const T w = T(float((e[qq] >> 16) & 0xffu) * 0.0078125f);
-#pragma unroll
-    for (int c = 0; c < B; ++c) {
-      const bool ms = MC && ((e[qq] >> (24 + c)) & 1u);
-      acc[c] += w * (ms ? T(0) : T(v[qq][c]));
+    const int kk = k + qq < last ? k + qq : last;          // past the end: the last slot again, not used
+    if constexpr (WIDE) {
+      j[qq] = uint32_t(M.col[int64_t(kk) * kWave + lane]);
+      e[qq] = uint32_t(M.cw[int64_t(kk) * kWave + lane]) << 16;
+    } else {
+      e[qq] = M.ent[int64_t(kk) * kWave + lane];
+      j[qq] = uint32_t(M.colbase[kk]);
     }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int qq = 0; qq < NB; ++qq) {
+    const uint64_t c0 = uint64_t(WIDE ? j[qq] : j[qq] + (e[qq] & 0xffffu)) * B;
+#pragma unroll
+    for (int c = 0; c < B; ++c) v[qq][c] = in[c0 + c];
+  }
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// the weighted sum of slot entry e in slot order
+template <int B, class X, class T, bool MC>
+__device__ __forceinline__ void tnode_add(uint32_t e, const X (&v)[B], T (&acc)[B]) {
+  const T w = T(float((e >> 16) & 0xffu) * 0.0078125f);
+#pragma unroll
+  for (int c = 0; c < B; ++c) {
+    const bool ms = MC && ((e >> (24 + c)) & 1u);
+    acc[c] += w * (ms ? T(0) : T(v[c]));
   }
 }
 
-template <int N, int B, class X, class T, bool MC>
+template <int NB, int B, class X, class T, bool MC, bool WIDE>
+__device__ __forceinline__ void tnode_batch(const TSellDev& M, int k, int lane, const X* __restrict__ in,
+                                            T (&acc)[B]) {
+  uint32_t e[NB];
+  X v[NB][B];
+  tnode_load<NB, B, X, WIDE>(M, k, k + NB - 1, lane, in, e, v);
+#pragma unroll
+  for (int qq = 0; qq < NB; ++qq) tnode_add<B, X, T, MC>(e[qq], v[qq], acc);
+}
+
+template <int N, int B, class X, class T, bool MC, bool WIDE>
 __device__ __forceinline__ void tnode_rest(int rem, const TSellDev& M, int k, int lane, const X* __restrict__ in,
                                            T (&acc)[B]) {
   if constexpr (N >= 1) {
-    if (rem == N) tnode_batch<N, B, X, T, MC>(M, k, lane, in, acc);
-    else tnode_rest<N - 1, B, X, T, MC>(rem, M, k, lane, in, acc);
+    if (rem == N) tnode_batch<N, B, X, T, MC, WIDE>(M, k, lane, in, acc);
+    else tnode_rest<N - 1, B, X, T, MC, WIDE>(rem, M, k, lane, in, acc);
   }
 }
 
 // MODE 0: out = restriction sum (zero on masked row DoFs); MODE 1: out += prolongation sum
 // (masked row DoFs left unchanged)
-template <int B, class X, class T, bool MC, int MODE>
+template <int B, class X, class T, bool MC, int MODE, bool WIDE>
 __device__ __forceinline__ void tnode_lane(const TSellDev& M, int slice, int lane, const X* __restrict__ in,
                                            X* __restrict__ out) {
   // slot batch: restriction rows hold up to 3^d entries (27 on 3D box meshes), prolongation
@@ -586,8 +605,8 @@ __device__ __forceinline__ void tnode_lane(const TSellDev& M, int slice, int lan
   T acc[B];
 #pragma unroll
   for (int c = 0; c < B; ++c) acc[c] = T(0);
-  for (; k + KB <= k1; k += KB) tnode_batch<KB, B, X, T, MC>(M, k, lane, in, acc);
-  tnode_rest<KB - 1, B, X, T, MC>(k1 - k, M, k, lane, in, acc);
+  for (; k + KB <= k1; k += KB) tnode_batch<KB, B, X, T, MC, WIDE>(M, k, lane, in, acc);
+  tnode_rest<KB - 1, B, X, T, MC, WIDE>(k1 - k, M, k, lane, in, acc);
 #pragma unroll
   for (int c = 0; c < B; ++c) {
     const bool masked = (rm >> c) & 1u;
@@ -596,10 +615,55 @@ __device__ __forceinline__ void tnode_lane(const TSellDev& M, int slice, int lan
   }
 }
 
-template <int B, class X, class T, bool MC, int MODE>
+// Restriction of a level with few slices: one slice per workgroup, a quarter of the slots per
+// wave, the sums passed on in slot order (the relay of the slice kernels).
+template <int B, class X, class T, bool MC, bool WIDE>
+__global__ __launch_bounds__(kThreads) void k_tnode_relay(TSellDev M, const X* __restrict__ in, X* __restrict__ out) {
+  constexpr int NB = 8;
+  __shared__ T sums[B][kWave];
+  const int slice = xcd_remap(blockIdx.x, gridDim.x);
+  const int lane = int(threadIdx.x) % kWave, w = int(threadIdx.x) / kWave;
+  const int node = slice * kWave + lane;
+  uint8_t rm = 0;
+  if (w == kSliceWaves - 1 && node < M.nrows) rm = M.rmask[node];
+  const int su = __builtin_amdgcn_readfirstlane(slice);
+  int k0, k1;
+  slot_range(M, su, k0, k1);
+  T acc[B];
+#pragma unroll
+  for (int c = 0; c < B; ++c) acc[c] = T(0);
+  for (int k = k0; k < k1; k += kSliceWaves * NB) {
+    const int left = k1 - k < kSliceWaves * NB ? k1 - k : kSliceWaves * NB;
+    const int per = (left + kSliceWaves - 1) / kSliceWaves;
+    const int first = w * per < left ? w * per : left;
+    const int cnt = left - first < per ? left - first : per;
+    uint32_t e[NB];
+    X v[NB][B];
+    if (cnt > 0) tnode_load<NB, B, X, WIDE>(M, k + first, k + first + cnt - 1, lane, in, e, v);
+    for (int turn = 0; turn < kSliceWaves; ++turn) {
+      if (turn == w) {
+        if (k > k0 || w > 0) {
+#pragma unroll
+          for (int c = 0; c < B; ++c) acc[c] = sums[c][lane];
+        }
+#pragma unroll
+        for (int qq = 0; qq < NB; ++qq)
+          if (qq < cnt) tnode_add<B, X, T, MC>(e[qq], v[qq], acc);
+#pragma unroll
+        for (int c = 0; c < B; ++c) sums[c][lane] = acc[c];
+      }
+      __syncthreads();
+    }
+  }
+  if (w != kSliceWaves - 1 || node >= M.nrows) return;
+#pragma unroll
+  for (int c = 0; c < B; ++c) out[int64_t(node) * B + c] = ((rm >> c) & 1u) ? X(0) : X(acc[c]);
+}
+
+template <int B, class X, class T, bool MC, int MODE, bool WIDE>
 __global__ __launch_bounds__(kThreads) void k_tnode(TSellDev M, const X* __restrict__ in, X* __restrict__ out) {
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
-  tnode_lane<B, X, T, MC, MODE>(M, bid * kSliceWaves + threadIdx.x / kWave, threadIdx.x % kWave, in, out);
+  tnode_lane<B, X, T, MC, MODE, WIDE>(M, bid * kSliceWaves + threadIdx.x / kWave, threadIdx.x % kWave, in, out);
 }
 
 // Gauss-Jordan with row pivoting on [M | I]; the right half becomes the inverse.  false: singular

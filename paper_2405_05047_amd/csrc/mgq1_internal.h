@@ -116,9 +116,13 @@ struct TSellDev {
   // colbase[k] | weight code (w * 128) << 16 | mask bits of the column's B DoFs << 24, and
   // rmask[node] = mask bits of the row's B DoFs
   int node = 0;
+  int64_t slots = 0;
   const uint32_t* ent = nullptr;
   const int32_t* colbase = nullptr;
   const uint8_t* rmask = nullptr;
+  // wide node form (cw set; ent and colbase absent): the column in col[k * 64 + r], the weight
+  // code | mask bits << 8 in cw[k * 64 + r]
+  const uint16_t* cw = nullptr;
 };
 
 // d = M_c P~^T M_f r (rows = coarse nodes; mask_f may be NULL) and x += M_f P~ M_c y

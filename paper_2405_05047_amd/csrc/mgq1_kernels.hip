@@ -563,21 +563,32 @@ hipError_t tsell_b(int mode, const TSellDev& M, const void* in, void* out, const
                : tsell_w<B, float, float, double>(mode, M, in, out, mrow, mcol, s);
 }
 
-template <int B, class X>
+// Restriction with one slice per workgroup (k_tnode_relay) where there are too few slices for
+// the CUs and rows of more than a batch; one wave per slice and relay: to 4,913 nodes (77
+// slices) 4 components 5.5 and 4.3 us, 3 components 4.5 and 4.1 us, to 14,620 nodes of the
+// face-refined mesh (229 slices, rows of up to 125 entries) 10.7 and 7.9 us; to 35,937 nodes (562
+// slices) 4.6 and 5.7 us.
+constexpr int kRestrictRelaySlices = 256;
+
+template <int B, class X, bool WIDE>
 hipError_t tnode_x(int mode, const TSellDev& M, const void* in, void* out, bool mc, hipStream_t s) {
   const unsigned g = slice_grid(M.nslices);
   if (g == 0) return hipSuccess;
   const X* ii = static_cast<const X*>(in);
   X* oo = static_cast<X*>(out);
-  if (mode == 1) hipLaunchKernelGGL((k_tnode<B, X, X, true, 1>), g, kThreads, 0, s, M, ii, oo);
-  else if (mc) hipLaunchKernelGGL((k_tnode<B, X, X, true, 0>), g, kThreads, 0, s, M, ii, oo);
-  else hipLaunchKernelGGL((k_tnode<B, X, X, false, 0>), g, kThreads, 0, s, M, ii, oo);
+  const bool relay = mode == 0 && M.nslices <= kRestrictRelaySlices && M.slots >= 12 * int64_t(M.nslices);
+  if (mode == 1) hipLaunchKernelGGL((k_tnode<B, X, X, true, 1, WIDE>), g, kThreads, 0, s, M, ii, oo);
+  else if (relay && mc) hipLaunchKernelGGL((k_tnode_relay<B, X, X, true, WIDE>), unsigned(M.nslices), kThreads, 0, s, M, ii, oo);
+  else if (relay) hipLaunchKernelGGL((k_tnode_relay<B, X, X, false, WIDE>), unsigned(M.nslices), kThreads, 0, s, M, ii, oo);
+  else if (mc) hipLaunchKernelGGL((k_tnode<B, X, X, true, 0, WIDE>), g, kThreads, 0, s, M, ii, oo);
+  else hipLaunchKernelGGL((k_tnode<B, X, X, false, 0, WIDE>), g, kThreads, 0, s, M, ii, oo);
   return hipGetLastError();
 }
 
 template <int B>
 hipError_t tnode_b(int mode, const TSellDev& M, const void* in, void* out, bool mc, int xk, hipStream_t s) {
-  return xk == X_F64 ? tnode_x<B, double>(mode, M, in, out, mc, s) : tnode_x<B, float>(mode, M, in, out, mc, s);
+  if (M.cw) return xk == X_F64 ? tnode_x<B, double, true>(mode, M, in, out, mc, s) : tnode_x<B, float, true>(mode, M, in, out, mc, s);
+  return xk == X_F64 ? tnode_x<B, double, false>(mode, M, in, out, mc, s) : tnode_x<B, float, false>(mode, M, in, out, mc, s);
 }
 
 // node form: the row and column masks are the ones built into the layout (the levels' own

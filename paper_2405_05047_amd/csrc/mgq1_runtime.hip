@@ -934,8 +934,8 @@ int upload_tsell(DevOwner* h, const TSellHost& T, TSellDev& D, hipStream_t s) {
 // Node form of a single-right-hand-side transfer C (rows x cols nodes, block size B): slices
 // of 64 nodes, one packed 32-bit entry per slot and lane.  Applies when every weight is a
 // multiple of 1/128 up to 255/128 (the weights of nested box meshes, with their hanging-node
-// products) and every slot's columns span less than 2^16; *applied tells whether it did (else
-// the caller stores the per-DoF form).  The span counts the lanes of non-empty rows only: an
+// products); where a slot's columns span 2^16 and more the level keeps 32-bit columns beside
+// the codes (wide).  *applied tells whether it did (else the caller stores the per-DoF form).  The span counts the lanes of non-empty rows only: an
 // empty row (a Dirichlet node's row of P~) and a lane past the last row add 0 * in[j] to +0
 // whatever j, so they read the slot's base column.  Padding slots of a row keep its last
 // column and weight 0, as in the per-DoF form, so every sum is the same bit for bit.
@@ -953,6 +953,7 @@ int upload_tnode(DevOwner* h, const CsrHost& C, int B, const std::vector<uint8_t
   const TSellHost T = build_tsell(C, 1, 1);            // 64 node rows per slice
   const int64_t slots = int64_t(T.col.size()) / T.R;
   std::vector<int32_t> base(size_t(std::max<int64_t>(slots, 1)), 0);
+  bool wide = false;
   for (int64_t k = 0; k < slots; ++k) {
     int32_t lo = INT32_MAX, hi = INT32_MIN;
     for (int r = 0; r < T.R; ++r) {
@@ -962,32 +963,44 @@ int upload_tnode(DevOwner* h, const CsrHost& C, int B, const std::vector<uint8_t
       hi = std::max(hi, T.col[e]);
     }
     if (lo > hi) lo = hi = 0;
-    if (int64_t(hi) - lo >= 65536) return MG_OK;
+    wide = wide || int64_t(hi) - lo >= 65536;
     base[size_t(k)] = lo;
   }
-  std::vector<uint32_t> ent(T.col.size(), 0u);
+  std::vector<uint32_t> ent(wide ? 0 : T.col.size(), 0u);
+  std::vector<int32_t> col(wide ? T.col.size() : 0, 0);
+  std::vector<uint16_t> cw(wide ? T.col.size() : 0, 0);
   for (int64_t k = 0; k < slots; ++k)
     for (int r = 0; r < T.R; ++r) {
       const size_t e = size_t(k * T.R + r);
       const int32_t j = T.empty[e] ? base[size_t(k)] : T.col[e];
-      uint32_t v = uint32_t(j - base[size_t(k)]) | (uint32_t(T.w[e] * 128.0) << 16);
+      uint32_t v = uint32_t(T.w[e] * 128.0);
       for (int c = 0; c < B; ++c)
-        if (col_mask[size_t(j) * B + c]) v |= 1u << (24 + c);
-      ent[e] = v;
+        if (col_mask[size_t(j) * B + c]) v |= 1u << (8 + c);
+      if (wide) {
+        col[e] = j;
+        cw[e] = uint16_t(v);
+      } else {
+        ent[e] = uint32_t(j - base[size_t(k)]) | v << 16;
+      }
     }
   std::vector<uint8_t> rm(size_t(C.nrows), 0);
   for (int64_t i = 0; i < C.nrows; ++i)
     for (int c = 0; c < B; ++c)
       if (row_mask[size_t(i) * B + c]) rm[size_t(i)] |= uint8_t(1u << c);
   int rc;
-  int32_t *sp, *cb;
-  uint32_t* en;
+  int32_t *sp, *cb = nullptr, *cl = nullptr;
+  uint32_t* en = nullptr;
+  uint16_t* cd = nullptr;
   uint8_t* rmd;
-  if ((rc = upload(h, &sp, T.sptr, s)) || (rc = upload(h, &cb, base, s)) || (rc = upload(h, &en, ent, s)) ||
-      (rc = upload(h, &rmd, rm, s)))
+  if ((rc = upload(h, &sp, T.sptr, s)) || (rc = upload(h, &rmd, rm, s))) return rc;
+  if (wide ? (rc = upload(h, &cl, col, s)) || (rc = upload(h, &cd, cw, s))
+           : (rc = upload(h, &cb, base, s)) || (rc = upload(h, &en, ent, s)))
     return rc;
   MG_HIP(hipStreamSynchronize(s));
   D = TSellDev();
+  D.slots = slots;
+  D.col = cl;
+  D.cw = cd;
   D.nrows = T.nrows;
   D.ncols = T.ncols;
   D.R = T.R;
@@ -3187,8 +3200,8 @@ int mg_level_transfer_format(const mg_handle* h, int32_t level, int32_t* p_col_b
   if (!h || level < 1 || level > h->L) return fail(MG_EINVAL, "bad handle or level (transfers exist on levels >= 1)");
   const TSellDev& P = h->lv[level].Ps;
   const TSellDev& R = h->lv[level].Rs;
-  if (p_col_bytes) *p_col_bytes = P.node ? 2 : 4;
-  if (r_col_bytes) *r_col_bytes = R.node ? 2 : 4;
+  if (p_col_bytes) *p_col_bytes = P.node && !P.cw ? 2 : 4;
+  if (r_col_bytes) *r_col_bytes = R.node && !R.cw ? 2 : 4;
   if (weight_bytes) *weight_bytes = P.node ? 1 : P.f32 ? 4 : 8;
   return MG_OK;
 }

@@ -31,6 +31,137 @@ __global__ __launch_bounds__(kThreads) void k_sweep(SellDev A, const X* __restri
   sweep_slice<B, 1, K, X, T, KB, C16>(A, S, b, x, xo, omega, s, beta, pmode);
 }
 
+// ------------------------------------------------------------------ relay form
+// One slice per workgroup: its four waves take a quarter of the slots each, read them all at once
+// (one chain of dependent reads instead of one per batch of slots), and pass the row sums on
+// in slot order through LDS, so the multiply-adds run in the order of the other kernels and
+// give the same bits.  For levels whose slices do not fill the chip and whose rows are long:
+// a 27-block row is 4 to 7 batches of two dependent reads each in one wave, and the kernel
+// lasts as long as that chain.
+constexpr int kRelayBatch = 8;        // slots per wave and round: 32 slots a round
+
+// this wave's slots k .. k + cnt - 1 (cnt <= kRelayBatch, wave-uniform)
+template <int B, int K, class XI, bool C16>
+__device__ __forceinline__ void relay_load(const SellDev& A, int k, int cnt, int r, int rl, const XI* __restrict__ x,
+                                           typename Val<K>::raw (&av)[kRelayBatch][B], XI (&xv)[kRelayBatch][B]) {
+  constexpr int R = kWave / B;
+  unsigned js[kRelayBatch];
+#pragma unroll
+  for (int q = 0; q < kRelayBatch; ++q) {
+    const int kk = k + (q < cnt ? q : cnt - 1);
+    js[q] = slot_col<C16, false>(A, kk, int64_t(kk) * R + r);
+#pragma unroll
+    for (int cc = 0; cc < B; ++cc) av[q][cc] = Val<K>::template load<false>(A.val, (int64_t(kk) * B + cc) * kWave + rl);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  // every lane reads all B components of its neighbours (a level this small has read slots to
+  // spare; exchanging them between the node's lanes would add a trip through LDS)
+#pragma unroll
+  for (int q = 0; q < kRelayBatch; ++q)
+#pragma unroll
+    for (int cc = 0; cc < B; ++cc) xv[q][cc] = x[uint64_t(js[q]) * B + cc];
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// the row sums of slice s, valid in the last wave
+template <int B, int K, class XI, class T, bool C16>
+__device__ __forceinline__ T relay_dot(const SellDev& A, const SliceLane& s, const XI* __restrict__ x) {
+  __shared__ T sums[kWave];
+  constexpr int R = kWave / B;
+  const int lane = s.lane, w = int(threadIdx.x) / kWave;
+  // lanes past the last row of the slice read a row that exists
+  const int r = lane / B < R ? lane / B : R - 1;
+  const int rl = lane < R * B ? lane : R * B - 1;
+  const int su = __builtin_amdgcn_readfirstlane(s.slice);
+  int k0, k1;
+  slot_range(A, su, k0, k1);
+  const bool wide = C16 && is_wide(A, su);
+  T acc = T(0);
+  for (int k = k0; k < k1; k += kSliceWaves * kRelayBatch) {
+    const int left = k1 - k < kSliceWaves * kRelayBatch ? k1 - k : kSliceWaves * kRelayBatch;
+    const int per = (left + kSliceWaves - 1) / kSliceWaves;
+    const int first = w * per < left ? w * per : left;
+    const int cnt = left - first < per ? left - first : per;
+    typename Val<K>::raw av[kRelayBatch][B];
+    XI xv[kRelayBatch][B];
+    if (cnt > 0) {
+      if (wide) relay_load<B, K, XI, false>(A, k + first, cnt, r, rl, x, av, xv);
+      else relay_load<B, K, XI, C16>(A, k + first, cnt, r, rl, x, av, xv);
+    }
+    for (int turn = 0; turn < kSliceWaves; ++turn) {
+      if (turn == w) {
+        if (k > k0 || w > 0) acc = sums[lane];
+#pragma unroll
+        for (int q = 0; q < kRelayBatch; ++q)
+          if (q < cnt) {
+#pragma unroll
+            for (int cc = 0; cc < B; ++cc) acc += T(Val<K>::dec(av[q][cc])) * T(xv[q][cc]);
+          }
+        sums[lane] = acc;
+      }
+      __syncthreads();
+    }
+  }
+  if (K == VK_F16 || K == VK_BF16) acc *= T(ldexpf(1.0f, A.rexp[int64_t(su) * kWave + rl]));
+  return acc;
+}
+
+// y = A x (MODE 0), b - A x (MODE 1), M (b - A x) (MODE 2)
+template <int B, int K, class XI, class XO, class T, int MODE, bool C16>
+__global__ __launch_bounds__(kThreads) void k_spmv_relay(SellDev A, const XO* __restrict__ b, const XI* __restrict__ x,
+                                                         XO* __restrict__ y, const uint8_t* __restrict__ mask) {
+  const int bid = xcd_remap(blockIdx.x, gridDim.x);
+  const SliceLane s = slice_lane<B, 1>(A, bid, int(threadIdx.x) % kWave);
+  const bool last = int(threadIdx.x) / kWave == kSliceWaves - 1 && s.valid;
+  XO bv = XO(0);
+  uint8_t mk = 0;
+  if (MODE != 0 && last) {
+    bv = b[s.dof];
+    if (MODE == 2) mk = mask[s.dof];
+  }
+  const T acc = relay_dot<B, K, XI, T, C16>(A, s, x);
+  if (!last) return;
+  T out = MODE == 0 ? acc : T(bv) - acc;
+  if (MODE == 2 && mk) out = T(0);
+  y[s.dof] = XO(out);
+}
+
+// x_out = x + omega S (b - A x) and its three-term form, as sweep_slice
+template <int B, int K, class X, class T, bool C16>
+__global__ __launch_bounds__(kThreads) void k_sweep_relay(SellDev A, const X* __restrict__ S, const X* __restrict__ b,
+                                                          const X* __restrict__ x, X* __restrict__ xo, T omega,
+                                                          T beta, int pmode) {
+  const int bid = xcd_remap(blockIdx.x, gridDim.x);
+  const SliceLane s = slice_lane<B, 1>(A, bid, int(threadIdx.x) % kWave);
+  const bool mine = int(threadIdx.x) / kWave == kSliceWaves - 1;
+  const bool last = mine && s.valid;
+  X bv = X(0), xv = X(0), pv = X(0), sv[B];
+#pragma unroll
+  for (int cc = 0; cc < B; ++cc) sv[cc] = X(0);
+  if (last) {
+    bv = b[s.dof];
+    xv = x[s.dof];
+    pv = (pmode == 1 ? static_cast<const X*>(xo) : x)[s.dof];
+#pragma unroll
+    for (int cc = 0; cc < B; ++cc) sv[cc] = S[(int64_t(s.slice) * B + cc) * kWave + s.lane];
+  }
+  const T acc = relay_dot<B, K, X, T, C16>(A, s, x);
+  if (!mine) return;                       // the whole wave stays together for the exchange
+  const T res = last ? T(bv) - acc : T(0);
+  const int base = (s.lane / B) * B;
+  T upd = T(0);
+#pragma unroll
+  for (int cc = 0; cc < B; ++cc) {
+    const T rc = __shfl(res, (base + cc) & (kWave - 1), kWave);
+    if (last) upd += T(sv[cc]) * rc;
+  }
+  if (last) {
+    T nx = T(xv) + omega * upd;
+    if (pmode != 0) nx = nx + beta * (T(xv) - (pmode == 1 ? T(pv) : T(0)));
+    xo[s.dof] = X(nx);
+  }
+}
+
 // two smoothing sweeps from x = 0 in one pass, one component per node:
 // x1 = omega S b (formed per column on the fly), x2 = x1 + omega S (b - A x1)
 template <int K, class X, class T, int KB, bool C16>
@@ -70,6 +201,18 @@ __global__ __launch_bounds__(kThreads) void k_sweep0(SellDev A, const X* __restr
 }
 
 
+// The relay form where a level's slices (4 waves each then) do not fill the chip and its rows
+// take more than one batch.  Sweep, one wave per slice and relay (4,913 nodes is 234 to 308
+// slices): 3 components 729 nodes 6.0 and 3.9 us, 4,913 nodes 6.2 and 4.1 us, 14,620 nodes with
+// FP16 values (697 slices) 6.4 and 5.5 us; 4 components 4,913 nodes 6.6 and 5.7 us; one component
+// with 27-point rows 9,537 nodes 3.8 and 3.0 us, 70,785 nodes (1,107 slices) 5.7 and 5.7 us.  At
+// 1,712 slices (35,937 nodes, 3 components) it loses: 13.2 and 15.4 us.
+constexpr int kRelaySlices = 1024;
+template <int B>
+inline bool relay_level(const SellDev& A) {
+  return !A.nt && A.nslices <= kRelaySlices && A.slots >= int64_t(B == 1 ? 12 : 5) * A.nslices;
+}
+
 template <int B, int K, class XI, class XO, class T>
 hipError_t spmv_t(const SellDev& A, const void* b, const void* x, void* y, const uint8_t* mask, int mode,
                   double* partials, hipStream_t s) {
@@ -78,6 +221,20 @@ hipError_t spmv_t(const SellDev& A, const void* b, const void* x, void* y, const
   const XO* bb = static_cast<const XO*>(b);
   const XI* xx = static_cast<const XI*>(x);
   XO* yy = static_cast<XO*>(y);
+  if (!partials && relay_level<B>(A)) {
+#define MGQ1_RELAY4(MODE, C16) \
+  hipLaunchKernelGGL((k_spmv_relay<B, K, XI, XO, T, MODE, C16>), unsigned(A.nslices), kThreads, 0, s, A, bb, xx, yy, mask)
+#define MGQ1_RELAY(MODE)                  \
+  if (A.col16) MGQ1_RELAY4(MODE, true);   \
+  else MGQ1_RELAY4(MODE, false)
+    if (mode == 0) { MGQ1_RELAY(0); }
+    else if (mode == 1) { MGQ1_RELAY(1); }
+    else if (mode == 2) { MGQ1_RELAY(2); }
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+#undef MGQ1_RELAY
+#undef MGQ1_RELAY4
+  }
   // slot batch and column format are runtime properties of the operator
 #define MGQ1_SPMV4(MODE, NORM, KB, C16)                                                                     \
   hipLaunchKernelGGL((k_spmv<B, K, XI, XO, T, MODE, NORM, KB, C16>), g, kThreads, 0, s, A, bb, xx, yy, mask, partials)
@@ -131,10 +288,16 @@ hipError_t sweep_t(const SellDev& A, const void* S, const void* b, const void* x
   const X* bb = static_cast<const X*>(b);
   const X* xx = static_cast<const X*>(x);
   X* oo = static_cast<X*>(xo);
+  const bool relay = relay_level<B>(A);
+#define MGQ1_SWEEPR(KIND, C16) \
+  hipLaunchKernelGGL((k_sweep_relay<B, KIND, X, T, C16>), unsigned(A.nslices), kThreads, 0, s, A, SS, bb, xx, oo, T(omega), T(beta), pmode)
 #define MGQ1_SWEEP4(KIND, KB, C16) \
   hipLaunchKernelGGL((k_sweep<B, KIND, X, T, KB, C16>), g, kThreads, 0, s, A, SS, bb, xx, oo, T(omega), T(beta), pmode)
 #define MGQ1_SWEEP(KIND)                                                   \
-  if (A.col16) {                                                           \
+  if (relay) {                                                             \
+    if (A.col16) MGQ1_SWEEPR(KIND, true);                                  \
+    else MGQ1_SWEEPR(KIND, false);                                         \
+  } else if (A.col16) {                                                           \
     if (A.kb == kb_alt<B>()) MGQ1_SWEEP4(KIND, kb_alt<B>(), true);         \
     else MGQ1_SWEEP4(KIND, kb_default<B>(), true);                         \
   } else {                                                                 \
@@ -155,6 +318,7 @@ hipError_t sweep_t(const SellDev& A, const void* S, const void* b, const void* x
   }
 #undef MGQ1_SWEEP
 #undef MGQ1_SWEEP4
+#undef MGQ1_SWEEPR
   return hipGetLastError();
 }
 

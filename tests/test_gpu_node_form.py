@@ -129,3 +129,41 @@ def test_node_form_rule():
                      (W.c4_oseen(4).with_(coarse_level=2), [False, False, False])):
         h = mg.Hierarchy(gen.build(wl).levels, mg.config_from(wl))
         assert [h.dictionary_blocks(l) > 0 for l in range(h.n_levels)] == want
+
+
+@pytest.mark.parametrize("wl", [W.c2_td().with_(coarse_level=3), W.c3_adaptive("face", 6)], ids=["td1m", "face6"])
+def test_wide_transfers_bitwise_equal(wl, monkeypatch):
+    """Transfers whose slots' columns span 2^16 and more (adaptive meshes of 1.0M and 0.7M
+    nodes): the node form with 32-bit columns gives the bits of the per-DoF form, in FP64 and
+    FP32."""
+    from paper_2405_05047_amd import gen, mg
+    levels = gen.build(wl).levels
+    for prec, real in (("fp64", torch.float64), ("fp32", torch.float32)):
+        got, wide = [], False
+        for plain in ("1", "0"):
+            monkeypatch.setenv("MGQ1_PLAIN_TRANSFERS", plain)
+            h = mg.Hierarchy(levels, mg.config_from(wl, precision=prec))
+            if plain == "0":
+                wide = any(h.transfer_format(l)[1:] == (4, 1) for l in range(1, h.n_levels))
+            out = []
+            for l in range(1, h.n_levels):
+                d = torch.zeros(h.ndof(l - 1), dtype=real, device="cuda")
+                h.restrict(l, _vec(700 + l, h.ndof(l), real), d)
+                x = _vec(740 + l, h.ndof(l), real)
+                h.prolong(l, _vec(780 + l, h.ndof(l - 1), real), x)
+                out += [d, x]
+            got.append(out)
+        assert wide and all(torch.equal(a, b) for a, b in zip(*got))
+
+
+@pytest.mark.parametrize("name,rounds", [("elast", 1), ("elast", 3), ("oseen", 1), ("oseen", 3), ("poisson3", 3)])
+@pytest.mark.parametrize("prec", ["fp64", "fp16"])
+def test_relay_bitwise_equal(name, rounds, prec, monkeypatch):
+    """The relay kernels of small levels (one slice per workgroup, MGQ1_NODE_FORM=0) against the
+    node form's one wave per slice: rows of 8 to 27 blocks, fewer rows than a slice, and the
+    one-component form."""
+    from paper_2405_05047_amd import gen
+    wl = {"elast": W.c3_elasticity(rounds).with_(coarse=(3, 2, 2)), "oseen": W.c4_oseen(rounds).with_(coarse=(2, 3, 2)),
+          "poisson3": W.c3_elasticity(rounds).with_(pde=W.PDE_POISSON, block=1, dir_comps=1, rhs=W.RHS_NONE,
+                                                    omega=0.8)}[name]
+    _compare(gen.build(wl).levels, wl, prec, W.SMOOTH_JACOBI, monkeypatch)
