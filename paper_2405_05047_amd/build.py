@@ -21,7 +21,7 @@ LIB_MG = os.path.join(HERE, "libmgq1.so")
 
 # (source, object, extra flags); the slice kernels are one object per block size
 HIP_UNITS = [("mgq1_slices.hip", f"mgq1_slices_b{b}", [f"-DMGQ1_B={b}"]) for b in (4, 3, 2, 1)] + \
-            [(f"mgq1_{u}.hip", f"mgq1_{u}", []) for u in ("kernels", "node", "batch", "runtime", "gs", "time", "cheb",
+            [(f"mgq1_{u}.hip", f"mgq1_{u}", []) for u in ("kernels", "node", "flow", "batch", "runtime", "gs", "time", "cheb",
                                                           "ns", "asm")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

@@ -18,6 +18,7 @@ constexpr int kRedThreads = 1024;
 constexpr int kMaxRedBlocks = 2048;   // grid (= partial count) of the vector reductions
 
 struct NodeDev;
+struct FlowDev;
 
 // Sliced ELL of a block matrix: one slice = 64 lanes = R = 64/B nodes x B components;
 // lane = r*B + c handles scalar row (node slice*R + r, component c).  For block slot k of
@@ -42,6 +43,7 @@ struct SellDev {
   const int32_t* perm = nullptr;    // node at row position slice*R + r (NULL: the position
                                     // itself); rows sorted by length inside windows of slices
   int nt = 1;                       // 1: values and indices read with non-temporal loads
+  const FlowDev* flow = nullptr;    // host: ... or in the flow form
   const NodeDev* node = nullptr;    // host: the level is stored in the node form instead (the
                                     // sliced arrays above are then absent)
 };
@@ -83,6 +85,27 @@ struct NodeDev {
   const uint16_t* sidx = nullptr;   // smoother block of each row position in stab (NULL: sfull)
   const void* stab = nullptr;       // the distinct smoother blocks, cycle type
   const void* sfull = nullptr;      // smoother block of every node (B = 1 always; else with no sidx)
+};
+
+// sliced-ELL levels of up to this many slices run one slice per workgroup (mgq1_slices.hip)
+constexpr int kRelaySlices = 1024;
+
+// Flow form of a four-component operator (mgq1_flow.hip): slices of kFlowNodes nodes, slots
+// sptr[s] .. of a slice, value v (0: pp, 1-3: pu pv pw, 4-6: up vp wp, 7: the velocity's diagonal)
+// of slot k and row r at val[(k * 8 + v) * kFlowNodes + r], column at col[k * kFlowNodes + r] or
+// base[k] + col16[...].  Padding slots hold zeros and the row's own node.
+constexpr int kFlowNodes = 32;
+struct FlowDev {
+  int32_t n = 0, nslices = 0;
+  int tk = X_F64;                   // type of the values
+  int nt = 1;                       // as SellDev::nt
+  const int32_t* sptr = nullptr;
+  const int32_t* col = nullptr;     // (NULL with col16)
+  const uint16_t* col16 = nullptr;
+  const int32_t* base = nullptr;
+  const int32_t* perm = nullptr;    // node at each row position (NULL: the position itself)
+  const void* val = nullptr;
+  const void* S = nullptr;          // smoother rows in the lanes' layout, cycle type
 };
 
 // the two slot-batch sizes the slice kernels are built for (default, alternative)
@@ -159,6 +182,13 @@ hipError_t launch_node_sweep(const NodeDev& A, const void* b, const void* x, voi
                              hipStream_t s, double beta, int pmode);
 hipError_t launch_node_sweep0(const NodeDev& A, const void* b, void* xo, double omega, int xk, hipStream_t s);
 hipError_t launch_node_sweep2z(const NodeDev& A, const void* b, void* xo, double omega, int xk, hipStream_t s);
+// operators in the flow form; S from one 4 x 4 block per row position
+hipError_t launch_flow_spmv(const FlowDev& A, const void* b, const void* x, void* y, const uint8_t* mask, int xk,
+                            int yk, int mode, double* partials, hipStream_t s);
+hipError_t launch_flow_sweep(const FlowDev& A, const void* b, const void* x, void* xo, double omega, int xk,
+                             hipStream_t s, double beta, int pmode);
+hipError_t launch_flow_sweep0(const FlowDev& A, const void* b, void* xo, double omega, int xk, hipStream_t s);
+hipError_t launch_flow_smoother(int n, int nslices, const void* blocks, void* S, int sk, hipStream_t s);
 // inverses of nb FP64 B x B blocks in double or float (sk); *flag = 1 if one is singular
 hipError_t launch_invert_blocks(int nb, int B, const double* blocks, void* out, int sk, int* flag, hipStream_t s);
 // S[node] = stab[sidx[pos]], node = perm[pos] (perm NULL: pos)

@@ -491,10 +491,11 @@ void slot_batch_choices(int B, int* kb_def, int* kb_other) {
     default: *kb_def = kb_default<4>(); *kb_other = kb_alt<4>(); break;
   }
 }
-int spmv_grid(const SellDev& A) { return int(slice_grid(A.node ? A.node->nslices : A.nslices)); }
+int spmv_grid(const SellDev& A) { return int(slice_grid(A.flow ? A.flow->nslices : A.node ? A.node->nslices : A.nslices)); }
 
 hipError_t launch_spmv(const SellDev& A, const void* b, const void* x, void* y, const uint8_t* mask, int xk, int yk,
                        int mode, double* partials, hipStream_t s) {
+  if (A.flow) return launch_flow_spmv(*A.flow, b, x, y, mask, xk, yk, mode, partials, s);
   if (A.node) return launch_node_spmv(*A.node, b, x, y, mask, xk, yk, mode, partials, s);
   switch (A.B) {
     case 1: return spmv_block<1>(A, b, x, y, mask, xk, yk, mode, partials, s);
@@ -507,6 +508,7 @@ hipError_t launch_spmv(const SellDev& A, const void* b, const void* x, void* y, 
 
 hipError_t launch_sweep(const SellDev& A, const void* S, const void* b, const void* x, void* xo, double omega,
                         int xk, hipStream_t s, double beta, int pmode) {
+  if (A.flow) return launch_flow_sweep(*A.flow, b, x, xo, omega, xk, s, beta, pmode);
   if (A.node) return launch_node_sweep(*A.node, b, x, xo, omega, xk, s, beta, pmode);
   switch (A.B) {
     case 1: return sweep_block<1>(A, S, b, x, xo, omega, beta, pmode, xk, s);
@@ -526,6 +528,7 @@ hipError_t launch_sweep2z(const SellDev& A, const void* S, const void* b, void* 
 
 hipError_t launch_sweep0(const SellDev& A, const void* S, const void* b, void* xo, double omega, int xk,
                          hipStream_t s) {
+  if (A.flow) return launch_flow_sweep0(*A.flow, b, xo, omega, xk, s);
   if (A.node) return launch_node_sweep0(*A.node, b, xo, omega, xk, s);
   switch (A.B) {
     case 1: return sweep0_block<1>(A, S, b, xo, omega, xk, s);

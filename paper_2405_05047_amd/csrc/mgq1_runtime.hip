@@ -518,6 +518,7 @@ struct LevelDev {
   // node form (single-problem handles): host description, FP64 and cycle operators
   std::unique_ptr<NodeHost> nh;
   std::unique_ptr<NodeDev> n64, nc;
+  std::unique_ptr<FlowDev> f64, fc;   // flow form
   std::vector<int8_t> hexp;         // row exponents (FP16 / BF16 values)
   std::vector<uint16_t> hcode;      // 16-bit codes of the distinct blocks (FP16 / BF16 values)
 };
@@ -869,6 +870,173 @@ int setup_node(DevOwner* h, const HostLevel& L, int vkind, int xk, bool must, in
   D.Ac.node = D.nc.get();
   D.hperm = H->perm;
   D.nh = std::move(H);
+  *applied = true;
+  return MG_OK;
+}
+
+// Every block of a four-component operator has the flow shape (mgq1_flow.hip): zeros and one
+// value three times, bit for bit.
+bool flow_shape(const HostLevel& L) {
+  if (L.B != 4) return false;
+  const int64_t nchunk = 64, per = (L.nnzb + nchunk - 1) / nchunk;
+  std::vector<int> bad(size_t(nchunk), 0);
+  parallel_for(nchunk, 1, [&](int64_t c0, int64_t c1) {
+    for (int64_t c = c0; c < c1; ++c)
+      for (int64_t k = c * per; k < std::min(L.nnzb, (c + 1) * per) && !bad[size_t(c)]; ++k) {
+        const double* a = &L.val[size_t(k) * 16];
+        bool ok = std::memcmp(a + 5, a + 10, 8) == 0 && std::memcmp(a + 5, a + 15, 8) == 0;
+        const double zero = 0.0;
+        for (int z : {6, 7, 9, 11, 13, 14}) ok = ok && std::memcmp(a + z, &zero, 8) == 0;
+        if (!ok)
+          bad[size_t(c)] = 1;
+      }
+  });
+  for (int b : bad)
+    if (b) return false;
+  return true;
+}
+
+constexpr int kFlowEntry[8] = {0, 1, 2, 3, 4, 8, 12, 5};   // block entry of value v
+
+// The flow form is for levels that the node form's size rule names and its distinct rows refuse,
+// above the relay's limit: at 9,261 nodes (579 slices) a sweep is 8.4 us in the relay and 9.2 us
+// in the flow form in FP64, 4.5 and 5.2 us in FP32; at 35,937 nodes 22.8 and 18.0, 12.2 and 7.8.
+// MGQ1_FLOW_FORM=0 / =1: off / on levels of any size, before the node form (tests; the bits
+// are the same); -1: not set.
+int flow_switch() {
+  const char* e = std::getenv("MGQ1_FLOW_FORM");
+  return e ? std::atoi(e) != 0 : -1;
+}
+
+// The flow form of level L: D.A64 and D.Ac (FP64 and FP32 values) with their smoother rows.
+// *applied: the operator has the shape.
+int setup_flow(DevOwner* h, const HostLevel& L, int vkind, int xk, int* flag, hipStream_t s, LevelDev& D,
+               bool* applied) {
+  *applied = false;
+  if ((vkind != VK_F64 && vkind != VK_F32) || !flow_shape(L)) return MG_OK;
+  const int R = kFlowNodes;
+  const int32_t n = L.n, ns = (n + R - 1) / R;
+  const std::vector<int32_t> perm = sorted_positions(L, R);
+  auto node_at = [&](int64_t pos) -> int64_t { return perm.empty() ? pos : perm[size_t(pos)]; };
+  std::vector<int32_t> sptr(size_t(ns) + 1, 0);
+  for (int32_t sl = 0; sl < ns; ++sl) {
+    int32_t w = 0;
+    for (int64_t pos = int64_t(sl) * R; pos < std::min<int64_t>(n, int64_t(sl + 1) * R); ++pos)
+      w = std::max(w, L.rowptr[node_at(pos) + 1] - L.rowptr[node_at(pos)]);
+    if (int64_t(sptr[size_t(sl)]) + w >= (int64_t(1) << 31)) return MG_OK;
+    sptr[size_t(sl) + 1] = sptr[size_t(sl)] + w;
+  }
+  const int64_t slots = sptr[size_t(ns)];
+  std::vector<double> val(size_t(slots) * 8 * R);
+  std::vector<int32_t> col(size_t(slots) * R), base(size_t(slots), 0);
+  std::vector<uint16_t> c16(size_t(slots) * R, 0);
+  std::vector<uint8_t> wide(size_t(ns), 0);
+  parallel_for(ns, 256, [&](int64_t s0, int64_t s1) {
+    for (int64_t sl = s0; sl < s1; ++sl)
+      for (int64_t k = sptr[size_t(sl)]; k < sptr[size_t(sl) + 1]; ++k) {
+        int32_t lo = INT32_MAX, hi = INT32_MIN;
+        for (int r = 0; r < R; ++r) {
+          const int64_t pos = std::min<int64_t>(sl * R + r, n - 1), i = node_at(pos);
+          const int64_t q = k - sptr[size_t(sl)], len = L.rowptr[i + 1] - L.rowptr[i];
+          const bool in = q < len && sl * R + r < n;
+          const int32_t j = q < len ? L.col[size_t(L.rowptr[i] + q)] : int32_t(i);
+          col[size_t(k) * R + r] = j;
+          lo = std::min(lo, j);
+          hi = std::max(hi, j);
+          for (int v = 0; v < 8; ++v)
+            val[(size_t(k) * 8 + v) * R + r] = in ? L.val[size_t(L.rowptr[i] + q) * 16 + kFlowEntry[v]] : 0.0;
+        }
+        base[size_t(k)] = lo;
+        if (int64_t(hi) - lo > 65535) {
+          wide[size_t(sl)] = 1;
+        } else {
+          for (int r = 0; r < R; ++r) c16[size_t(k) * R + r] = uint16_t(col[size_t(k) * R + r] - lo);
+        }
+      }
+  });
+  bool any_wide = false;
+  for (uint8_t w : wide) any_wide = any_wide || w;
+  FlowDev F;
+  F.n = n;
+  F.nslices = ns;
+  int rc;
+  int32_t *p32;
+  if ((rc = upload(h, &p32, sptr, s))) return rc;
+  F.sptr = p32;
+  if (!perm.empty()) {
+    if ((rc = upload(h, &p32, perm, s))) return rc;
+    F.perm = p32;
+  }
+  if (any_wide) {
+    if ((rc = upload(h, &p32, col, s))) return rc;
+    F.col = p32;
+  } else {
+    uint16_t* p16;
+    if ((rc = upload(h, &p16, c16, s))) return rc;
+    F.col16 = p16;
+    if ((rc = upload(h, &p32, base, s))) return rc;
+    F.base = p32;
+  }
+  const int64_t cb = int64_t(col.size()) * (any_wide ? 4 : 2);
+  D.f64 = std::make_unique<FlowDev>(F);
+  D.fc = std::make_unique<FlowDev>(F);
+  double* dv;
+  if ((rc = upload(h, &dv, val, s))) return rc;
+  MG_HIP(hipStreamSynchronize(s));
+  D.f64->val = dv;
+  D.f64->tk = X_F64;
+  D.f64->nt = stream_nt(int64_t(val.size()) * 8 + cb);
+  if (vkind == VK_F64) {
+    *D.fc = *D.f64;
+  } else {
+    std::vector<float> f(val.size());
+    parallel_for(int64_t(val.size()), int64_t(1) << 20, [&](int64_t a, int64_t b) {
+      for (int64_t i = a; i < b; ++i) f[size_t(i)] = float(val[size_t(i)]);
+    });
+    float* fv;
+    if ((rc = upload(h, &fv, f, s))) return rc;
+    MG_HIP(hipStreamSynchronize(s));
+    D.fc->val = fv;
+    D.fc->tk = X_F32;
+    D.fc->nt = stream_nt(int64_t(f.size()) * 4 + cb);
+  }
+  // smoother: the caller's blocks, or the inverses of the diagonal blocks, by row position, then
+  // in the lanes' layout
+  DevOwner tmp;
+  std::vector<double> blk(size_t(n) * 16);
+  parallel_for(n, 1 << 12, [&](int64_t a, int64_t b) {
+    for (int64_t pos = a; pos < b; ++pos) {
+      const int64_t i = node_at(pos);
+      const double* src = nullptr;
+      if (!L.sblk.empty()) src = &L.sblk[size_t(i) * 16];
+      for (int64_t k = L.rowptr[i]; !src && k < L.rowptr[i + 1]; ++k)
+        if (L.col[size_t(k)] == i) src = &L.val[size_t(k) * 16];
+      std::memcpy(&blk[size_t(pos) * 16], src, 16 * sizeof(double));
+    }
+  });
+  double* db;
+  char *inv, *S;
+  if ((rc = upload(&tmp, &db, blk, s))) return rc;
+  if ((rc = dalloc(h, &S, size_t(ns) * 8 * kWave * xsize(xk)))) return rc;
+  if ((rc = dalloc(&tmp, &inv, size_t(n) * 16 * xsize(xk)))) return rc;
+  if (L.sblk.empty()) MG_HIP(launch_invert_blocks(n, 4, db, inv, xk, flag, s));
+  else MG_HIP(launch_convert(int64_t(n) * 16, db, X_F64, inv, xk, s));
+  MG_HIP(launch_flow_smoother(n, ns, inv, S, xk, s));
+  MG_HIP(hipStreamSynchronize(s));
+  D.fc->S = S;
+  D.f64->S = xk == X_F64 ? S : nullptr;
+  for (SellDev* A : {&D.A64, &D.Ac}) {
+    A->n = n;
+    A->B = 4;
+    A->R = kWave / 4;
+    A->nslices = (n + A->R - 1) / A->R;
+  }
+  D.A64.kind = VK_F64;
+  D.Ac.kind = vkind;
+  D.A64.flow = D.f64.get();
+  D.Ac.flow = D.fc.get();
+  D.hsptr = sptr;
+  D.hperm = perm;
   *applied = true;
   return MG_OK;
 }
@@ -1450,9 +1618,16 @@ int setup_level(DevOwner* h, const HostLevel& L, bool has_p, int NR, int vkind, 
   PhaseTimer pt;
   bool node = false;
   bool must = dict;
-  if (single && NR == 1 && (dict || want_node(L, tail_dofs, &must))) {
+  const int ff = flow_switch();
+  if (single && NR == 1 && ff != 1 && (dict || want_node(L, tail_dofs, &must))) {
     if ((rc = setup_node(h, L, vkind, xk, must, flag, s, D, &node))) return rc;
     pt.mark("  node form");
+  }
+  if (single && NR == 1 && !node && !dict && L.B == 4 && ff != 0 &&
+      (ff == 1 ? int64_t(L.n) * 4 > tail_dofs
+               : L.n > kRelaySlices * (kWave / 4) && want_node(L, tail_dofs, &must))) {
+    if ((rc = setup_flow(h, L, vkind, xk, flag, s, D, &node))) return rc;
+    pt.mark("  flow form");
   }
   if (!node) {
   HostSell S = build_sell(L, NR);
@@ -1588,7 +1763,7 @@ int tune_levels(mg_handle* h, hipStream_t s) {
   const double omega = h->cfg.omega;
   for (size_t l = 0; l < h->lv.size() && rc == MG_OK; ++l) {
     LevelDev& D = h->lv[l];
-    if (D.Ac.node) continue;             // one batch size
+    if (D.Ac.node || D.Ac.flow) continue;   // one batch size
     int kb[2];
     slot_batch_choices(D.B, &kb[0], &kb[1]);
     if ((rc = launch_fill(D.N, D.x, h->xk, 1.0, s) == hipSuccess ? MG_OK : MG_EDEVICE)) break;
@@ -1610,7 +1785,7 @@ int tune_levels(mg_handle* h, hipStream_t s) {
     D.us_def = 100.0 * best[0];          // ms per 10 launches -> us per launch
     D.us_alt = 100.0 * best[1];
   }
-  if (rc == MG_OK && h->xk != X_F64 && !h->lv[h->L].A64.node) {
+  if (rc == MG_OK && h->xk != X_F64 && !h->lv[h->L].A64.node && !h->lv[h->L].A64.flow) {
     // FP64 outer defect of a mixed-precision handle: r = b - A x with norm partials
     LevelDev& T = h->lv[h->L];
     int kb[2];
@@ -1670,7 +1845,7 @@ int setup_dense(mg_handle* h, const std::vector<HostLevel>& H, hipStream_t s) {
   for (int l = 0; l <= top; ++l) {
     // the workgroup's cycle reads sliced ELL: a level in the node form gets a copy in it
     LevelDev* D = &h->lv[l];
-    if (D->Ac.node) {
+    if (D->Ac.node || D->Ac.flow) {
       D = &copy[size_t(l)];
       if ((rc = setup_level(&tmp, H[size_t(l)], l > 0, 1, VK_F64, X_F64, false, h->dflag, s, *D))) return rc;
     }
@@ -3147,6 +3322,27 @@ int mg_level_export(const mg_handle* h, int32_t level, void* values, int8_t* row
     return MG_OK;
   }
   const int64_t slots = L.hsptr.back();
+  if (A.flow) {
+    // value of each block entry (-1: zero)
+    int of[16];
+    for (int z = 0; z < 16; ++z) of[z] = -1;
+    for (int v = 0; v < 8; ++v) of[kFlowEntry[v]] = v;
+    of[10] = of[15] = 7;
+    std::vector<char> fv(size_t(slots) * 8 * kFlowNodes * vb);
+    MG_HIP(hipMemcpy(fv.data(), A.flow->val, fv.size(), hipMemcpyDeviceToHost));
+    char* out = static_cast<char*>(values);
+    for (int64_t pos = 0; pos < L.n; ++pos) {
+      const int64_t node = L.hperm.empty() ? pos : L.hperm[size_t(pos)];
+      const int64_t k0 = L.hsptr[size_t(pos / kFlowNodes)], r = pos % kFlowNodes;
+      for (int64_t k = 0; k < L.hrow[size_t(node) + 1] - L.hrow[size_t(node)]; ++k)
+        for (int z = 0; z < 16; ++z) {
+          char* dst = out + ((size_t(L.hrow[size_t(node)]) + k) * 16 + z) * vb;
+          if (of[z] < 0) std::memset(dst, 0, size_t(vb));
+          else std::memcpy(dst, fv.data() + ((size_t(k0 + k) * 8 + of[z]) * kFlowNodes + r) * vb, size_t(vb));
+        }
+    }
+    return MG_OK;
+  }
   std::vector<char> dv(size_t(slots) * B * W * vb);
   MG_HIP(hipMemcpy(dv.data(), A.val, dv.size(), hipMemcpyDeviceToHost));
   std::vector<int8_t> de;
@@ -3189,7 +3385,7 @@ int mg_level_tuning(const mg_handle* h, int32_t level, int32_t* slot_batch, int3
   int kd, ko;
   slot_batch_choices(L.B, &kd, &ko);
   if (slot_batch) *slot_batch = L.Ac.kb ? L.Ac.kb : kd;
-  if (col_bytes) *col_bytes = L.A64.col16 || L.A64.node ? 2 : 4;
+  if (col_bytes) *col_bytes = L.A64.col16 || L.A64.node || (L.A64.flow && L.A64.flow->col16) ? 2 : 4;
   if (us_default) *us_default = L.us_def;
   if (us_other) *us_other = L.us_alt;
   return MG_OK;

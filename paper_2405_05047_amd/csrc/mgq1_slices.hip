@@ -206,8 +206,7 @@ __global__ __launch_bounds__(kThreads) void k_sweep0(SellDev A, const X* __restr
 // slices): 3 components 729 nodes 6.0 and 3.9 us, 4,913 nodes 6.2 and 4.1 us, 14,620 nodes with
 // FP16 values (697 slices) 6.4 and 5.5 us; 4 components 4,913 nodes 6.6 and 5.7 us; one component
 // with 27-point rows 9,537 nodes 3.8 and 3.0 us, 70,785 nodes (1,107 slices) 5.7 and 5.7 us.  At
-// 1,712 slices (35,937 nodes, 3 components) it loses: 13.2 and 15.4 us.
-constexpr int kRelaySlices = 1024;
+// 1,712 slices (35,937 nodes, 3 components) it loses: 13.2 and 15.4 us; the limit is kRelaySlices.
 template <int B>
 inline bool relay_level(const SellDev& A) {
   return !A.nt && A.nslices <= kRelaySlices && A.slots >= int64_t(B == 1 ? 12 : 5) * A.nslices;
