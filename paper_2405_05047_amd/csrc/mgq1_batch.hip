@@ -5,6 +5,8 @@
 // block and right-hand side, re-summed in a fixed order by the consumer kernel.
 #include "mgq1_device.h"
 
+#include <climits>
+
 namespace mgq1 {
 
 // ======================================================================== batched form
@@ -33,25 +35,315 @@ __device__ __forceinline__ void block_entry(const BEntry* __restrict__ E, int n,
   __syncthreads();
 }
 
+// ---- work of a launch: blocks of kSliceWaves slices, those of inactive problems left out.
+// A launch of more than kBatchGrid blocks (and up to 64 entries, one per lane) starts
+// kBatchGrid workgroups that share the active problems' blocks, each XCD a contiguous range,
+// so that the gathered neighbours of a slice come from its own L2 and problems that have
+// converged cost nothing.  Smaller launches start one workgroup per block.
+struct BatchWork {
+  int start, total;                        // first block of the lane's entry; blocks of all entries
+  bool strided;
+};
+
+__device__ __forceinline__ BatchWork batch_work(const BEntry* __restrict__ E, int ne, int nb,
+                                                const int* __restrict__ active) {
+  BatchWork w;
+  w.strided = int(gridDim.x) < nb;
+  w.start = INT_MAX;
+  w.total = nb;
+  if (!w.strided) return w;
+  const int lane = int(threadIdx.x) % kWave;
+  int n = 0;
+  bool off = false;
+  if (lane < ne) {
+    w.start = E[lane].first;
+    n = (lane + 1 < ne ? E[lane + 1].first : nb) - w.start;
+    off = active && !active[E[lane].prob];
+  }
+  if (__ballot(off) == 0) return w;
+  int sum = off ? 0 : n;                   // inclusive prefix sums over the entries
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int v = __shfl_up(sum, o, kWave);
+    if (lane >= o) sum += v;
+  }
+  w.total = __shfl(sum, kWave - 1, kWave);
+  if (lane < ne) w.start = sum - (off ? 0 : n);
+  return w;
+}
+
+// entry and block of work item v: the last entry that starts at or before v (an inactive one
+// starts where the next one does)
+__device__ __forceinline__ int work_entry(const BatchWork& w, int v, int* blk) {
+  const int e = __popcll(__ballot(w.start <= v)) - 1;
+  *blk = v - __shfl(w.start, e, kWave);
+  return __builtin_amdgcn_readfirstlane(e);
+}
+
+// f(entry, block of the entry) for this workgroup's share
+template <class F>
+__device__ __forceinline__ void for_batch(const BEntry* __restrict__ E, int ne, int nb,
+                                          const int* __restrict__ active, F f) {
+  const BatchWork w = batch_work(E, ne, nb, active);
+  for (int v = int(blockIdx.x); v < w.total; v += int(gridDim.x)) {
+    int e, blk;
+    if (w.strided) {
+      e = work_entry(w, xcd_remap(v, w.total), &blk);
+    } else {
+      e = __builtin_amdgcn_readfirstlane(find_entry_wave(E, ne, v));
+      if (active && !active[E[e].prob]) return;
+      blk = v - E[e].first;
+    }
+    f(E[e], __builtin_amdgcn_readfirstlane(blk));
+  }
+}
+
+// ---- eight right-hand sides of one component: kRowLanes lanes per row, each with kRowRhs of the
+// row's values, which lie together in memory.  With one lane per value every wave load of
+// operator values brought 64 bytes for 64 lanes, and the vector memory pipe bound the sweep.
+//
+// Measured on 16 problems, 1.96M nodes together, 8 right-hand sides, FP64 (560 MB that a sweep
+// moves): sweep 265 us with one lane per value and workgroups over all XCDs in turn, 169 us with 4
+// lanes per row and the work shared as above; product 207 and 139, prolongation 110 and 68; with
+// one of the problems left 28 and 14.8 us.  Whole solve 62.0 ms; 49.0 with 4 lanes per row, 45.6 with
+// 2, 51.7 with 1.  Grids of 2,048 and 8,192 workgroups are within 0.5% of 4,096.
+constexpr int kRowRhs = 8 / kRowLanes;
+constexpr int kRows = kWave / kRowLanes;
+
+template <class X>
+struct RowVec {
+  X v[kRowRhs];
+};
+template <class X>
+__device__ __forceinline__ RowVec<X> row_load(const X* p) {      // 8-byte alignment is enough
+  RowVec<X> r;
+  __builtin_memcpy(&r, p, sizeof(r));
+  return r;
+}
+template <class X>
+__device__ __forceinline__ void row_store(X* p, const RowVec<X>& r) {
+  __builtin_memcpy(p, &r, sizeof(r));
+}
+
+struct RowLane {
+  int slice, r, node;
+  int64_t at;                              // the lane's first value in a vector
+  int q;                                   // its first right-hand side
+  bool valid;
+};
+__device__ __forceinline__ RowLane row_lane(int n, int nslices, const int32_t* perm, int slice, int lane) {
+  RowLane s;
+  s.slice = __builtin_amdgcn_readfirstlane(slice);
+  s.r = lane / kRowLanes;
+  s.q = lane % kRowLanes * kRowRhs;
+  const int pos = s.slice * kRows + s.r;
+  s.valid = s.slice < nslices && pos < n;
+  s.node = s.valid ? (perm ? perm[pos] : pos) : 0;
+  s.at = int64_t(s.node) * 8 + s.q;
+  return s;
+}
+
+// NB slots as in sell_batch: indices and values, then the gathers, then the multiply-adds
+template <int NB, int K, class XI, class T, bool C16>
+__device__ __forceinline__ void rows_batch(const SellDev& A, int k, const RowLane& s, const XI* __restrict__ x,
+                                           T (&acc)[kRowRhs]) {
+  unsigned js[NB];
+  typename Val<K>::raw av[NB];
+  RowVec<XI> xv[NB];
+#pragma unroll
+  for (int u = 0; u < NB; ++u) {
+    const int64_t e = int64_t(k + u) * kRows + s.r;
+    js[u] = slot_col<C16, true>(A, k + u, e);
+    av[u] = Val<K>::template load<true>(A.val, e);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int u = 0; u < NB; ++u) xv[u] = row_load(x + uint64_t(js[u]) * 8 + s.q);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int u = 0; u < NB; ++u)
+#pragma unroll
+    for (int i = 0; i < kRowRhs; ++i) acc[i] += T(Val<K>::dec(av[u])) * T(xv[u].v[i]);
+}
+template <int N, int K, class XI, class T, bool C16>
+__device__ __forceinline__ void rows_rest(int rem, const SellDev& A, int k, const RowLane& s,
+                                          const XI* __restrict__ x, T (&acc)[kRowRhs]) {
+  if constexpr (N >= 1) {
+    if (rem == N) rows_batch<N, K, XI, T, C16>(A, k, s, x, acc);
+    else rows_rest<N - 1, K, XI, T, C16>(rem, A, k, s, x, acc);
+  }
+}
+template <int K, class XI, class T, int KB, bool C16>
+__device__ __forceinline__ void rows_loop(const SellDev& A, const RowLane& s, const XI* __restrict__ x,
+                                          T (&acc)[kRowRhs]) {
+  constexpr int NB = KB / 2;               // two or more values per slot
+  int k, k1;
+  slot_range(A, s.slice, k, k1);
+  for (; k + NB <= k1; k += NB) rows_batch<NB, K, XI, T, C16>(A, k, s, x, acc);
+  rows_rest<NB - 1, K, XI, T, C16>(k1 - k, A, k, s, x, acc);
+}
+template <int K, class XI, class T, int KB, bool C16>
+__device__ __forceinline__ void rows_dot(const SellDev& A, const RowLane& s, const XI* __restrict__ x,
+                                         T (&acc)[kRowRhs]) {
+#pragma unroll
+  for (int i = 0; i < kRowRhs; ++i) acc[i] = T(0);
+  if (!s.valid) return;
+  if (C16 && is_wide(A, s.slice)) rows_loop<K, XI, T, KB, false>(A, s, x, acc);
+  else rows_loop<K, XI, T, KB, C16>(A, s, x, acc);
+  if (K == VK_F16 || K == VK_BF16) {
+    const T f = T(ldexpf(1.0f, A.rexp[int64_t(s.slice) * kRows + s.r]));
+#pragma unroll
+    for (int i = 0; i < kRowRhs; ++i) acc[i] *= f;
+  }
+}
+
+// spmv_slice of one component for the lane's right-hand sides
+template <int K, class XI, class XO, class T, int MODE, int KB, bool C16>
+__device__ __forceinline__ RowVec<XO> rows_spmv(const SellDev& A, const XO* __restrict__ b, const XI* __restrict__ x,
+                                          XO* __restrict__ y, const uint8_t* __restrict__ mask, int slice) {
+  const RowLane s = row_lane(A.n, A.nslices, A.perm, slice, int(threadIdx.x) % kWave);
+  RowVec<XO> bv = {};
+  uint8_t mk = 0;
+  if (MODE != 0 && s.valid) {
+    bv = row_load(b + s.at);
+    if (MODE == 2) mk = mask[s.node];
+  }
+  T acc[kRowRhs];
+  rows_dot<K, XI, T, KB, C16>(A, s, x, acc);
+  RowVec<XO> o;
+#pragma unroll
+  for (int i = 0; i < kRowRhs; ++i) {
+    T out = T(0);
+    if (s.valid) out = MODE == 0 ? acc[i] : T(bv.v[i]) - acc[i];
+    if (MODE == 2 && mk) out = T(0);
+    o.v[i] = XO(out);
+  }
+  if (s.valid) row_store(y + s.at, o);
+  return o;
+}
+
+template <int K, class X, class T, int KB, bool C16>
+__device__ __forceinline__ void rows_sweep(const SellDev& A, const X* __restrict__ S, const X* __restrict__ b,
+                                           const X* __restrict__ x, X* __restrict__ xo, T omega, int slice) {
+  const RowLane s = row_lane(A.n, A.nslices, A.perm, slice, int(threadIdx.x) % kWave);
+  RowVec<X> bv = {}, xv = {};
+  X sv = X(0);
+  if (s.valid) {
+    bv = row_load(b + s.at);
+    xv = row_load(x + s.at);
+    sv = S[int64_t(s.slice) * kRows + s.r];
+  }
+  T acc[kRowRhs];
+  rows_dot<K, X, T, KB, C16>(A, s, x, acc);
+  RowVec<X> o;
+#pragma unroll
+  for (int i = 0; i < kRowRhs; ++i) {
+    T upd = T(0);
+    upd += T(sv) * (T(bv.v[i]) - acc[i]);
+    o.v[i] = X(T(xv.v[i]) + omega * upd);
+  }
+  if (s.valid) row_store(xo + s.at, o);
+}
+
+template <class X, class T>
+__device__ __forceinline__ void rows_sweep0(const SellDev& A, const X* __restrict__ S, const X* __restrict__ b,
+                                            X* __restrict__ xo, T omega, int slice) {
+  const RowLane s = row_lane(A.n, A.nslices, A.perm, slice, int(threadIdx.x) % kWave);
+  if (!s.valid) return;
+  const RowVec<X> bv = row_load(b + s.at);
+  const X sv = S[int64_t(s.slice) * kRows + s.r];
+  RowVec<X> o;
+#pragma unroll
+  for (int i = 0; i < kRowRhs; ++i) {
+    T upd = T(0);
+    upd += T(sv) * T(bv.v[i]);
+    o.v[i] = X(omega * upd);
+  }
+  row_store(xo + s.at, o);
+}
+
+// transfers, as tsell_lane
+template <int NB, class X, class T, class WT, bool MC, bool NT>
+__device__ __forceinline__ void trows_batch(const TSellDev& M, int k, const RowLane& s, const X* __restrict__ in,
+                                            const uint8_t* __restrict__ mcol, T (&acc)[kRowRhs]) {
+  unsigned js[NB];
+  WT ws[NB];
+  RowVec<X> vs[NB];
+  uint8_t ms[NB];
+#pragma unroll
+  for (int u = 0; u < NB; ++u) {
+    const int64_t e = int64_t(k + u) * kRows + s.r;
+    js[u] = unsigned(stream_load<NT>(M.col + e));
+    ws[u] = stream_load<NT>(static_cast<const WT*>(M.w) + e);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int u = 0; u < NB; ++u) {
+    vs[u] = row_load(in + uint64_t(js[u]) * 8 + s.q);
+    ms[u] = MC ? mcol[js[u]] : uint8_t(0);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int u = 0; u < NB; ++u)
+#pragma unroll
+    for (int i = 0; i < kRowRhs; ++i) acc[i] += T(ws[u]) * (ms[u] ? T(0) : T(vs[u].v[i]));
+}
+template <int N, class X, class T, class WT, bool MC, bool NT>
+__device__ __forceinline__ void trows_rest(int rem, const TSellDev& M, int k, const RowLane& s,
+                                           const X* __restrict__ in, const uint8_t* __restrict__ mcol,
+                                           T (&acc)[kRowRhs]) {
+  if constexpr (N >= 1) {
+    if (rem == N) trows_batch<N, X, T, WT, MC, NT>(M, k, s, in, mcol, acc);
+    else trows_rest<N - 1, X, T, WT, MC, NT>(rem, M, k, s, in, mcol, acc);
+  }
+}
+template <class X, class T, class WT, bool MC, bool NT>
+__device__ __forceinline__ void trows_loop(const TSellDev& M, const RowLane& s, const X* __restrict__ in,
+                                           const uint8_t* __restrict__ mcol, T (&acc)[kRowRhs]) {
+  constexpr int KB = 4;
+  int k, k1;
+  slot_range(M, s.slice, k, k1);
+  for (; k + KB <= k1; k += KB) trows_batch<KB, X, T, WT, MC, NT>(M, k, s, in, mcol, acc);
+  trows_rest<KB - 1, X, T, WT, MC, NT>(k1 - k, M, k, s, in, mcol, acc);
+}
+template <class X, class T, class WT, bool MC, int MODE>
+__device__ __forceinline__ void trows(const TSellDev& M, int slice, const X* __restrict__ in, X* __restrict__ out,
+                                      const uint8_t* __restrict__ mrow, const uint8_t* __restrict__ mcol) {
+  const RowLane s = row_lane(M.nrows, M.nslices, nullptr, slice, int(threadIdx.x) % kWave);
+  if (!s.valid) return;
+  const uint8_t masked = mrow[s.node];
+  RowVec<X> old = {};
+  if (MODE == 1) old = row_load(out + s.at);
+  T acc[kRowRhs];
+#pragma unroll
+  for (int i = 0; i < kRowRhs; ++i) acc[i] = T(0);
+  if (M.nt) trows_loop<X, T, WT, MC, true>(M, s, in, mcol, acc);
+  else trows_loop<X, T, WT, MC, false>(M, s, in, mcol, acc);
+  RowVec<X> o;
+#pragma unroll
+  for (int i = 0; i < kRowRhs; ++i) o.v[i] = MODE == 0 ? (masked ? X(0) : X(acc[i])) : X(T(old.v[i]) + acc[i]);
+  if (MODE == 0 || !masked) row_store(out + s.at, o);
+}
+
 // V-cycle steps on slices (sweep0, sweep, masked defect) for every problem of the batch
 template <int B, int NR, int K, class X, class T, int KIND, int KB, bool C16>
-__global__ __launch_bounds__(kThreads) void k_bsell(const BEntry* __restrict__ E, int ne, T omega,
+__global__ __launch_bounds__(kThreads) void k_bsell(const BEntry* __restrict__ E, int ne, int nb, T omega,
                                                     const int* __restrict__ active) {
-  __shared__ int se;
-  block_entry(E, ne, se);
-  const BEntry& e = E[se];
-  if (active && !active[e.prob]) return;
-  const SliceLane s = slice_lane<B, NR>(e.A, (blockIdx.x - e.first) * kSliceWaves + threadIdx.x / kWave,
-                                        threadIdx.x % kWave);
-  if (KIND == BK_SWEEP0)
-    sweep0_slice<B, NR, X, T>(static_cast<const X*>(e.S), static_cast<const X*>(e.in0), static_cast<X*>(e.out),
-                              omega, s);
-  else if (KIND == BK_SWEEP)
-    sweep_slice<B, NR, K, X, T, KB, C16, 1>(e.A, static_cast<const X*>(e.S), static_cast<const X*>(e.in0),
-                                    static_cast<const X*>(e.in1), static_cast<X*>(e.out), omega, s);
-  else
-    spmv_slice<B, NR, K, X, X, T, 2, KB, C16, 1>(e.A, static_cast<const X*>(e.in0), static_cast<const X*>(e.in1),
-                                         static_cast<X*>(e.out), e.mask, s);
+  for_batch(E, ne, nb, active, [&](const BEntry& e, int blk) {
+    const int slice = blk * kSliceWaves + int(threadIdx.x) / kWave;
+    const X *S = static_cast<const X*>(e.S), *in0 = static_cast<const X*>(e.in0), *in1 = static_cast<const X*>(e.in1);
+    X* out = static_cast<X*>(e.out);
+    if constexpr (NR == 8) {
+      if (KIND == BK_SWEEP0) rows_sweep0<X, T>(e.A, S, in0, out, omega, slice);
+      else if (KIND == BK_SWEEP) rows_sweep<K, X, T, KB, C16>(e.A, S, in0, in1, out, omega, slice);
+      else rows_spmv<K, X, X, T, 2, KB, C16>(e.A, in0, in1, out, e.mask, slice);
+    } else {
+      const SliceLane s = slice_lane<B, NR>(e.A, slice, threadIdx.x % kWave);
+      if (KIND == BK_SWEEP0) sweep0_slice<B, NR, X, T>(S, in0, out, omega, s);
+      else if (KIND == BK_SWEEP) sweep_slice<B, NR, K, X, T, KB, C16, 1>(e.A, S, in0, in1, out, omega, s);
+      else spmv_slice<B, NR, K, X, X, T, 2, KB, C16, 1>(e.A, in0, in1, out, e.mask, s);
+    }
+  });
 }
 
 // fixed-order sum over the block of values that belong to rhs q = tid % NR; thread q of
@@ -73,31 +365,43 @@ __device__ __forceinline__ double block_sum_rhs(double v, int NR, double* lds) {
 // outer-loop products with the FP64 operator: w = A z (KIND SPMV64) or r = b - A x with
 // partial sums of squares per (block, rhs) (KIND DEFECT64)
 template <int B, int NR, class XI, int KIND, int KB, bool C16>
-__global__ __launch_bounds__(kThreads) void k_bsell64(const BEntry* __restrict__ E, int ne,
+__global__ __launch_bounds__(kThreads) void k_bsell64(const BEntry* __restrict__ E, int ne, int nb,
                                                       const int* __restrict__ active, double* __restrict__ partials) {
-  __shared__ int se;
   __shared__ double lds[kThreads];
-  block_entry(E, ne, se);
-  const BEntry& e = E[se];
-  const bool on = !(active && !active[e.prob]);
-  double out = 0.0, other = 0.0;
-  if (on) {
-    const SliceLane s = slice_lane<B, NR>(e.A, (blockIdx.x - e.first) * kSliceWaves + threadIdx.x / kWave,
-                                          threadIdx.x % kWave);
-    if (KIND == BK_SPMV64) {
-      out = spmv_slice<B, NR, VK_F64, XI, double, double, 0, KB, C16, 1>(e.A, nullptr, static_cast<const XI*>(e.in1),
-                                                                 static_cast<double*>(e.out), nullptr, s);
+  constexpr int MODE = KIND == BK_SPMV64 ? 0 : 1;
+  for_batch(E, ne, nb, active, [&](const BEntry& e, int blk) {
+    const int slice = blk * kSliceWaves + int(threadIdx.x) / kWave;
+    const double* b = static_cast<const double*>(e.in0);
+    const XI* x = static_cast<const XI*>(e.in1);
+    double* y = static_cast<double*>(e.out);
+    if constexpr (NR == 8) {
+      const RowVec<double> out = rows_spmv<VK_F64, XI, double, double, MODE, KB, C16>(e.A, b, x, y, nullptr, slice);
+      if (KIND == BK_DEFECT64) {
+        // wave sums of equal right-hand sides, then the waves in order
+        const int wv = int(threadIdx.x) / kWave, ln = int(threadIdx.x) % kWave;
+#pragma unroll
+        for (int i = 0; i < kRowRhs; ++i) {
+          double v = out.v[i] * out.v[i];
+          for (int o = kWave / 2; o >= kRowLanes; o >>= 1) v += __shfl_down(v, o, kWave);
+          if (ln < kRowLanes) lds[wv * 8 + ln * kRowRhs + i] = v;
+        }
+        __syncthreads();
+        if (threadIdx.x < 8) {
+          double t = 0.0;
+          for (int w = 0; w < kSliceWaves; ++w) t += lds[w * 8 + threadIdx.x];
+          partials[int64_t(e.first + blk) * 8 + threadIdx.x] = t;
+        }
+        __syncthreads();
+      }
     } else {
-      out = spmv_slice<B, NR, VK_F64, double, double, double, 1, KB, C16, 1>(e.A, static_cast<const double*>(e.in0),
-                                                                     static_cast<const double*>(e.in1),
-                                                                     static_cast<double*>(e.out), nullptr, s);
-      other = out;
+      const SliceLane s = slice_lane<B, NR>(e.A, slice, threadIdx.x % kWave);
+      const double out = spmv_slice<B, NR, VK_F64, XI, double, double, MODE, KB, C16, 1>(e.A, b, x, y, nullptr, s);
+      if (KIND == BK_DEFECT64) {
+        const double t = block_sum_rhs(out * out, NR, lds);
+        if (threadIdx.x < NR) partials[int64_t(e.first + blk) * NR + threadIdx.x] = t;
+      }
     }
-  }
-  if (KIND == BK_DEFECT64) {               // lane % NR is the right-hand side
-    const double t = block_sum_rhs(out * other, NR, lds);
-    if (threadIdx.x < NR) partials[int64_t(blockIdx.x) * NR + threadIdx.x] = t;
-  }
+  });
 }
 
 template <int B, int NR, class X, class T, int KIND>
@@ -114,23 +418,29 @@ __global__ __launch_bounds__(kThreads) void k_belem(const BEntry* __restrict__ E
 // restriction (rows = coarse nodes, row mask M_c) and prolongation + correction (rows =
 // fine nodes, row mask M_f, column mask M_c) of every problem with the sliced transfers
 template <int B, int NR, class X, class T, int KIND>
-__global__ __launch_bounds__(kThreads) void k_btsell(const BEntry* __restrict__ E, int ne,
+__global__ __launch_bounds__(kThreads) void k_btsell(const BEntry* __restrict__ E, int ne, int nb,
                                                      const int* __restrict__ active) {
-  __shared__ int se;
-  block_entry(E, ne, se);
-  const BEntry& e = E[se];
-  if (active && !active[e.prob]) return;
-  const int slice = (blockIdx.x - e.first) * kSliceWaves + threadIdx.x / kWave;
-  const int lane = threadIdx.x % kWave;
-  const X* in = static_cast<const X*>(e.in0);
-  X* out = static_cast<X*>(e.out);
-  if (KIND == BK_RESTRICT) {
-    if (e.Ts.f32) tsell_lane<B, NR, X, T, float, false, 0>(e.Ts, slice, lane, in, out, e.mask_c, nullptr);
-    else tsell_lane<B, NR, X, T, double, false, 0>(e.Ts, slice, lane, in, out, e.mask_c, nullptr);
-  } else {
-    if (e.Ts.f32) tsell_lane<B, NR, X, T, float, true, 1>(e.Ts, slice, lane, in, out, e.mask, e.mask_c);
-    else tsell_lane<B, NR, X, T, double, true, 1>(e.Ts, slice, lane, in, out, e.mask, e.mask_c);
-  }
+  for_batch(E, ne, nb, active, [&](const BEntry& e, int blk) {
+    const int slice = blk * kSliceWaves + int(threadIdx.x) / kWave;
+    const int lane = int(threadIdx.x) % kWave;
+    const X* in = static_cast<const X*>(e.in0);
+    X* out = static_cast<X*>(e.out);
+    if constexpr (NR == 8) {
+      if (KIND == BK_RESTRICT) {
+        if (e.Ts.f32) trows<X, T, float, false, 0>(e.Ts, slice, in, out, e.mask_c, nullptr);
+        else trows<X, T, double, false, 0>(e.Ts, slice, in, out, e.mask_c, nullptr);
+      } else {
+        if (e.Ts.f32) trows<X, T, float, true, 1>(e.Ts, slice, in, out, e.mask, e.mask_c);
+        else trows<X, T, double, true, 1>(e.Ts, slice, in, out, e.mask, e.mask_c);
+      }
+    } else if (KIND == BK_RESTRICT) {
+      if (e.Ts.f32) tsell_lane<B, NR, X, T, float, false, 0>(e.Ts, slice, lane, in, out, e.mask_c, nullptr);
+      else tsell_lane<B, NR, X, T, double, false, 0>(e.Ts, slice, lane, in, out, e.mask_c, nullptr);
+    } else {
+      if (e.Ts.f32) tsell_lane<B, NR, X, T, float, true, 1>(e.Ts, slice, lane, in, out, e.mask, e.mask_c);
+      else tsell_lane<B, NR, X, T, double, true, 1>(e.Ts, slice, lane, in, out, e.mask, e.mask_c);
+    }
+  });
 }
 
 // coarse solve x = Ainv b for NR right-hand sides, one wavefront per row
@@ -418,33 +728,33 @@ __global__ void k_bclose(int j, int n_inst, int* kk, const int* iact) {
 }
 
 template <int B, int NR, int K, class X, class T, int KB, bool C16>
-hipError_t batched_sell(int kind, const BEntry* E, int ne, int nb, double omega, const int* active,
+hipError_t batched_sell(int kind, const BEntry* E, int ne, int nb, int g, double omega, const int* active,
                         double* partials, hipStream_t s) {
   switch (kind) {
-    case BK_SWEEP: hipLaunchKernelGGL((k_bsell<B, NR, K, X, T, BK_SWEEP, KB, C16>), nb, kThreads, 0, s, E, ne, T(omega), active); break;
-    case BK_DEFECT: hipLaunchKernelGGL((k_bsell<B, NR, K, X, T, BK_DEFECT, KB, C16>), nb, kThreads, 0, s, E, ne, T(omega), active); break;
-    case BK_SPMV64: hipLaunchKernelGGL((k_bsell64<B, NR, X, BK_SPMV64, KB, C16>), nb, kThreads, 0, s, E, ne, active, partials); break;
-    case BK_DEFECT64: hipLaunchKernelGGL((k_bsell64<B, NR, double, BK_DEFECT64, KB, C16>), nb, kThreads, 0, s, E, ne, active, partials); break;
+    case BK_SWEEP: hipLaunchKernelGGL((k_bsell<B, NR, K, X, T, BK_SWEEP, KB, C16>), g, kThreads, 0, s, E, ne, nb, T(omega), active); break;
+    case BK_DEFECT: hipLaunchKernelGGL((k_bsell<B, NR, K, X, T, BK_DEFECT, KB, C16>), g, kThreads, 0, s, E, ne, nb, T(omega), active); break;
+    case BK_SPMV64: hipLaunchKernelGGL((k_bsell64<B, NR, X, BK_SPMV64, KB, C16>), g, kThreads, 0, s, E, ne, nb, active, partials); break;
+    case BK_DEFECT64: hipLaunchKernelGGL((k_bsell64<B, NR, double, BK_DEFECT64, KB, C16>), g, kThreads, 0, s, E, ne, nb, active, partials); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
 template <int B, int NR, int K, class X, class T>
-hipError_t batched_t(int kind, const BEntry* E, int ne, int nb, double omega, const int* active, double* partials,
+hipError_t batched_t(int kind, const BEntry* E, int ne, int nb, int g, double omega, const int* active, double* partials,
                      int kb, hipStream_t s) {
   switch (kind) {
     case BK_SWEEP: case BK_DEFECT: case BK_SPMV64: case BK_DEFECT64:
       // kb < 0 selects the 16-bit column format (every entry of the launch has it)
       if (kb < 0) {
-        if (-kb == kb_alt<B>()) return batched_sell<B, NR, K, X, T, kb_alt<B>(), true>(kind, E, ne, nb, omega, active, partials, s);
-        return batched_sell<B, NR, K, X, T, kb_default<B>(), true>(kind, E, ne, nb, omega, active, partials, s);
+        if (-kb == kb_alt<B>()) return batched_sell<B, NR, K, X, T, kb_alt<B>(), true>(kind, E, ne, nb, g, omega, active, partials, s);
+        return batched_sell<B, NR, K, X, T, kb_default<B>(), true>(kind, E, ne, nb, g, omega, active, partials, s);
       }
-      if (kb == kb_alt<B>()) return batched_sell<B, NR, K, X, T, kb_alt<B>(), false>(kind, E, ne, nb, omega, active, partials, s);
-      return batched_sell<B, NR, K, X, T, kb_default<B>(), false>(kind, E, ne, nb, omega, active, partials, s);
-    case BK_SWEEP0: hipLaunchKernelGGL((k_bsell<B, NR, K, X, T, BK_SWEEP0, kb_default<B>(), false>), nb, kThreads, 0, s, E, ne, T(omega), active); break;
-    case BK_RESTRICT: hipLaunchKernelGGL((k_btsell<B, NR, X, T, BK_RESTRICT>), nb, kThreads, 0, s, E, ne, active); break;
-    case BK_PROLONG: hipLaunchKernelGGL((k_btsell<B, NR, X, T, BK_PROLONG>), nb, kThreads, 0, s, E, ne, active); break;
+      if (kb == kb_alt<B>()) return batched_sell<B, NR, K, X, T, kb_alt<B>(), false>(kind, E, ne, nb, g, omega, active, partials, s);
+      return batched_sell<B, NR, K, X, T, kb_default<B>(), false>(kind, E, ne, nb, g, omega, active, partials, s);
+    case BK_SWEEP0: hipLaunchKernelGGL((k_bsell<B, NR, K, X, T, BK_SWEEP0, kb_default<B>(), false>), g, kThreads, 0, s, E, ne, nb, T(omega), active); break;
+    case BK_RESTRICT: hipLaunchKernelGGL((k_btsell<B, NR, X, T, BK_RESTRICT>), g, kThreads, 0, s, E, ne, nb, active); break;
+    case BK_PROLONG: hipLaunchKernelGGL((k_btsell<B, NR, X, T, BK_PROLONG>), g, kThreads, 0, s, E, ne, nb, active); break;
     case BK_FILL0: hipLaunchKernelGGL((k_belem<B, NR, X, T, BK_FILL0>), nb, kThreads, 0, s, E, ne, active); break;
     case BK_COARSE: hipLaunchKernelGGL((k_bcoarse<NR, X>), nb, kThreads, 0, s, E, ne, active); break;
     default: return hipErrorInvalidValue;
@@ -453,16 +763,16 @@ hipError_t batched_t(int kind, const BEntry* E, int ne, int nb, double omega, co
 }
 
 template <int B, int NR>
-hipError_t batched_bn(int kind, const BEntry* E, int ne, int nb, int vkind, int xk, double omega, const int* active,
+hipError_t batched_bn(int kind, const BEntry* E, int ne, int nb, int g, int vkind, int xk, double omega, const int* active,
                       double* partials, int kb, hipStream_t s) {
   if (xk == X_F64) {
     if (vkind != VK_F64) return hipErrorInvalidValue;
-    return batched_t<B, NR, VK_F64, double, double>(kind, E, ne, nb, omega, active, partials, kb, s);
+    return batched_t<B, NR, VK_F64, double, double>(kind, E, ne, nb, g, omega, active, partials, kb, s);
   }
   switch (vkind) {
-    case VK_F32: return batched_t<B, NR, VK_F32, float, float>(kind, E, ne, nb, omega, active, partials, kb, s);
-    case VK_F16: return batched_t<B, NR, VK_F16, float, float>(kind, E, ne, nb, omega, active, partials, kb, s);
-    case VK_BF16: return batched_t<B, NR, VK_BF16, float, float>(kind, E, ne, nb, omega, active, partials, kb, s);
+    case VK_F32: return batched_t<B, NR, VK_F32, float, float>(kind, E, ne, nb, g, omega, active, partials, kb, s);
+    case VK_F16: return batched_t<B, NR, VK_F16, float, float>(kind, E, ne, nb, g, omega, active, partials, kb, s);
+    case VK_BF16: return batched_t<B, NR, VK_BF16, float, float>(kind, E, ne, nb, g, omega, active, partials, kb, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -485,19 +795,20 @@ int batched_blocks(int kind, const SellDev& A, const TSellDev& Ts, int n0, int N
 }
 
 hipError_t launch_batched(int kind, const BEntry* E, int ne, int nb, int B, int NR, int vkind, int xk, double omega,
-                          const int* active, double* partials, int kb, hipStream_t s) {
+                          const int* active, double* partials, int kb, int grid, hipStream_t s) {
   if (nb == 0 || ne == 0) return hipSuccess;
+  const int g = ne <= kWave && nb > grid ? grid : nb;
   if (NR == 1) {
     switch (B) {
-      case 1: return batched_bn<1, 1>(kind, E, ne, nb, vkind, xk, omega, active, partials, kb, s);
-      case 3: return batched_bn<3, 1>(kind, E, ne, nb, vkind, xk, omega, active, partials, kb, s);
-      case 4: return batched_bn<4, 1>(kind, E, ne, nb, vkind, xk, omega, active, partials, kb, s);
+      case 1: return batched_bn<1, 1>(kind, E, ne, nb, g, vkind, xk, omega, active, partials, kb, s);
+      case 3: return batched_bn<3, 1>(kind, E, ne, nb, g, vkind, xk, omega, active, partials, kb, s);
+      case 4: return batched_bn<4, 1>(kind, E, ne, nb, g, vkind, xk, omega, active, partials, kb, s);
       default: return hipErrorInvalidValue;
     }
   }
   if (NR == 8) {
     switch (B) {
-      case 1: return batched_bn<1, 8>(kind, E, ne, nb, vkind, xk, omega, active, partials, kb, s);
+      case 1: return batched_bn<1, 8>(kind, E, ne, nb, g, vkind, xk, omega, active, partials, kb, s);
       default: return hipErrorInvalidValue;
     }
   }

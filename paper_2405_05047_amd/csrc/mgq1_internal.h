@@ -238,7 +238,7 @@ hipError_t launch_unit_columns(int n, int c0, int cols, double* v, hipStream_t s
 hipError_t launch_columns_to_rows(int n, int c0, int cols, const double* v, double* M, hipStream_t s);
 // nodal block inverses of the diagonal blocks of A (FP64 SELL) into S (lane layout,
 // double or float per sk); flag != 0 if a block is singular
-hipError_t launch_block_invert(const SellDev& A, void* S, int sk, int* flag, int NR, hipStream_t s);
+hipError_t launch_block_invert(const SellDev& A, void* S, int sk, int* flag, int row_lanes, hipStream_t s);
 
 // vector kernels (n elements)
 hipError_t launch_fill(int64_t n, void* y, int yk, double v, hipStream_t s);
@@ -362,6 +362,10 @@ enum BKind {
   BK_FILL0 = 8     // out = 0
 };
 
+// lanes per row of one component with 8 right-hand sides (mgq1_batch.hip)
+constexpr int kRowLanes = 2;
+constexpr int row_lanes(int NR) { return NR == 8 ? kRowLanes : NR; }
+
 struct BEntry {
   SellDev A;
   const void* S = nullptr;
@@ -382,8 +386,10 @@ int batched_blocks(int kind, const SellDev& A, const TSellDev& Ts, int n0, int N
 // one batched step; `active[prob] == 0` skips a problem; `partials` for BK_DEFECT64
 // kb: slot batch of the slice kernels (sweep, defect, SpMV64, defect64); 0 = default;
 // negative: -kb with the 16-bit column format (all entries of the launch must have it)
+// grid: workgroups that share the blocks of a larger launch (kBatchGrid)
+constexpr int kBatchGrid = 4096;
 hipError_t launch_batched(int kind, const BEntry* entries, int n_entries, int n_blocks, int B, int NR, int vkind,
-                          int xk, double omega, const int* active, double* partials, int kb, hipStream_t s);
+                          int xk, double omega, const int* active, double* partials, int kb, int grid, hipStream_t s);
 
 // vector segments of the concatenated batch vectors: problem p owns elements
 // [off[p], off[p] + len[p]) and vector blocks [vfirst[p], vfirst[p] + vcount[p])

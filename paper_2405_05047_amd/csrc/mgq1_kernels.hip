@@ -676,15 +676,15 @@ hipError_t launch_columns_to_rows(int n, int c0, int cols, const double* v, doub
   return hipGetLastError();
 }
 
-hipError_t launch_block_invert(const SellDev& A, void* S, int sk, int* flag, int NR, hipStream_t s) {
+hipError_t launch_block_invert(const SellDev& A, void* S, int sk, int* flag, int row_lanes, hipStream_t s) {
   const unsigned g = grid_for(A.n, 256);
   if (g == 0) return hipSuccess;
 #define MGQ1_BI(BB, NN)                                                                                           \
   if (sk == X_F64) hipLaunchKernelGGL((k_block_invert<BB, NN, double>), g, 256, 0, s, A, static_cast<double*>(S), flag); \
   else hipLaunchKernelGGL((k_block_invert<BB, NN, float>), g, 256, 0, s, A, static_cast<float*>(S), flag);
-  if (NR == 8) {
+  if (row_lanes == kRowLanes) {
     if (A.B != 1) return hipErrorInvalidValue;
-    MGQ1_BI(1, 8)
+    MGQ1_BI(1, kRowLanes)
     return hipGetLastError();
   }
   switch (A.B) {

@@ -1630,7 +1630,7 @@ int setup_level(DevOwner* h, const HostLevel& L, bool has_p, int NR, int vkind, 
     pt.mark("  flow form");
   }
   if (!node) {
-  HostSell S = build_sell(L, NR);
+  HostSell S = build_sell(L, row_lanes(NR));
   pt.mark("  sliced layout");
   if ((rc = upload_sell(h, S, VK_F64, D.A64, s))) return rc;
   pt.mark("  FP64 operator upload");
@@ -1641,7 +1641,7 @@ int setup_level(DevOwner* h, const HostLevel& L, bool has_p, int NR, int vkind, 
   if ((rc = dalloc(h, reinterpret_cast<char**>(&D.S), sblk * xsize(xk)))) return rc;
   if (L.sblk.empty()) {
     MG_HIP(launch_fill(int64_t(sblk), D.S, xk, 0.0, s));
-    MG_HIP(launch_block_invert(D.A64, D.S, xk, flag, NR, s));
+    MG_HIP(launch_block_invert(D.A64, D.S, xk, flag, row_lanes(NR), s));
   } else {
     // the caller's fixed smoother matrix S (Sec. 4.1) in the lane layout of the sweeps:
     // lane r * B + c of a slice holds row c of its node's block, column cc at
@@ -1687,8 +1687,8 @@ int setup_level(DevOwner* h, const HostLevel& L, bool has_p, int NR, int vkind, 
       if ((rc = upload_tnode(h, P, L.B, L.mask, coarser->mask, D.Ps, s, &pn))) return rc;
       if ((rc = upload_tnode(h, R, L.B, coarser->mask, L.mask, D.Rs, s, &rn))) return rc;
     }
-    if (!pn && (rc = upload_tsell(h, build_tsell(P, L.B, NR), D.Ps, s))) return rc;
-    if (!rn && (rc = upload_tsell(h, build_tsell(R, L.B, NR), D.Rs, s))) return rc;
+    if (!pn && (rc = upload_tsell(h, build_tsell(P, L.B, row_lanes(NR)), D.Ps, s))) return rc;
+    if (!rn && (rc = upload_tsell(h, build_tsell(R, L.B, row_lanes(NR)), D.Rs, s))) return rc;
     pt.mark("  transfers");
   }
   if (vectors) {
@@ -2026,6 +2026,7 @@ struct mg_batch : DevOwner {
   std::vector<BLaunch> spmv64;        // per Krylov index: w = A z_j
   int nbig = 0;                       // blocks of the outer FP64 products
   int kb64 = 0;                       // slot batch of the outer FP64 products
+  int grid = kBatchGrid;              // MGQ1_BATCH_GRID=n at creation: another (tests; same bits)
   bool c16 = false;                   // all operators carry 16-bit column differences
   hipStream_t cap = nullptr;
   std::vector<hipGraphExec_t> graphs;
@@ -2216,7 +2217,7 @@ int run_launch(mg_batch* h, const BLaunch& L, const BEntry* table, const int* ac
     kb = -(kb ? kb : kd);
   }
   MG_HIP(launch_batched(L.kind, table + L.e0, L.ne, L.nb, h->B, h->NR, h->vkind, h->xk, h->cfg.omega, active,
-                        partials, kb, s));
+                        partials, kb, h->grid, s));
   return MG_OK;
 }
 
@@ -2359,6 +2360,7 @@ int setup_batch(mg_batch* h, const std::vector<std::vector<HostLevel>>& HH, hipS
   const int P = h->P, NR = h->NR;
   int rc;
   int* flag;
+  if (const char* e = std::getenv("MGQ1_BATCH_GRID")) h->grid = std::max(1, std::atoi(e));
   if ((rc = dalloc(h, &flag, 1))) return rc;
   MG_HIP(hipMemsetAsync(flag, 0, sizeof(int), s));
   h->pr.resize(P);
@@ -2382,8 +2384,8 @@ int setup_batch(mg_batch* h, const std::vector<std::vector<HostLevel>>& HH, hipS
   // only if the whole batch's do, so the load kind of the transfers follows the batch
   // total (the batched slice kernels always read their operators non-temporally)
   {
-    // value lanes per slot: B * W with the row-lane stride W = kWave / NR of the batch
-    const int64_t W = kWave / NR;
+    // value lanes per slot: B * W with the row-lane stride W of the batch
+    const int64_t W = kWave / row_lanes(NR);
     auto sbytes = [W](const SellDev& A) {
       const int vb = A.kind == VK_F64 ? 8 : A.kind == VK_F32 ? 4 : 2;
       return A.slots * (int64_t(A.B) * W * vb + int64_t(A.R) * (A.col16 ? 2 : 4));
