@@ -265,6 +265,33 @@ __device__ __forceinline__ T wave_sum(T v) {
   return v;
 }
 
+// The sums over the lanes of equal lane % OMIN of P values per lane (P a power of two up to
+// 32): at every step each half of the lanes keeps one half of the values and hands over the
+// other (P - 1 shuffles and then one per remaining step, instead of one per value and
+// step).  On return v[0], v[1] .. are the sums of the values number `which`, `which` + 1 ..
+// (P * OMIN / 64 of them, at least one); the order of the additions is fixed.
+template <int P, int O, int OMIN, int NT>
+__device__ __forceinline__ void wave_sums_step(double (&v)[NT], int lane, int& which) {
+  if constexpr (O >= OMIN) {
+    if constexpr (P > 1) {
+      constexpr int H = P / 2;
+      const bool up = (lane & O) != 0;
+#pragma unroll
+      for (int i = 0; i < H; ++i) {
+        const double send = up ? v[i] : v[i + H];
+        v[i] = (up ? v[i + H] : v[i]) + __shfl_xor(send, O, kWave);
+      }
+      which += up ? H : 0;
+      wave_sums_step<H, O / 2, OMIN, NT>(v, lane, which);
+    } else {
+      v[0] = v[0] + __shfl_xor(v[0], O, kWave);
+      wave_sums_step<1, O / 2, OMIN, NT>(v, lane, which);
+    }
+  }
+}
+
+constexpr int pow2_above(int n) { int p = 1; while (p < n) p *= 2; return p; }
+
 // sum over the block in a fixed order, returned to every thread
 __device__ __forceinline__ double block_allsum(double v, double* lds) {
   v = wave_sum(v);

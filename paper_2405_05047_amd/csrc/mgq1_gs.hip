@@ -24,32 +24,6 @@ namespace {
 
 constexpr int kGsMaxBlocks = 256;          // partial sums per dot product: one block per CU
 
-// The sums over the wave of P values per lane (P a power of two up to 32): at every step
-// each half of the lanes keeps one half of the values and hands over the other (P - 1
-// shuffles and then one per remaining step, instead of 6 P).  On return v[0] is the wave's
-// sum of value number `which`; the order of the additions is fixed.
-template <int P, int O, int NT>
-__device__ __forceinline__ void wave_sums_step(double (&v)[NT], int lane, int& which) {
-  if constexpr (O >= 1) {
-    if constexpr (P > 1) {
-      constexpr int H = P / 2;
-      const bool up = (lane & O) != 0;
-#pragma unroll
-      for (int i = 0; i < H; ++i) {
-        const double send = up ? v[i] : v[i + H];
-        v[i] = (up ? v[i + H] : v[i]) + __shfl_xor(send, O, kWave);
-      }
-      which += up ? H : 0;
-      wave_sums_step<H, O / 2, NT>(v, lane, which);
-    } else {
-      v[0] = v[0] + __shfl_xor(v[0], O, kWave);
-      wave_sums_step<1, O / 2, NT>(v, lane, which);
-    }
-  }
-}
-
-constexpr int pow2_above(int n) { int p = 1; while (p < n) p *= 2; return p; }
-
 // Partial sums of the NV dot products (w, v_i) (rows 0 .. NV-1 of the group's output) and
 // (v_j, v_i) (rows NV .. 2 NV - 1), v_i = V + i * ldv for the group's NV vectors, row q of
 // block blk at out[q * gridDim.x + blk].  OWN: v_j is the group's last vector.
@@ -77,7 +51,7 @@ __global__ __launch_bounds__(kRedThreads) void k_gs_dots(int64_t n, const double
   }
   const int lane = int(threadIdx.x) % kWave, wv = int(threadIdx.x) / kWave;
   int which = 0;
-  wave_sums_step<P, kWave / 2, P>(acc, lane, which);
+  wave_sums_step<P, kWave / 2, 1>(acc, lane, which);
   if (which < NQ) lds[wv][which] = acc[0];   // several lanes may hold the same sum
   __syncthreads();
   if (int(threadIdx.x) < NQ) {

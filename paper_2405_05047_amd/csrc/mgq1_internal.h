@@ -411,10 +411,13 @@ hipError_t launch_bdot(const BSegs& g, const double* a, const double* b, double*
 // (pfirst / pcount: blocks per problem of the producing launch)
 hipError_t launch_bfinish(const double* partials, const int* pfirst, const int* pcount, int n_inst, int NR,
                           double* out, int sqrt_out, hipStream_t s);
-// batched modified Gram-Schmidt step / normalisation; per-instance Hessenberg entries are
-// written to H[inst * hstride] (H points at the entry's offset inside each instance block)
-hipError_t launch_bmgs_step(const BSegs& g, double* w, const double* vi, const double* vnext, const double* pin,
-                            double* pout, double* H, int64_t hstride, hipStream_t s);
+// Gram-Schmidt of step j of every instance of the active problems: w loses its parts along the
+// basis V_0 .. V_j (stride ldv), h_i goes to H[inst * hstride + i], the partial sums of the new
+// (w, w) to pnorm.  partials: 2 * m * NR * n_blocks, gram: n_inst * m * m doubles
+hipError_t launch_bgram_schmidt(const BSegs& g, int n_inst, int j, int m, int64_t ldv, double* w, const double* V,
+                                double* partials, double* gram, double* H, int64_t hstride, double* pnorm,
+                                hipStream_t s);
+// normalisation w / ||w||; the norms are written to H[inst * hstride]
 hipError_t launch_bmgs_normalize(const BSegs& g, double* w, const double* pin, double* H, int64_t hstride,
                                  hipStream_t s, float* wc = nullptr);
 // y = x / beta[inst] (0 where beta == 0 or the instance is inactive)

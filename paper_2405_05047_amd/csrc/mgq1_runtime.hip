@@ -2015,7 +2015,9 @@ struct mg_batch : DevOwner {
   int *kk = nullptr, *iact = nullptr;
   int* pact = nullptr;                // problem has an unconverged instance
   int* pstep = nullptr;               // problem has an instance whose Krylov cycle is still open
-  double* pvec[2] = {nullptr, nullptr};
+  double* pvec = nullptr;             // per-block partials of the vector reductions
+  double* pgs = nullptr;              // ... of the Gram-Schmidt dot products
+  double* gram = nullptr;             // Gram entries of the Krylov bases
   double* pbig = nullptr;
   BSegs segs, segs_act, segs_step;   // vector segments: all problems / pact / pstep
   int *bigfirst = nullptr, *bigcount = nullptr;
@@ -2299,22 +2301,15 @@ int enqueue_batch_step(mg_batch* h, int j, hipStream_t s) {
   // the cycle-precision copy of v_j (btop) was written by the kernel that produced v_j
   for (const BLaunch& L : h->plan[j])
     if ((rc = run_launch(h, L, h->dE, h->pstep, nullptr, s))) return rc;
-  // w = A z_j.  (The first Gram-Schmidt dot is a separate pass here: the SpMV's blocks are
-  // far more numerous than the vector blocks, and re-summing their partials per block of
-  // the first step would cost more than the pass.)
+  // w = A z_j
   if ((rc = run_launch(h, h->spmv64[j], h->dE, h->pstep, nullptr, s))) return rc;
   double* w = h->V + int64_t(j + 1) * N;
   const int64_t hs = int64_t(m + 1) * m;
   double* Hj = h->H + int64_t(j) * (m + 1);
   const BSegs& sg = h->segs_step;
-  MG_HIP(launch_bdot(sg, w, h->V, h->pvec[0], s));
-  for (int i = 0; i <= j; ++i) {
-    const double* vi = h->V + int64_t(i) * N;
-    const double* vn = (i < j) ? h->V + int64_t(i + 1) * N : nullptr;
-    MG_HIP(launch_bmgs_step(sg, w, vi, vn, h->pvec[i & 1], h->pvec[(i + 1) & 1], Hj + i, hs, s));
-  }
+  MG_HIP(launch_bgram_schmidt(sg, h->n_inst, j, m, N, w, h->V, h->pgs, h->gram, Hj, hs, h->pvec, s));
   float* wc = h->xk == X_F64 ? nullptr : static_cast<float*>(h->btop);
-  MG_HIP(launch_bmgs_normalize(sg, w, h->pvec[(j + 1) & 1], Hj + j + 1, hs, s, wc));
+  MG_HIP(launch_bmgs_normalize(sg, w, h->pvec, Hj + j + 1, hs, s, wc));
   MG_HIP(launch_bgivens(j, m, h->n_inst, h->H, h->cs, h->sn, h->g, h->st, h->tolv, h->kk, h->iact, s));
   return MG_OK;
 }
@@ -2451,8 +2446,9 @@ int setup_batch(mg_batch* h, const std::vector<std::vector<HostLevel>>& HH, hipS
   h->segs_act.on = h->pact;
   h->segs_step = h->segs;
   h->segs_step.on = h->pstep;
-  for (int q = 0; q < 2; ++q)
-    if ((rc = dalloc(h, &h->pvec[q], blk.size() * NR))) return rc;
+  if ((rc = dalloc(h, &h->pvec, blk.size() * NR))) return rc;
+  if ((rc = dalloc(h, &h->pgs, size_t(2) * m * NR * blk.size()))) return rc;
+  if ((rc = dalloc(h, &h->gram, size_t(ni) * m * m))) return rc;
   // outer FP64 products: blocks per problem
   std::vector<int> bf(P), bc(P);
   int nbig = 0;
@@ -2528,8 +2524,8 @@ int solve_batch_impl(mg_batch* h, const double* b, double* x, mg_solve_stats* st
   }
   if ((rc = to_dev(h->dEdef, es.data(), es.size(), s))) return rc;
   // per-instance ||b|| and tolerances
-  MG_HIP(launch_bdot(h->segs, b, nullptr, h->pvec[0], s));
-  MG_HIP(launch_bfinish(h->pvec[0], h->segs.vfirst, h->segs.vcount, ni, NR, h->bnorm, 1, s));
+  MG_HIP(launch_bdot(h->segs, b, nullptr, h->pvec, s));
+  MG_HIP(launch_bfinish(h->pvec, h->segs.vfirst, h->segs.vcount, ni, NR, h->bnorm, 1, s));
   std::vector<double> bn(ni), tol(ni), beta(ni), res0(ni), resf(ni);
   if ((rc = to_host(bn.data(), h->bnorm, ni, s))) return rc;
   for (int i = 0; i < ni; ++i) tol[i] = c.rtol * bn[i];
