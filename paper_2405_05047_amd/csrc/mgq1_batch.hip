@@ -476,6 +476,57 @@ __global__ __launch_bounds__(kThreads) void k_bcoarse(const BEntry* __restrict__
   if (lane < NR) static_cast<X*>(e.out)[int64_t(i) * NR + lane] = X(acc);
 }
 
+// The same product for the matrices of whole small levels (FP64): a workgroup has
+// kDenseBlockRows rows, its lanes (waves side by side) the columns, so that a matrix row is read
+// in full lines, the right-hand sides once for four rows, and 512 columns are one round of loads.
+constexpr int kDenseBlockRows = 4;
+
+template <int NR>
+__global__ __launch_bounds__(kThreads) void k_bdense(const BEntry* __restrict__ E, int ne, int nb,
+                                                     const int* __restrict__ active) {
+  constexpr int P = kDenseBlockRows * NR, U = 2;
+  __shared__ double lds[kSliceWaves][P];
+  for_batch(E, ne, nb, active, [&](const BEntry& e, int blk) {
+    const int n = e.n0, lane = int(threadIdx.x) % kWave, wave = int(threadIdx.x) / kWave;
+    const int i0 = blk * kDenseBlockRows;
+    const double* b = static_cast<const double*>(e.in0);
+    const double* row[kDenseBlockRows];
+#pragma unroll
+    for (int r = 0; r < kDenseBlockRows; ++r) row[r] = e.Ainv + int64_t(min(i0 + r, n - 1)) * n;
+    double acc[P];
+#pragma unroll
+    for (int q = 0; q < P; ++q) acc[q] = 0.0;
+    for (int k0 = int(threadIdx.x); k0 < n; k0 += U * kThreads) {
+      double a[U][kDenseBlockRows], bv[U][NR];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = min(k0 + u * kThreads, n - 1);
+        const bool ok = k0 + u * kThreads < n;
+#pragma unroll
+        for (int r = 0; r < kDenseBlockRows; ++r) a[u][r] = ok ? row[r][k] : 0.0;
+#pragma unroll
+        for (int q = 0; q < NR; ++q) bv[u][q] = ok ? b[int64_t(k) * NR + q] : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int r = 0; r < kDenseBlockRows; ++r)
+#pragma unroll
+          for (int q = 0; q < NR; ++q) acc[r * NR + q] += a[u][r] * bv[u][q];
+    }
+    int which = 0;
+    wave_sums_step<P, kWave / 2, 1>(acc, lane, which);
+    if (lane % (kWave / P) == 0) lds[wave][which] = acc[0];
+    __syncthreads();
+    if (int(threadIdx.x) < P && i0 + int(threadIdx.x) / NR < n) {
+      double t = 0.0;
+      for (int w = 0; w < kSliceWaves; ++w) t += lds[w][threadIdx.x];
+      static_cast<double*>(e.out)[int64_t(i0) * NR + threadIdx.x] = t;
+    }
+    __syncthreads();
+  });
+}
+
 // ---- segmented vector kernels: block -> problem segment, thread keeps rhs q = tid % NR
 struct SegPos {
   int p, lb, nb, first;
@@ -855,6 +906,10 @@ hipError_t batched_t(int kind, const BEntry* E, int ne, int nb, int g, double om
     case BK_PROLONG: hipLaunchKernelGGL((k_btsell<B, NR, X, T, BK_PROLONG>), g, kThreads, 0, s, E, ne, nb, active); break;
     case BK_FILL0: hipLaunchKernelGGL((k_belem<B, NR, X, T, BK_FILL0>), nb, kThreads, 0, s, E, ne, active); break;
     case BK_COARSE: hipLaunchKernelGGL((k_bcoarse<NR, X>), nb, kThreads, 0, s, E, ne, active); break;
+    case BK_DENSE:
+      if constexpr (sizeof(X) != 8) return hipErrorInvalidValue;
+      else hipLaunchKernelGGL(k_bdense<NR>, g, kThreads, 0, s, E, ne, nb, active);
+      break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -887,6 +942,8 @@ int batched_blocks(int kind, const SellDev& A, const TSellDev& Ts, int n0, int N
       return int(grid_for(int64_t(A.n) * A.B * NR, kThreads));
     case BK_COARSE:
       return int(grid_for(n0, kSliceWaves));
+    case BK_DENSE:
+      return int(grid_for(n0, kDenseBlockRows));
     default:
       return 0;
   }

@@ -359,7 +359,8 @@ enum BKind {
   BK_COARSE = 5,   // out = Ainv in0
   BK_SPMV64 = 6,   // out (FP64) = A64 in1 (cycle precision)
   BK_DEFECT64 = 7, // out = in0 - A64 in1 (all FP64), partial sums of squares per (block, rhs)
-  BK_FILL0 = 8     // out = 0
+  BK_FILL0 = 8,    // out = 0
+  BK_DENSE = 9     // out = Ainv in0 as BK_COARSE, FP64, for larger matrices
 };
 
 // lanes per row of one component with 8 right-hand sides (mgq1_batch.hip)

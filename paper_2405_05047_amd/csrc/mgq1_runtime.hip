@@ -1825,23 +1825,62 @@ int tune_levels(mg_handle* h, hipStream_t s) {
 // damped sweeps only: reduced cycles keep their rounding.  MGQ1_NO_DENSE=1: off (tests).
 constexpr int64_t kDenseRows = 2048;
 
+// The matrix of the V-cycle on levels tl.back() .. 0 (A, S, mask, P, R of the levels, sliced ELL,
+// N[l] unknowns each)
+int dense_cycle(DevOwner* h, const mg_config& c, int coarse_mode, std::vector<TailLevel>& tl,
+                const std::vector<int64_t>& N, int B, const double* Ainv, int n0, double** out, hipStream_t s) {
+  const int top = int(tl.size()) - 1, n = int(N[size_t(top)]);
+  const int cols = std::min(n, 512);             // two workgroups per CU at a time
+  DevOwner tmp;                                  // work vectors, freed on return
+  int rc;
+  int64_t total = 0;
+  for (int64_t v : N) total += v;
+  double* work;
+  if ((rc = dalloc(&tmp, &work, size_t(total) * 4 * cols))) return rc;
+  for (int l = 0; l <= top; ++l)
+    for (void** v : {&tl[size_t(l)].x, &tl[size_t(l)].b, &tl[size_t(l)].r, &tl[size_t(l)].t}) {
+      *v = work;
+      work += size_t(N[size_t(l)]) * cols;
+    }
+  TailLevel* dt;
+  if ((rc = upload(&tmp, &dt, tl, s))) return rc;
+  if ((rc = dalloc(h, out, size_t(n) * n))) return rc;
+  TailParams tp;
+  tp.top = top;
+  tp.nu1 = c.nu1;
+  tp.nu2 = c.nu2;
+  tp.omega = c.omega;
+  tp.Ainv = Ainv;
+  tp.n0 = n0;
+  tp.coarse_mode = coarse_mode;
+  tp.coarse_sweeps = c.coarse_sweeps;
+  TailLevel& T = tl[size_t(top)];
+  for (int c0 = 0; c0 < n; c0 += cols) {
+    const int k = std::min(cols, n - c0);
+    MG_HIP(launch_unit_columns(n, c0, k, static_cast<double*>(T.b), s));
+    MG_HIP(launch_tail(dt, B, VK_F64, X_F64, tp, s, k));
+    MG_HIP(launch_columns_to_rows(n, c0, k, static_cast<double*>(T.x), *out, s));
+  }
+  MG_HIP(hipStreamSynchronize(s));
+  return MG_OK;
+}
+
+bool dense_off() {
+  const char* off = std::getenv("MGQ1_NO_DENSE");
+  return off && std::atoi(off) != 0;
+}
+
 int setup_dense(mg_handle* h, const std::vector<HostLevel>& H, hipStream_t s) {
   const mg_config& c = h->cfg;
-  const char* off = std::getenv("MGQ1_NO_DENSE");
-  if (h->xk != X_F64 || c.smoother != MG_SMOOTH_JACOBI || h->tail_top > 0 || (off && std::atoi(off) != 0)) return MG_OK;
+  if (h->xk != X_F64 || c.smoother != MG_SMOOTH_JACOBI || h->tail_top > 0 || dense_off()) return MG_OK;
   int top = 0;
   for (int l = 1; l <= h->L && h->lv[l].N <= kDenseRows; ++l) top = l;
   if (top < 1) return MG_OK;
-  const int n = int(h->lv[top].N);
-  const int cols = std::min(n, 512);             // two workgroups per CU at a time
-  DevOwner tmp;                                  // work vectors (and copies), freed on return
+  DevOwner tmp;                                  // copies, freed on return
   std::vector<LevelDev> copy(static_cast<size_t>(top) + 1);
   std::vector<TailLevel> tl(size_t(top) + 1);
+  std::vector<int64_t> N(size_t(top) + 1);
   int rc;
-  int64_t total = 0;
-  for (int l = 0; l <= top; ++l) total += h->lv[l].N;
-  double* work;
-  if ((rc = dalloc(&tmp, &work, size_t(total) * 4 * cols))) return rc;
   for (int l = 0; l <= top; ++l) {
     // the workgroup's cycle reads sliced ELL: a level in the node form gets a copy in it
     LevelDev* D = &h->lv[l];
@@ -1855,31 +1894,9 @@ int setup_dense(mg_handle* h, const std::vector<HostLevel>& H, hipStream_t s) {
     T.mask = D->mask;
     T.P = D->P;
     T.R = D->R;
-    for (void** v : {&T.x, &T.b, &T.r, &T.t}) {
-      *v = work;
-      work += size_t(D->N) * cols;
-    }
+    N[size_t(l)] = D->N;
   }
-  TailLevel* dt;
-  if ((rc = upload(&tmp, &dt, tl, s))) return rc;
-  if ((rc = dalloc(h, &h->dense, size_t(n) * n))) return rc;
-  TailParams tp;
-  tp.top = top;
-  tp.nu1 = c.nu1;
-  tp.nu2 = c.nu2;
-  tp.omega = c.omega;
-  tp.Ainv = h->Ainv;
-  tp.n0 = h->n0;
-  tp.coarse_mode = c.coarse_mode;
-  tp.coarse_sweeps = c.coarse_sweeps;
-  TailLevel& T = tl[size_t(top)];
-  for (int c0 = 0; c0 < n; c0 += cols) {
-    const int k = std::min(cols, n - c0);
-    MG_HIP(launch_unit_columns(n, c0, k, static_cast<double*>(T.b), s));
-    MG_HIP(launch_tail(dt, h->lv[0].B, VK_F64, X_F64, tp, s, k));
-    MG_HIP(launch_columns_to_rows(n, c0, k, static_cast<double*>(T.x), h->dense, s));
-  }
-  MG_HIP(hipStreamSynchronize(s));
+  if ((rc = dense_cycle(h, c, c.coarse_mode, tl, N, h->lv[0].B, h->Ainv, h->n0, &h->dense, s))) return rc;
   h->dense_top = top;
   return MG_OK;
 }
@@ -2001,6 +2018,7 @@ struct mg_batch : DevOwner {
   struct Prob {
     int L = 0;
     std::vector<LevelDev> lv;
+    int base = 0;                     // level that Ainv solves (above 0: a dense V-cycle)
     double* Ainv = nullptr;
     int n0 = 0;
   };
@@ -2028,6 +2046,7 @@ struct mg_batch : DevOwner {
   std::vector<BLaunch> spmv64;        // per Krylov index: w = A z_j
   int nbig = 0;                       // blocks of the outer FP64 products
   int kb64 = 0;                       // slot batch of the outer FP64 products
+  bool dense = false;                 // some problem has base > 0
   int grid = kBatchGrid;              // MGQ1_BATCH_GRID=n at creation: another (tests; same bits)
   bool c16 = false;                   // all operators carry 16-bit column differences
   hipStream_t cap = nullptr;
@@ -2105,7 +2124,7 @@ void build_plan(mg_batch* h, int j, std::vector<BLaunch>& out) {
   for (int d = 0; d < h->Dmax; ++d) {
     std::vector<int> ps;
     for (int p = 0; p < P; ++p)
-      if (h->pr[p].L - d >= 1) ps.push_back(p);
+      if (h->pr[p].L - d > h->pr[p].base) ps.push_back(p);
     if (ps.empty()) continue;
     std::vector<BEntry> es;
     if (c.nu1 >= 1) {
@@ -2167,20 +2186,21 @@ void build_plan(mg_batch* h, int j, std::vector<BLaunch>& out) {
   {
     std::vector<BEntry> es;
     for (int p = 0; p < P; ++p) {
-      BEntry e = level_entry(p, 0);
+      const int base = h->pr[p].base;
+      BEntry e = level_entry(p, base);
       e.Ainv = h->pr[p].Ainv;
       e.n0 = h->pr[p].n0;
-      e.in0 = bb[p][0];
-      e.out = own[p][0];
+      e.in0 = bb[p][base];
+      e.out = own[p][base];
       es.push_back(e);
     }
-    out.push_back(add_launch(h, BK_COARSE, es));
+    out.push_back(add_launch(h, h->dense ? BK_DENSE : BK_COARSE, es));
   }
   // ascent
   for (int d = h->Dmax - 1; d >= 0; --d) {
     std::vector<int> ps;
     for (int p = 0; p < P; ++p)
-      if (h->pr[p].L - d >= 1) ps.push_back(p);
+      if (h->pr[p].L - d > h->pr[p].base) ps.push_back(p);
     if (ps.empty()) continue;
     // the descent left cur at the pre-smoothed iterate; the coarser level's correction
     // sits in its own x (its post-smoothing ends there)
@@ -2350,6 +2370,58 @@ int batch_defect(mg_batch* h, hipStream_t s) {
   return MG_OK;
 }
 
+// The same for every problem of a FP64 batch: its levels of up to a common number of unknowns
+// become one dense product in place of the coarse solve, which takes the launches of those
+// depths out of every step.  The rows are the most that keep all matrices within
+// kDenseBatchBytes (30 us of reading while every problem is active, against 7 launches of 5 us
+// per depth).  16 problems with 8 right-hand sides, 1.96M nodes: 42.1 -> 39.9 ms a solve.
+constexpr int64_t kDenseBatchBytes = int64_t(128) << 20;
+
+int setup_batch_dense(mg_batch* h, const std::vector<std::vector<HostLevel>>& HH, int* flag, hipStream_t s) {
+  if (h->xk != X_F64 || dense_off()) return MG_OK;
+  std::vector<int> top(size_t(h->P), 0);
+  bool any = false;
+  for (int64_t rows = kDenseRows; rows >= 64 && !any; rows /= 2) {
+    int64_t bytes = 0;
+    for (int p = 0; p < h->P; ++p) {
+      top[size_t(p)] = 0;
+      for (int l = 1; l <= h->pr[p].L && h->pr[p].lv[l].N <= rows; ++l) top[size_t(p)] = l;
+      const int64_t n = h->pr[p].lv[top[size_t(p)]].N;
+      if (top[size_t(p)] > 0) bytes += n * n * 8;
+    }
+    any = bytes > 0 && bytes <= kDenseBatchBytes;
+  }
+  if (!any) return MG_OK;
+  for (int p = 0; p < h->P; ++p) {
+    auto& pr = h->pr[p];
+    const int t = top[size_t(p)];
+    if (t == 0) continue;
+    DevOwner tmp;                                  // operators in one-right-hand-side slices
+    std::vector<TailLevel> tl(size_t(t) + 1);
+    std::vector<int64_t> N(size_t(t) + 1);
+    int rc;
+    for (int l = 0; l <= t; ++l) {
+      const HostSell S = build_sell(HH[p][l], 1);
+      const size_t sblk = size_t(S.nslices) * h->B * S.W;
+      TailLevel& T = tl[size_t(l)];
+      double* sd;
+      if ((rc = upload_sell(&tmp, S, VK_F64, T.A, s)) || (rc = dalloc(&tmp, &sd, sblk))) return rc;
+      MG_HIP(launch_fill(int64_t(sblk), sd, X_F64, 0.0, s));
+      MG_HIP(launch_block_invert(T.A, sd, X_F64, flag, 1, s));
+      T.S = sd;
+      T.mask = pr.lv[l].mask;
+      T.P = pr.lv[l].P;
+      T.R = pr.lv[l].R;
+      N[size_t(l)] = pr.lv[l].N;
+    }
+    if ((rc = dense_cycle(h, h->cfg, MG_COARSE_EXACT, tl, N, h->B, pr.Ainv, pr.n0, &pr.Ainv, s))) return rc;
+    pr.n0 = int(N[size_t(t)]);
+    pr.base = t;
+  }
+  h->dense = true;
+  return MG_OK;
+}
+
 int setup_batch(mg_batch* h, const std::vector<std::vector<HostLevel>>& HH, hipStream_t s) {
   const mg_config& c = h->cfg;
   const int P = h->P, NR = h->NR;
@@ -2372,6 +2444,7 @@ int setup_batch(mg_batch* h, const std::vector<std::vector<HostLevel>>& HH, hipS
     h->off[p + 1] = h->off[p] + pr.lv[pr.L].N * NR;
   }
   if ((rc = check_flag(flag, s))) return rc;
+  if ((rc = setup_batch_dense(h, HH, flag, s))) return rc;
   h->c16 = true;
   for (const auto& pr : h->pr)
     for (const LevelDev& D : pr.lv) h->c16 = h->c16 && D.Ac.col16 && D.A64.col16;
