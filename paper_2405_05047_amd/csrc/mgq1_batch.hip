@@ -1,7 +1,7 @@
 // HIP kernels of the batched form: every V-cycle step and Krylov vector operation of many
-// independent problems (1 or 8 right-hand sides each) in one launch.  The per-slice
-// bodies are those of the single-problem kernels; a block finds its problem entry with
-// one wave-wide compare of 64 entries, and segmented reductions keep one partial per
+// independent problems (1 or 8 right-hand sides each) in one launch.  With one right-hand side
+// the per-slice bodies are those of the single-problem kernels; a wave finds its problem
+// entry with one compare of 64 entries, and segmented reductions keep one partial per
 // block and right-hand side, re-summed in a fixed order by the consumer kernel.
 #include "mgq1_device.h"
 

@@ -43,9 +43,9 @@ struct SellDev {
   const int32_t* perm = nullptr;    // node at row position slice*R + r (NULL: the position
                                     // itself); rows sorted by length inside windows of slices
   int nt = 1;                       // 1: values and indices read with non-temporal loads
-  const FlowDev* flow = nullptr;    // host: ... or in the flow form
   const NodeDev* node = nullptr;    // host: the level is stored in the node form instead (the
                                     // sliced arrays above are then absent)
+  const FlowDev* flow = nullptr;    // host: ... or in the flow form
 };
 
 // Node form of an operator whose rows repeat: slices of 64 nodes, lane = node, the distinct

@@ -5,9 +5,10 @@
 // value / index streams, cached gathers of x, one pass over A per smoothing sweep, short
 // chains of dependent loads on small levels, and deterministic reductions (no atomics).
 //
-//   SELL slice kernels (defect / SpMV, smoothing sweep): one wavefront per slice of
-//   64/(B*NR) nodes; lane = (node*B + component)*NR + rhs owns one scalar row of one
-//   right-hand side.  Block slots are consumed in batches of KB (chosen per level by the
+//   SELL slice kernels (mgq1_slices.hip; defect / SpMV, smoothing sweep): one wavefront per
+//   slice of 64/B nodes; lane = node*B + component owns one scalar row.  Levels in the node form
+//   (mgq1_node.hip) or the flow form (mgq1_flow.hip) branch off in the launch functions here.
+//   Block slots are consumed in batches of KB (chosen per level by the
 //   setup's autotuner): column indices and values of a batch are loaded first, then the x
 //   gathers, then the FMAs in slot order, as straight-line code between scheduling
 //   barriers, so a row of 9 (2D) or 27 (3D) blocks costs a few memory round trips instead
@@ -33,9 +34,9 @@
 //   Tail kernel (optional, off by default): the levels below a size threshold and the
 //   coarse solve as one single-workgroup launch with barriers between the steps.
 //
-//   Batched form (mgq1_batch.hip): the same slice bodies over the entries of many problems
-//   per launch, and segmented Krylov kernels (each block belongs to one problem's vector
-//   segment).  The shared device code is in mgq1_device.h.
+//   Batched form (mgq1_batch.hip): the same steps over the entries of many problems per launch,
+//   and segmented Krylov kernels (each block belongs to one problem's vector segment).
+//   Gram-Schmidt of the single problem: mgq1_gs.hip.  Shared device code: mgq1_device.h.
 //
 // Paper correspondence: smoother x + omega S (b - A x), transfers P and R = P^T and the
 // coarse solve (Sec. 4.1 "Geometric Multigrid CUDA", Algorithm "Geometric multigrid
@@ -47,23 +48,37 @@ namespace {
 
 // x = Ainv b or (add) x += Ainv b, one wavefront per row (Ainv row-major, FP64)
 // U row chunks of 64 elements have their loads issued together; every lane sums its
-// elements in increasing column order whatever U is, so U does not change the result
-template <class XI, class XO, int U = 8>
+// elements in increasing column order whatever U is, so U does not change the result.
+// FP32 vectors: 12 chunks at clamped columns.  A load under a condition whose result is then
+// converted waits per element (2,187 rows 13.9 us, 7.9 without; 864 rows 4.0 and 3.7); in FP64
+// nothing is converted and the condition saves the loads past the row (864 rows 3.1 us, clamped 4.0).
+template <class XI, class XO, int UMAX = 8>
 __device__ __forceinline__ void gemv_row(int n, const double* __restrict__ Ainv, const XI* __restrict__ b,
                                          XO* __restrict__ x, int i, int lane, bool add = false) {
+  constexpr bool CLAMP = sizeof(XI) == 4;
+  constexpr int U = CLAMP && UMAX > 12 ? 12 : UMAX;
   double acc = 0.0;
   const double* row = Ainv + int64_t(i) * n;
   for (int k0 = lane; k0 < n; k0 += kWave * U) {
     double av[U];
-    XI bv[U];                                // widened only when used: a conditional load
-#pragma unroll                               // converted in place would wait per element
+    XI bv[U];
+#pragma unroll
     for (int u = 0; u < U; ++u) {
       const int k = k0 + u * kWave;
-      av[u] = k < n ? row[k] : 0.0;
-      bv[u] = k < n ? b[k] : XI(0);
+      if constexpr (CLAMP) {
+        av[u] = row[min(k, n - 1)];
+        bv[u] = b[min(k, n - 1)];
+      } else {
+        av[u] = k < n ? row[k] : 0.0;
+        bv[u] = k < n ? b[k] : XI(0);
+      }
     }
+    if constexpr (CLAMP) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int u = 0; u < U; ++u) acc += av[u] * double(bv[u]);
+    for (int u = 0; u < U; ++u) {
+      const bool in = !CLAMP || k0 + u * kWave < n;
+      acc += (in ? av[u] : 0.0) * (in ? double(bv[u]) : 0.0);
+    }
   }
   acc = wave_sum(acc);
   if (lane == 0) x[i] = add ? XO(double(x[i]) + acc) : XO(acc);

@@ -493,6 +493,10 @@ CsrHost transpose(int32_t nrows, int32_t ncols, const std::vector<int32_t>& rp, 
 // owner of device allocations (freed on destruction)
 struct DevOwner {
   std::vector<void*> allocs;
+  // an arena that allocations are taken from while they fit (setup's temporary storage: an
+  // allocation and its release cost 20 to 100 us each)
+  char* arena = nullptr;
+  size_t arena_size = 0, arena_used = 0;
   DevOwner() = default;
   DevOwner(const DevOwner&) = delete;
   DevOwner& operator=(const DevOwner&) = delete;
@@ -576,6 +580,12 @@ template <class T>
 int dalloc(DevOwner* h, T** p, size_t count) {
   *p = nullptr;
   if (count == 0) count = 1;
+  const size_t bytes = (count * sizeof(T) + 255) / 256 * 256;
+  if (bytes <= h->arena_size - h->arena_used) {
+    *p = reinterpret_cast<T*>(h->arena + h->arena_used);
+    h->arena_used += bytes;
+    return MG_OK;
+  }
   void* q = nullptr;
   hipError_t e = hipMalloc(&q, count * sizeof(T));
   if (e != hipSuccess) return fail(MG_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
@@ -1826,25 +1836,25 @@ int tune_levels(mg_handle* h, hipStream_t s) {
 constexpr int64_t kDenseRows = 2048;
 
 // The matrix of the V-cycle on levels tl.back() .. 0 (A, S, mask, P, R of the levels, sliced ELL,
-// N[l] unknowns each)
-int dense_cycle(DevOwner* h, const mg_config& c, int coarse_mode, std::vector<TailLevel>& tl,
-                const std::vector<int64_t>& N, int B, const double* Ainv, int n0, double** out, hipStream_t s) {
+// N[l] unknowns each) into out; tmp holds the work vectors of up to dense_columns right-hand sides
+int dense_columns(int64_t n) { return int(std::min<int64_t>(n, 512)); }   // two workgroups per CU at a time
+
+int dense_cycle(DevOwner* tmp, const mg_config& c, int coarse_mode, std::vector<TailLevel>& tl,
+                const std::vector<int64_t>& N, int B, const double* Ainv, int n0, double* out, hipStream_t s) {
   const int top = int(tl.size()) - 1, n = int(N[size_t(top)]);
-  const int cols = std::min(n, 512);             // two workgroups per CU at a time
-  DevOwner tmp;                                  // work vectors, freed on return
+  const int cols = dense_columns(n);
   int rc;
   int64_t total = 0;
   for (int64_t v : N) total += v;
   double* work;
-  if ((rc = dalloc(&tmp, &work, size_t(total) * 4 * cols))) return rc;
+  if ((rc = dalloc(tmp, &work, size_t(total) * 4 * cols))) return rc;
   for (int l = 0; l <= top; ++l)
     for (void** v : {&tl[size_t(l)].x, &tl[size_t(l)].b, &tl[size_t(l)].r, &tl[size_t(l)].t}) {
       *v = work;
       work += size_t(N[size_t(l)]) * cols;
     }
   TailLevel* dt;
-  if ((rc = upload(&tmp, &dt, tl, s))) return rc;
-  if ((rc = dalloc(h, out, size_t(n) * n))) return rc;
+  if ((rc = upload(tmp, &dt, tl, s))) return rc;
   TailParams tp;
   tp.top = top;
   tp.nu1 = c.nu1;
@@ -1859,7 +1869,7 @@ int dense_cycle(DevOwner* h, const mg_config& c, int coarse_mode, std::vector<Ta
     const int k = std::min(cols, n - c0);
     MG_HIP(launch_unit_columns(n, c0, k, static_cast<double*>(T.b), s));
     MG_HIP(launch_tail(dt, B, VK_F64, X_F64, tp, s, k));
-    MG_HIP(launch_columns_to_rows(n, c0, k, static_cast<double*>(T.x), *out, s));
+    MG_HIP(launch_columns_to_rows(n, c0, k, static_cast<double*>(T.x), out, s));
   }
   MG_HIP(hipStreamSynchronize(s));
   return MG_OK;
@@ -1896,7 +1906,9 @@ int setup_dense(mg_handle* h, const std::vector<HostLevel>& H, hipStream_t s) {
     T.R = D->R;
     N[size_t(l)] = D->N;
   }
-  if ((rc = dense_cycle(h, c, c.coarse_mode, tl, N, h->lv[0].B, h->Ainv, h->n0, &h->dense, s))) return rc;
+  const size_t n = size_t(N[size_t(top)]);
+  if ((rc = dalloc(h, &h->dense, n * n))) return rc;
+  if ((rc = dense_cycle(&tmp, c, c.coarse_mode, tl, N, h->lv[0].B, h->Ainv, h->n0, h->dense, s))) return rc;
   h->dense_top = top;
   return MG_OK;
 }
@@ -2372,51 +2384,81 @@ int batch_defect(mg_batch* h, hipStream_t s) {
 
 // The same for every problem of a FP64 batch: its levels of up to a common number of unknowns
 // become one dense product in place of the coarse solve, which takes the launches of those
-// depths out of every step.  The rows are the most that keep all matrices within
-// kDenseBatchBytes (30 us of reading while every problem is active, against 7 launches of 5 us
-// per depth).  16 problems with 8 right-hand sides, 1.96M nodes: 42.1 -> 39.9 ms a solve.
+// depths out of every step.  The rows are the most, up to kDenseBatchRows, that keep all matrices
+// within kDenseBatchBytes (30 us of reading while every problem is active, against 7 launches of
+// 5 us per depth).  16 problems with 8 right-hand sides, 1.96M nodes: 42.1 -> 39.9 ms a solve.
+// 4 problems of up to 6 levels with 8 right-hand sides, setup and solve in ms: without 25 and 10.9,
+// 1,024 rows 26.5 and 8.2, 2,048 rows 29 and 7.1: 1,024 is the least for a batch solved once.
+constexpr int64_t kDenseBatchRows = 1024;
 constexpr int64_t kDenseBatchBytes = int64_t(128) << 20;
 
 int setup_batch_dense(mg_batch* h, const std::vector<std::vector<HostLevel>>& HH, int* flag, hipStream_t s) {
   if (h->xk != X_F64 || dense_off()) return MG_OK;
   std::vector<int> top(size_t(h->P), 0);
-  bool any = false;
-  for (int64_t rows = kDenseRows; rows >= 64 && !any; rows /= 2) {
-    int64_t bytes = 0;
+  int64_t bytes = 0;
+  for (int64_t rows = kDenseBatchRows; rows >= 64 && (bytes == 0 || bytes > kDenseBatchBytes); rows /= 2) {
+    bytes = 0;
     for (int p = 0; p < h->P; ++p) {
-      top[size_t(p)] = 0;
-      for (int l = 1; l <= h->pr[p].L && h->pr[p].lv[l].N <= rows; ++l) top[size_t(p)] = l;
-      const int64_t n = h->pr[p].lv[top[size_t(p)]].N;
-      if (top[size_t(p)] > 0) bytes += n * n * 8;
+      int& t = top[size_t(p)];
+      t = 0;
+      for (int l = 1; l <= h->pr[p].L && h->pr[p].lv[l].N <= rows; ++l) t = l;
+      const int64_t n = h->pr[p].lv[t].N;
+      if (t > 0) bytes += n * n * 8;
     }
-    any = bytes > 0 && bytes <= kDenseBatchBytes;
   }
-  if (!any) return MG_OK;
+  if (bytes == 0 || bytes > kDenseBatchBytes) return MG_OK;
+  double* out;
+  int rc;
+  if ((rc = dalloc(h, &out, size_t(bytes) / 8))) return rc;
+  // temporary storage of the largest problem, used by one after the other
+  DevOwner tmp;
+  size_t need = 0;
+  for (int p = 0; p < h->P; ++p) {
+    size_t rows = 0, blocks = 0;
+    for (int l = 0; l <= top[size_t(p)]; ++l) {
+      rows += size_t(h->pr[p].lv[l].N);
+      blocks += size_t(h->pr[p].lv[l].nnzb);
+    }
+    need = std::max(need, rows * (32 * size_t(dense_columns(h->pr[p].lv[top[size_t(p)]].N)) + 256) +
+                              blocks * size_t(h->B * h->B * 16 + 16) + (size_t(1) << 20));
+  }
+  char* arena;
+  if ((rc = dalloc(&tmp, &arena, need))) return rc;
+  tmp.arena = arena;
+  tmp.arena_size = need;
   for (int p = 0; p < h->P; ++p) {
     auto& pr = h->pr[p];
     const int t = top[size_t(p)];
     if (t == 0) continue;
-    DevOwner tmp;                                  // operators in one-right-hand-side slices
+    tmp.arena_used = 0;
     std::vector<TailLevel> tl(size_t(t) + 1);
     std::vector<int64_t> N(size_t(t) + 1);
-    int rc;
+    std::vector<HostSell> S(size_t(t) + 1);
     for (int l = 0; l <= t; ++l) {
-      const HostSell S = build_sell(HH[p][l], 1);
-      const size_t sblk = size_t(S.nslices) * h->B * S.W;
+      const LevelDev& D = pr.lv[l];
       TailLevel& T = tl[size_t(l)];
-      double* sd;
-      if ((rc = upload_sell(&tmp, S, VK_F64, T.A, s)) || (rc = dalloc(&tmp, &sd, sblk))) return rc;
-      MG_HIP(launch_fill(int64_t(sblk), sd, X_F64, 0.0, s));
-      MG_HIP(launch_block_invert(T.A, sd, X_F64, flag, 1, s));
-      T.S = sd;
-      T.mask = pr.lv[l].mask;
-      T.P = pr.lv[l].P;
-      T.R = pr.lv[l].R;
-      N[size_t(l)] = pr.lv[l].N;
+      if (h->NR == 1) {
+        T.A = D.A64;
+        T.S = D.S;
+      } else {                                     // the operator in one-right-hand-side slices
+        S[size_t(l)] = build_sell(HH[p][l], 1);
+        const size_t sblk = size_t(S[size_t(l)].nslices) * h->B * S[size_t(l)].W;
+        double* sd;
+        if ((rc = upload_sell(&tmp, S[size_t(l)], VK_F64, T.A, s)) || (rc = dalloc(&tmp, &sd, sblk))) return rc;
+        MG_HIP(launch_fill(int64_t(sblk), sd, X_F64, 0.0, s));
+        MG_HIP(launch_block_invert(T.A, sd, X_F64, flag, 1, s));
+        T.S = sd;
+      }
+      T.mask = D.mask;
+      T.P = D.P;
+      T.R = D.R;
+      N[size_t(l)] = D.N;
     }
-    if ((rc = dense_cycle(h, h->cfg, MG_COARSE_EXACT, tl, N, h->B, pr.Ainv, pr.n0, &pr.Ainv, s))) return rc;
+    if ((rc = dense_cycle(&tmp, h->cfg, MG_COARSE_EXACT, tl, N, h->B, pr.Ainv, pr.n0, out, s))) return rc;
+    pr.Ainv = out;
     pr.n0 = int(N[size_t(t)]);
     pr.base = t;
+    out += size_t(pr.n0) * pr.n0;
   }
   h->dense = true;
   return MG_OK;

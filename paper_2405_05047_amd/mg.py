@@ -268,7 +268,7 @@ class Hierarchy:
         return pc.value, rc.value, wb.value
 
     def dictionary_blocks(self, l):
-        """Distinct blocks of level l's operator in the dictionary form (0: plain values)."""
+        """Distinct blocks of level l's operator where its rows are stored once (0: other forms)."""
         n = C.c_int32()
         _check(lib().mg_level_dictionary(self.h, l, C.byref(n)))
         return n.value
@@ -298,7 +298,7 @@ class Hierarchy:
     def export(self, l):
         """Stored cycle operator of level l in BSR order: (values (nnzb, b, b) of the storage
         dtype: float64, float32 or uint16 codes; row exponents (n * b,) int8 or None).  A
-        block-dictionary handle keeps no per-block values: the library refuses it (MGError)."""
+        dictionary handle keeps no per-block values: the library refuses it (MGError)."""
         n, b, nnzb = self.sizes[l]
         prec = self.cfg.precision
         dt = {0: np.float64, 1: np.float32, 2: np.uint16, 3: np.uint16, 4: np.float64}[prec]
