@@ -1633,7 +1633,7 @@ int setup_level(DevOwner* h, const HostLevel& L, bool has_p, int NR, int vkind, 
     if ((rc = setup_node(h, L, vkind, xk, must, flag, s, D, &node))) return rc;
     pt.mark("  node form");
   }
-  if (single && NR == 1 && !node && !dict && L.B == 4 && ff != 0 &&
+  if (single && NR == 1 && !node && L.B == 4 && ff != 0 &&
       (ff == 1 ? int64_t(L.n) * 4 > tail_dofs
                : L.n > kRelaySlices * (kWave / 4) && want_node(L, tail_dofs, &must))) {
     if ((rc = setup_flow(h, L, vkind, xk, flag, s, D, &node))) return rc;

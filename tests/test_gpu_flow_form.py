@@ -64,9 +64,9 @@ def test_flow_form_one_other_block(entry, value, monkeypatch):
     _two(levels[:-1] + [dataclasses.replace(lv, val=val)], wl, "fp64", W.SMOOTH_JACOBI, monkeypatch)
 
 
-@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp64dict"])
 def test_flow_form_by_size(prec, monkeypatch):
-    """35,937 nodes take the form by themselves; columns span less than 2^16."""
+    """35,937 nodes take the form by themselves (their blocks are too many for a dictionary)."""
     from paper_2405_05047_amd import gen
     wl = W.c4_oseen(4)
     levels = gen.build(wl).levels
