@@ -1611,6 +1611,42 @@ struct PhaseTimer {
   }
 };
 
+// The smoother blocks of level L, stored as S (A64 on the device), in the lane layout of the
+// sweeps: lane r * B + c of a slice holds row c of its node's block, column cc at
+// out[(slice * B + cc) * W + r * B + c].  The caller's fixed smoother matrix S (Sec. 4.1) where
+// the level has one, else the inverses of the diagonal blocks (*flag = 1 if one is singular).
+int upload_smoother(DevOwner* h, const HostLevel& L, const HostSell& S, const SellDev& A64, int xk, int* flag,
+                    hipStream_t s, void** out) {
+  const size_t sblk = size_t(S.nslices) * L.B * S.W;
+  char* p;
+  int rc;
+  if ((rc = dalloc(h, &p, sblk * xsize(xk)))) return rc;
+  *out = p;
+  if (L.sblk.empty()) {
+    MG_HIP(launch_fill(int64_t(sblk), p, xk, 0.0, s));
+    MG_HIP(launch_block_invert(A64, p, xk, flag, kWave / S.W, s));
+    return MG_OK;
+  }
+  std::vector<double> lane(sblk, 0.0);
+  const int B = L.B;
+  for (int64_t pos = 0; pos < L.n; ++pos) {
+    const int64_t node = S.perm.empty() ? pos : S.perm[size_t(pos)];
+    const int64_t slice = pos / S.R, r = pos % S.R;
+    for (int c = 0; c < B; ++c)
+      for (int cc = 0; cc < B; ++cc)
+        lane[size_t((slice * B + cc) * S.W + r * B + c)] = L.sblk[size_t(node * B * B + c * B + cc)];
+  }
+  if (xk == X_F64) {
+    MG_HIP(hipMemcpyAsync(p, lane.data(), sblk * sizeof(double), hipMemcpyHostToDevice, s));
+    MG_HIP(hipStreamSynchronize(s));
+  } else {
+    std::vector<float> lf(lane.begin(), lane.end());
+    MG_HIP(hipMemcpyAsync(p, lf.data(), sblk * sizeof(float), hipMemcpyHostToDevice, s));
+    MG_HIP(hipStreamSynchronize(s));
+  }
+  return MG_OK;
+}
+
 // one level on the device: FP64 and cycle operators (sliced ELL for NR right-hand sides),
 // smoother blocks, mask, P~ and R = P~^T; with vectors = true also x, b, r, t
 // single: a single-problem handle (keeps the host pattern for the step-wise entry points
@@ -1647,33 +1683,7 @@ int setup_level(DevOwner* h, const HostLevel& L, bool has_p, int NR, int vkind, 
   if (vkind == VK_F64) D.Ac = D.A64;
   else if ((rc = upload_sell(h, S, vkind, D.Ac, s))) return rc;
   pt.mark("  cycle operator");
-  const size_t sblk = size_t(S.nslices) * L.B * S.W;
-  if ((rc = dalloc(h, reinterpret_cast<char**>(&D.S), sblk * xsize(xk)))) return rc;
-  if (L.sblk.empty()) {
-    MG_HIP(launch_fill(int64_t(sblk), D.S, xk, 0.0, s));
-    MG_HIP(launch_block_invert(D.A64, D.S, xk, flag, row_lanes(NR), s));
-  } else {
-    // the caller's fixed smoother matrix S (Sec. 4.1) in the lane layout of the sweeps:
-    // lane r * B + c of a slice holds row c of its node's block, column cc at
-    // S[(slice * B + cc) * W + r * B + c]
-    std::vector<double> lane(sblk, 0.0);
-    const int B = L.B;
-    for (int64_t pos = 0; pos < L.n; ++pos) {
-      const int64_t node = S.perm.empty() ? pos : S.perm[size_t(pos)];
-      const int64_t slice = pos / S.R, r = pos % S.R;
-      for (int c = 0; c < B; ++c)
-        for (int cc = 0; cc < B; ++cc)
-          lane[size_t((slice * B + cc) * S.W + r * B + c)] = L.sblk[size_t(node * B * B + c * B + cc)];
-    }
-    if (xk == X_F64) {
-      MG_HIP(hipMemcpyAsync(D.S, lane.data(), sblk * sizeof(double), hipMemcpyHostToDevice, s));
-      MG_HIP(hipStreamSynchronize(s));
-    } else {
-      std::vector<float> lf(lane.begin(), lane.end());
-      MG_HIP(hipMemcpyAsync(D.S, lf.data(), sblk * sizeof(float), hipMemcpyHostToDevice, s));
-      MG_HIP(hipStreamSynchronize(s));
-    }
-  }
+  if ((rc = upload_smoother(h, L, S, D.A64, xk, flag, s, &D.S))) return rc;
   if (keep_host) {
     D.hsptr = S.sptr;
     D.hperm = S.perm;
@@ -2442,11 +2452,10 @@ int setup_batch_dense(mg_batch* h, const std::vector<std::vector<HostLevel>>& HH
         T.S = D.S;
       } else {                                     // the operator in one-right-hand-side slices
         S[size_t(l)] = build_sell(HH[p][l], 1);
-        const size_t sblk = size_t(S[size_t(l)].nslices) * h->B * S[size_t(l)].W;
-        double* sd;
-        if ((rc = upload_sell(&tmp, S[size_t(l)], VK_F64, T.A, s)) || (rc = dalloc(&tmp, &sd, sblk))) return rc;
-        MG_HIP(launch_fill(int64_t(sblk), sd, X_F64, 0.0, s));
-        MG_HIP(launch_block_invert(T.A, sd, X_F64, flag, 1, s));
+        void* sd;
+        if ((rc = upload_sell(&tmp, S[size_t(l)], VK_F64, T.A, s)) ||
+            (rc = upload_smoother(&tmp, HH[p][l], S[size_t(l)], T.A, X_F64, flag, s, &sd)))
+          return rc;
         T.S = sd;
       }
       T.mask = D.mask;
