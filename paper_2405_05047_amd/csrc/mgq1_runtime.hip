@@ -1675,20 +1675,21 @@ int setup_level(DevOwner* h, const HostLevel& L, bool has_p, int NR, int vkind, 
     if ((rc = setup_flow(h, L, vkind, xk, flag, s, D, &node))) return rc;
     pt.mark("  flow form");
   }
+  HostSell S;                       // read by copies until the stream is waited for at the end
   if (!node) {
-  HostSell S = build_sell(L, row_lanes(NR));
-  pt.mark("  sliced layout");
-  if ((rc = upload_sell(h, S, VK_F64, D.A64, s))) return rc;
-  pt.mark("  FP64 operator upload");
-  if (vkind == VK_F64) D.Ac = D.A64;
-  else if ((rc = upload_sell(h, S, vkind, D.Ac, s))) return rc;
-  pt.mark("  cycle operator");
-  if ((rc = upload_smoother(h, L, S, D.A64, xk, flag, s, &D.S))) return rc;
-  if (keep_host) {
-    D.hsptr = S.sptr;
-    D.hperm = S.perm;
-  }
-  pt.mark("  smoother blocks");
+    S = build_sell(L, row_lanes(NR));
+    pt.mark("  sliced layout");
+    if ((rc = upload_sell(h, S, VK_F64, D.A64, s))) return rc;
+    pt.mark("  FP64 operator upload");
+    if (vkind == VK_F64) D.Ac = D.A64;
+    else if ((rc = upload_sell(h, S, vkind, D.Ac, s))) return rc;
+    pt.mark("  cycle operator");
+    if ((rc = upload_smoother(h, L, S, D.A64, xk, flag, s, &D.S))) return rc;
+    if (keep_host) {
+      D.hsptr = S.sptr;
+      D.hperm = S.perm;
+    }
+    pt.mark("  smoother blocks");
   }
   if (keep_host) D.hrow = L.rowptr;
   if ((rc = upload(h, &D.mask, L.mask, s))) return rc;
