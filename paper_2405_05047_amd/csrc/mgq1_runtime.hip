@@ -727,8 +727,7 @@ int upload_sell(DevOwner* h, const HostSell& S, int kind, SellDev& D, hipStream_
 // the same).
 constexpr int64_t kNodeFormBytes = int64_t(16) << 20;
 
-bool want_node(const HostLevel& L, int64_t tail_dofs, bool* must) {
-  if (int64_t(L.n) * L.B <= tail_dofs) return false;       // the single-workgroup tail reads sliced ELL
+bool want_node(const HostLevel& L, bool* must) {
   if (const char* e = std::getenv("MGQ1_NODE_FORM")) {
     *must = std::atoi(e) != 0;
     return *must;
@@ -1651,10 +1650,11 @@ int upload_smoother(DevOwner* h, const HostLevel& L, const HostSell& S, const Se
 // smoother blocks, mask, P~ and R = P~^T; with vectors = true also x, b, r, t
 // single: a single-problem handle (keeps the host pattern for the step-wise entry points
 // and stores its transfers in the node form where they qualify); the batch reads the
-// per-DoF form
+// per-DoF form.  sliced: the level keeps the sliced layout whatever its size (the
+// single-workgroup tail reads that alone)
 int setup_level(DevOwner* h, const HostLevel& L, bool has_p, int NR, int vkind, int xk, bool vectors, int* flag,
                 hipStream_t s, LevelDev& D, bool single = false, const HostLevel* coarser = nullptr,
-                bool dict = false, int64_t tail_dofs = 0) {
+                bool dict = false, bool sliced = false) {
   const bool keep_host = single;
   int rc;
   D.n = L.n;
@@ -1665,13 +1665,12 @@ int setup_level(DevOwner* h, const HostLevel& L, bool has_p, int NR, int vkind, 
   bool node = false;
   bool must = dict;
   const int ff = flow_switch();
-  if (single && NR == 1 && ff != 1 && (dict || want_node(L, tail_dofs, &must))) {
+  if (single && !sliced && ff != 1 && (dict || want_node(L, &must))) {
     if ((rc = setup_node(h, L, vkind, xk, must, flag, s, D, &node))) return rc;
     pt.mark("  node form");
   }
-  if (single && NR == 1 && !node && L.B == 4 && ff != 0 &&
-      (ff == 1 ? int64_t(L.n) * 4 > tail_dofs
-               : L.n > kRelaySlices * (kWave / 4) && want_node(L, tail_dofs, &must))) {
+  if (single && !sliced && !node && L.B == 4 && ff != 0 &&
+      (ff == 1 || (L.n > kRelaySlices * (kWave / 4) && want_node(L, &must)))) {
     if ((rc = setup_flow(h, L, vkind, xk, flag, s, D, &node))) return rc;
     pt.mark("  flow form");
   }
@@ -1936,9 +1935,15 @@ int setup_handle(mg_handle* h, const std::vector<HostLevel>& H, hipStream_t s) {
   const int vkind = value_kind(c.precision);
   int64_t tail_dofs = 0;
   if (const char* e = std::getenv("MGQ1_TAIL_DOFS")) tail_dofs = std::atoll(e);
+  // tail: every level up to the largest one with at most tail_dofs unknowns (a level below
+  // it may have more).  Default off: on MI355X one workgroup walking several levels was
+  // measured slower (dependent-load latency serialises) than separate grid launches per step.
+  int top = 0;
+  for (int l = 1; l <= h->L; ++l)
+    if (int64_t(H[l].n) * H[l].B <= tail_dofs) top = l;
   for (int l = 0; l < n_levels; ++l) {
     if ((rc = setup_level(h, H[l], l > 0, 1, vkind, h->xk, true, flag, s, h->lv[l], true,
-                          l > 0 ? &H[l - 1] : nullptr, c.precision == MG_PREC_FP64_DICT, tail_dofs)))
+                          l > 0 ? &H[l - 1] : nullptr, c.precision == MG_PREC_FP64_DICT, top >= 1 && l <= top)))
       return rc;
     if (pt.on) MG_HIP(hipStreamSynchronize(s));
     pt.mark("level", l);
@@ -1982,12 +1987,6 @@ int setup_handle(mg_handle* h, const std::vector<HostLevel>& H, hipStream_t s) {
   pt.mark("Chebyshev bounds and slot-batch timing");
   if (const char* e = std::getenv("MGQ1_NO_FUSE")) h->fuse2z = std::atoi(e) == 0;
   if (c.smoother == MG_SMOOTH_CHEBYSHEV) h->fuse2z = false;   // the fused pair is two Jacobi sweeps
-  // tail: every level up to the largest one with at most tail_dofs unknowns.  Default off:
-  // on MI355X one workgroup walking several levels was measured slower (dependent-load
-  // latency serialises) than separate grid launches per step.
-  int top = 0;
-  for (int l = 1; l <= h->L; ++l)
-    if (h->lv[l].N <= tail_dofs) top = l;
   if (top >= 1 && c.precision == MG_PREC_FP64_DICT)
     return fail(MG_EUNSUPPORTED, "the single-workgroup tail reads plain values");
   if (top >= 1 && c.smoother == MG_SMOOTH_CHEBYSHEV)
