@@ -90,7 +90,7 @@ def node_sweep_bytes(n, b):
 
 
 def dict_sweep_bytes(n, b, nnzb, col_bytes, ndict):
-    """The same where no rows repeat, every block looked up: a 16-bit block index and the
+    """The same where the blocks are stored once but not the rows: a 16-bit block number and the
     column index per stored block, the distinct blocks once, vectors and smoother blocks as
     in sweep_bytes."""
     return nnzb * (2 + col_bytes) + ndict * b * b * 8 + 4 * (n + 1) + 3 * n * b * 8 + n * b * b * 8
@@ -538,7 +538,10 @@ def main():
             results[prec]["dictionary_blocks_per_level"] = [h.dictionary_blocks(l) for l in range(h.n_levels)]
             if ndict:
                 ksec = kernel_time(torch, h, Ld, nd * bsd)
-                kbytes = node_sweep_bytes(nd, bsd)
+                # whole rows stored once where the plain handle does so too, else numbered blocks
+                plain = handles.get("fp64")
+                rows = plain is None or plain.dictionary_blocks(Ld) > 0
+                kbytes = node_sweep_bytes(nd, bsd) if rows else dict_sweep_bytes(nd, bsd, nnzbd, h.col_bytes(Ld), ndict)
                 results[prec]["finest_sweep"] = {"us_per_launch": round(ksec * 1e6, 2), "bytes_per_launch": kbytes,
                                                  "achieved_gbs": round(kbytes / ksec / 1e9, 1)}
         if sm == "cheb":

@@ -53,9 +53,11 @@ enum { MG_SMOOTH_JACOBI = 0, MG_SMOOTH_CHEBYSHEV = 1 };
  * Every precision stores a level's distinct blocks once (lossless: the same bits in every
  * step, V-cycle and solve) where the level's FP64 blocks fill 16 MiB and more, at most 65,535 of
  * them are distinct and most rows repeat whole rows (single-problem handles).
- * MG_PREC_FP64_DICT: FP64 throughout with that form on every level of at most 65,535
- * distinct blocks, whatever its size and repetition; every result is bitwise that of
- * MG_PREC_FP64 (single-problem handles only). */
+ * MG_PREC_FP64_DICT: FP64 throughout with the distinct blocks stored once on every level
+ * of at most 65,535 of them, whatever its size and repetition (a 16-bit number per stored
+ * block where rows do not repeat; not on levels that keep half of their blocks' values,
+ * as the flow step's); every result, norms included, is bitwise that of MG_PREC_FP64
+ * (single-problem handles only). */
 enum { MG_PREC_FP64 = 0, MG_PREC_FP32 = 1, MG_PREC_FP32_F16VAL = 2, MG_PREC_FP32_BF16VAL = 3,
        MG_PREC_FP64_DICT = 4 };
 
@@ -240,9 +242,9 @@ int mg_level_tuning(const mg_handle* h, int32_t level, int32_t* slot_batch, int3
 int mg_level_transfer_format(const mg_handle* h, int32_t level, int32_t* p_col_bytes, int32_t* r_col_bytes,
                              int32_t* weight_bytes);
 
-/* Distinct blocks of level `level`'s operator where they are stored once (the zero block of
- * the padding included; 16-bit values: blocks distinct with their row exponents), or 0 when
- * its values are stored plainly. */
+/* Distinct blocks of level `level`'s operator where they are stored once, with their rows or
+ * by number (the zero block of the padding included; 16-bit values: blocks distinct with
+ * their row exponents), or 0 when its values are stored plainly. */
 int mg_level_dictionary(const mg_handle* h, int32_t level, int32_t* n_blocks);
 
 /* Host-only structural validation of one level (and its coarser neighbour for P~);

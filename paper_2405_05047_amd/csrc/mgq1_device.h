@@ -63,6 +63,11 @@ template <> struct Val<VK_F16> {
   }
   __device__ __forceinline__ static float dec(raw u) { return __half2float(__ushort_as_half(u)); }
 };
+// FP64 blocks from the level's dictionary (loaded in sell_batch, not through load())
+template <> struct Val<VK_DICT> {
+  using raw = double;
+  __device__ __forceinline__ static double dec(raw u) { return u; }
+};
 template <> struct Val<VK_BF16> {
   using raw = unsigned short;
   template <bool NT>
@@ -116,13 +121,36 @@ __device__ __forceinline__ void sell_batch(const SellDev& A, int k, int r, int n
   XI xv[NB][B];
 #pragma unroll
   for (int qq = 0; qq < NB; ++qq) js[qq] = slot_col<C16, NT>(A, k + qq, int64_t(k + qq) * R + r);
+  if constexpr (K == VK_DICT) {
+    // column and block numbers first, then the block's row from the (cached) dictionary together
+    // with the x gathers
+    static_assert(NR == 1, "the dictionary form has one right-hand side");
+    unsigned short di[NB];
 #pragma unroll
-  for (int qq = 0; qq < NB; ++qq) {
-    const int64_t vb = int64_t(k + qq) * B * W + rl;
+    for (int qq = 0; qq < NB; ++qq) di[qq] = stream_load<NT>(A.didx + int64_t(k + qq) * R + r);
+    __builtin_amdgcn_sched_barrier(0);
+    const int c = rl % B;
+    if (A.dlds) {
+      extern __shared__ double dict_lds[];
 #pragma unroll
-    for (int cc = 0; cc < B; ++cc) av[qq][cc] = Val<K>::template load<NT>(A.val, vb + cc * W);
+      for (int qq = 0; qq < NB; ++qq)
+#pragma unroll
+        for (int cc = 0; cc < B; ++cc) av[qq][cc] = dict_lds[(int(di[qq]) * B + c) * B + cc];
+    } else {
+#pragma unroll
+      for (int qq = 0; qq < NB; ++qq)
+#pragma unroll
+        for (int cc = 0; cc < B; ++cc) av[qq][cc] = A.dtab[(int64_t(di[qq]) * B + c) * B + cc];
+    }
+  } else {
+#pragma unroll
+    for (int qq = 0; qq < NB; ++qq) {
+      const int64_t vb = int64_t(k + qq) * B * W + rl;
+#pragma unroll
+      for (int cc = 0; cc < B; ++cc) av[qq][cc] = Val<K>::template load<NT>(A.val, vb + cc * W);
+    }
+    __builtin_amdgcn_sched_barrier(0);
   }
-  __builtin_amdgcn_sched_barrier(0);
   if constexpr (B > 1 && NR == 1) {
     // each lane gathers only its own component of the neighbour node (the B lanes of a
     // node read one contiguous B-vector together) and takes the others from its node's
@@ -151,6 +179,26 @@ __device__ __forceinline__ void sell_batch(const SellDev& A, int k, int r, int n
     for (int cc = 0; cc < B; ++cc) acc += T(Val<K>::dec(av[qq][cc])) * T(xv[qq][cc]);
 }
 
+// dictionary form with dlds set: the workgroup copies the dictionary into LDS before any
+// slice work (all threads reach the barrier); launched with ndict * B * B doubles of
+// dynamic shared memory
+template <int K>
+__device__ __forceinline__ void dict_stage(const SellDev& A) {
+  if constexpr (K == VK_DICT) {
+    if (A.dlds) {
+      extern __shared__ double dict_lds[];
+      const int n = A.ndict * A.B * A.B;
+      for (int i = int(threadIdx.x); i < n; i += int(blockDim.x)) dict_lds[i] = A.dtab[i];
+      __syncthreads();
+    }
+  }
+}
+
+template <int K>
+inline size_t dict_lds_bytes(const SellDev& A) {
+  return (K == VK_DICT && A.dlds) ? size_t(A.ndict) * A.B * A.B * sizeof(double) : 0;
+}
+
 // The same batch for the second of two sweeps from x = 0 with b = 1: the iterate after the
 // first sweep, x1_j = omega * (S_j * b_j), is formed on the fly from S and b instead of being
 // read (S of node j sits at S[j] for one component and one right-hand side), with the
@@ -164,9 +212,24 @@ __device__ __forceinline__ void sell_batch_z(const SellDev& A, int k, int rl, in
   X sv[NB], bv[NB];
 #pragma unroll
   for (int qq = 0; qq < NB; ++qq) js[qq] = slot_col<C16, NT>(A, k + qq, int64_t(k + qq) * kWave + rl);
+  if constexpr (K == VK_DICT) {
+    unsigned short di[NB];
 #pragma unroll
-  for (int qq = 0; qq < NB; ++qq) av[qq] = Val<K>::template load<NT>(A.val, int64_t(k + qq) * kWave + rl);
-  __builtin_amdgcn_sched_barrier(0);
+    for (int qq = 0; qq < NB; ++qq) di[qq] = stream_load<NT>(A.didx + int64_t(k + qq) * kWave + rl);
+    __builtin_amdgcn_sched_barrier(0);
+    if (A.dlds) {
+      extern __shared__ double dict_lds[];
+#pragma unroll
+      for (int qq = 0; qq < NB; ++qq) av[qq] = dict_lds[di[qq]];
+    } else {
+#pragma unroll
+      for (int qq = 0; qq < NB; ++qq) av[qq] = A.dtab[di[qq]];
+    }
+  } else {
+#pragma unroll
+    for (int qq = 0; qq < NB; ++qq) av[qq] = Val<K>::template load<NT>(A.val, int64_t(k + qq) * kWave + rl);
+    __builtin_amdgcn_sched_barrier(0);
+  }
 #pragma unroll
   for (int qq = 0; qq < NB; ++qq) {
     sv[qq] = S[js[qq]];

@@ -720,11 +720,75 @@ int upload_sell(DevOwner* h, const HostSell& S, int kind, SellDev& D, hipStream_
   return MG_OK;
 }
 
-// Which levels take the node form (besides all that can on a MG_PREC_FP64_DICT handle): those
-// whose FP64 blocks would fill kNodeFormBytes and more.  Smaller levels wait for memory
-// latency, not bytes, and the node form's descriptor is one more dependent load in their
-// chain.  MGQ1_NODE_FORM=1 / =0: every level that can / none (tests; the V-cycle's bits are
-// the same).
+// Dictionary form of a level's FP64 blocks (MG_PREC_FP64_DICT, levels in the sliced layout): the
+// distinct B x B blocks of the layout once (padding blocks are zero blocks), a 16-bit number per
+// slot and node row.  Applied when the level has at most 65,535 distinct blocks (compared
+// bitwise); the kernels then read the same doubles, so every result has the same bits.
+int upload_dict(DevOwner* h, const HostSell& S, SellDev& D, hipStream_t s, bool* applied) {
+  using nodebuild::BlockSet;
+  *applied = false;
+  const int B = S.B, BB = B * B, W = S.W, R = S.R;
+  const int64_t nblk = S.slots * R, nchunk = 64, per = (nblk + nchunk - 1) / nchunk;
+  std::vector<BlockSet> sets(static_cast<size_t>(nchunk), BlockSet(BB));
+  std::vector<int> bad(size_t(nchunk), 0);
+  std::vector<uint16_t> idx(static_cast<size_t>(nblk));
+  parallel_for(nchunk, 1, [&](int64_t c0, int64_t c1) {
+    for (int64_t c = c0; c < c1; ++c) {
+      try {
+        double blk[16];
+        uint64_t key[16];
+        for (int64_t e = c * per; e < std::min(nblk, (c + 1) * per); ++e) {
+          const int64_t k = e / R, r = e % R;
+          for (int z = 0; z < BB; ++z) blk[z] = S.val[size_t((k * B + z % B) * W + r * B + z / B)];
+          std::memcpy(key, blk, size_t(BB) * 8);
+          const int32_t g = sets[size_t(c)].find_or_add(key);
+          if (g >= nodebuild::kMaxBlocks) { bad[size_t(c)] = 1; break; }
+          idx[size_t(e)] = uint16_t(g);
+        }
+      } catch (...) {
+        bad[size_t(c)] = 2;
+      }
+    }
+  });
+  for (int b : bad)
+    if (b == 2) throw std::bad_alloc();
+  for (int b : bad)
+    if (b) return MG_OK;                           // too many distinct blocks: plain values
+  BlockSet all(BB);
+  std::vector<std::vector<uint16_t>> number(static_cast<size_t>(nchunk));
+  for (size_t c = 0; c < sets.size(); ++c) {
+    number[c].resize(size_t(sets[c].size()));
+    for (int32_t e = 0; e < sets[c].size(); ++e) {
+      const int32_t g = all.find_or_add(&sets[c].keys[size_t(e) * BB]);
+      if (g >= nodebuild::kMaxBlocks) return MG_OK;
+      number[c][size_t(e)] = uint16_t(g);
+    }
+  }
+  parallel_for(nchunk, 1, [&](int64_t c0, int64_t c1) {
+    for (int64_t c = c0; c < c1; ++c)
+      for (int64_t e = c * per; e < std::min(nblk, (c + 1) * per); ++e) idx[size_t(e)] = number[size_t(c)][idx[size_t(e)]];
+  });
+  std::vector<double> tab(all.keys.size());
+  std::memcpy(tab.data(), all.keys.data(), tab.size() * 8);
+  int rc;
+  uint16_t* di;
+  double* dt;
+  if ((rc = upload(h, &di, idx, s)) || (rc = upload(h, &dt, tab, s))) return rc;
+  MG_HIP(hipStreamSynchronize(s));
+  D.kind = VK_DICT;
+  D.didx = di;
+  D.dtab = dt;
+  D.ndict = all.size();
+  D.dlds = tab.size() * sizeof(double) <= 16384 ? 1 : 0;     // small tables: one LDS copy per workgroup
+  D.nt = stream_nt(int64_t(S.col.size()) * (D.col16 ? 2 : 4) + nblk * 2);
+  *applied = true;
+  return MG_OK;
+}
+
+// Which levels take the node form: those whose FP64 blocks would fill kNodeFormBytes and more.
+// Smaller levels wait for memory latency, not bytes, and the node form's descriptor is one
+// more dependent load in their chain.  MGQ1_NODE_FORM=1 / =0: every level that can / none
+// (tests; the V-cycle's bits are the same).
 constexpr int64_t kNodeFormBytes = int64_t(16) << 20;
 
 bool want_node(const HostLevel& L, bool* must) {
@@ -736,8 +800,7 @@ bool want_node(const HostLevel& L, bool* must) {
 }
 
 // The node form of level L (NodeDev): D.A64 and D.Ac with their smoother blocks.  *applied
-// tells whether the operator qualified; must: a MG_PREC_FP64_DICT handle, which takes it with
-// any share of general slices.
+// tells whether the operator qualified; must: with any share of general slices.
 int setup_node(DevOwner* h, const HostLevel& L, int vkind, int xk, bool must, int* flag, hipStream_t s, LevelDev& D,
                bool* applied) {
   *applied = false;
@@ -1651,10 +1714,11 @@ int upload_smoother(DevOwner* h, const HostLevel& L, const HostSell& S, const Se
 // single: a single-problem handle (keeps the host pattern for the step-wise entry points
 // and stores its transfers in the node form where they qualify); the batch reads the
 // per-DoF form.  sliced: the level keeps the sliced layout whatever its size (the
-// single-workgroup tail reads that alone)
+// single-workgroup tail reads that alone).  dict: a level in the sliced layout keeps its
+// distinct blocks once; any_size: the node form needs no size and no share of repeating rows
 int setup_level(DevOwner* h, const HostLevel& L, bool has_p, int NR, int vkind, int xk, bool vectors, int* flag,
                 hipStream_t s, LevelDev& D, bool single = false, const HostLevel* coarser = nullptr,
-                bool dict = false, bool sliced = false) {
+                bool dict = false, bool sliced = false, bool any_size = false) {
   const bool keep_host = single;
   int rc;
   D.n = L.n;
@@ -1662,10 +1726,9 @@ int setup_level(DevOwner* h, const HostLevel& L, bool has_p, int NR, int vkind, 
   D.N = int64_t(L.n) * L.B;
   D.nnzb = L.nnzb;
   PhaseTimer pt;
-  bool node = false;
-  bool must = dict;
+  bool node = false, must = any_size;
   const int ff = flow_switch();
-  if (single && !sliced && ff != 1 && (dict || want_node(L, &must))) {
+  if (single && !sliced && ff != 1 && (want_node(L, &must) || any_size)) {
     if ((rc = setup_node(h, L, vkind, xk, must, flag, s, D, &node))) return rc;
     pt.mark("  node form");
   }
@@ -1689,6 +1752,14 @@ int setup_level(DevOwner* h, const HostLevel& L, bool has_p, int NR, int vkind, 
       D.hperm = S.perm;
     }
     pt.mark("  smoother blocks");
+    if (dict) {
+      // the smoother blocks above came from the plain FP64 values; from here on the level's
+      // kernels read the dictionary form of the same values
+      bool ok = false;
+      if ((rc = upload_dict(h, S, D.A64, s, &ok))) return rc;
+      if (ok) D.Ac = D.A64;
+      pt.mark("  block dictionary");
+    }
   }
   if (keep_host) D.hrow = L.rowptr;
   if ((rc = upload(h, &D.mask, L.mask, s))) return rc;
@@ -1902,9 +1973,9 @@ int setup_dense(mg_handle* h, const std::vector<HostLevel>& H, hipStream_t s) {
   std::vector<int64_t> N(size_t(top) + 1);
   int rc;
   for (int l = 0; l <= top; ++l) {
-    // the workgroup's cycle reads sliced ELL: a level in the node form gets a copy in it
+    // the workgroup's cycle reads plain sliced ELL: a level in another form gets a copy in it
     LevelDev* D = &h->lv[l];
-    if (D->Ac.node || D->Ac.flow) {
+    if (D->Ac.node || D->Ac.flow || D->Ac.kind == VK_DICT) {
       D = &copy[size_t(l)];
       if ((rc = setup_level(&tmp, H[size_t(l)], l > 0, 1, VK_F64, X_F64, false, h->dflag, s, *D))) return rc;
     }
@@ -1942,8 +2013,14 @@ int setup_handle(mg_handle* h, const std::vector<HostLevel>& H, hipStream_t s) {
   for (int l = 1; l <= h->L; ++l)
     if (int64_t(H[l].n) * H[l].B <= tail_dofs) top = l;
   for (int l = 0; l < n_levels; ++l) {
+    // dictionary handles: the sliced dictionary where the size rule declines the node form (10
+    // cycles of the 4,913-node flow step 1.21 ms, 3.17 in the node form; of the 43,861-node
+    // face-refined elasticity 2.44 and 2.92), but the node form on the inner levels of one
+    // component, where it is the faster one (263,169-node uniform mesh, 1.26 and 1.34 ms).  The finest level follows the rule of the plain handles, so
+    // that the reported norms, summed in the order of its slices, have the same bits.
+    const bool dict = c.precision == MG_PREC_FP64_DICT;
     if ((rc = setup_level(h, H[l], l > 0, 1, vkind, h->xk, true, flag, s, h->lv[l], true,
-                          l > 0 ? &H[l - 1] : nullptr, c.precision == MG_PREC_FP64_DICT, top >= 1 && l <= top)))
+                          l > 0 ? &H[l - 1] : nullptr, dict, top >= 1 && l <= top, dict && H[l].B == 1 && l < h->L)))
       return rc;
     if (pt.on) MG_HIP(hipStreamSynchronize(s));
     pt.mark("level", l);
@@ -3420,7 +3497,7 @@ int mg_level_export(const mg_handle* h, int32_t level, void* values, int8_t* row
   const LevelDev& L = h->lv[level];
   const SellDev& A = L.Ac;
   if (L.hrow.empty()) return fail(MG_EUNSUPPORTED, "no host geometry kept for this level");
-  if (A.node && h->cfg.precision == MG_PREC_FP64_DICT)
+  if (A.kind == VK_DICT || (A.node && h->cfg.precision == MG_PREC_FP64_DICT))
     return fail(MG_EUNSUPPORTED, "the level's values are stored as a block dictionary");
   if ((A.kind == VK_F16 || A.kind == VK_BF16) && !row_exp) return fail(MG_EINVAL, "row_exp is required for 16-bit values");
   const int B = L.B, W = kWave, R = A.R;
@@ -3527,7 +3604,7 @@ int mg_level_transfer_format(const mg_handle* h, int32_t level, int32_t* p_col_b
 int mg_level_dictionary(const mg_handle* h, int32_t level, int32_t* n_blocks) {
   if (!h || !n_blocks || level < 0 || level > h->L) return fail(MG_EINVAL, "bad handle, level or output");
   const LevelDev& D = h->lv[level];
-  *n_blocks = D.nh ? D.nh->nblocks() : 0;
+  *n_blocks = D.nh ? D.nh->nblocks() : D.A64.kind == VK_DICT ? D.A64.ndict : 0;
   return MG_OK;
 }
 

@@ -12,6 +12,7 @@ template <int B, int K, class XI, class XO, class T, int MODE, bool NORM, int KB
 __global__ __launch_bounds__(kThreads) void k_spmv(SellDev A, const XO* __restrict__ b, const XI* __restrict__ x,
                                                    XO* __restrict__ y, const uint8_t* __restrict__ mask,
                                                    double* __restrict__ partials) {
+  dict_stage<K>(A);
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
   const SliceLane s = slice_lane<B, 1>(A, bid * kSliceWaves + threadIdx.x / kWave, threadIdx.x % kWave);
   const T out = spmv_slice<B, 1, K, XI, XO, T, MODE, KB, C16>(A, b, x, y, mask, s);
@@ -26,6 +27,7 @@ template <int B, int K, class X, class T, int KB, bool C16>
 __global__ __launch_bounds__(kThreads) void k_sweep(SellDev A, const X* __restrict__ S, const X* __restrict__ b,
                                                     const X* __restrict__ x, X* __restrict__ xo, T omega,
                                                     T beta, int pmode) {
+  dict_stage<K>(A);
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
   const SliceLane s = slice_lane<B, 1>(A, bid * kSliceWaves + threadIdx.x / kWave, threadIdx.x % kWave);
   sweep_slice<B, 1, K, X, T, KB, C16>(A, S, b, x, xo, omega, s, beta, pmode);
@@ -167,6 +169,7 @@ __global__ __launch_bounds__(kThreads) void k_sweep_relay(SellDev A, const X* __
 template <int K, class X, class T, int KB, bool C16>
 __global__ __launch_bounds__(kThreads) void k_sweep2z(SellDev A, const X* __restrict__ S, const X* __restrict__ b,
                                                       X* __restrict__ xo, T omega) {
+  dict_stage<K>(A);                          // before a wave past the last slice leaves
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
   const int slice = bid * kSliceWaves + threadIdx.x / kWave;
   const int lane = threadIdx.x % kWave;
@@ -220,23 +223,26 @@ hipError_t spmv_t(const SellDev& A, const void* b, const void* x, void* y, const
   const XO* bb = static_cast<const XO*>(b);
   const XI* xx = static_cast<const XI*>(x);
   XO* yy = static_cast<XO*>(y);
-  if (!partials && relay_level<B>(A)) {
+  if constexpr (K != VK_DICT) {
+    if (!partials && relay_level<B>(A)) {
 #define MGQ1_RELAY4(MODE, C16) \
-  hipLaunchKernelGGL((k_spmv_relay<B, K, XI, XO, T, MODE, C16>), unsigned(A.nslices), kThreads, 0, s, A, bb, xx, yy, mask)
+    hipLaunchKernelGGL((k_spmv_relay<B, K, XI, XO, T, MODE, C16>), unsigned(A.nslices), kThreads, 0, s, A, bb, xx, yy, mask)
 #define MGQ1_RELAY(MODE)                  \
-  if (A.col16) MGQ1_RELAY4(MODE, true);   \
-  else MGQ1_RELAY4(MODE, false)
-    if (mode == 0) { MGQ1_RELAY(0); }
-    else if (mode == 1) { MGQ1_RELAY(1); }
-    else if (mode == 2) { MGQ1_RELAY(2); }
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
+    if (A.col16) MGQ1_RELAY4(MODE, true);   \
+    else MGQ1_RELAY4(MODE, false)
+      if (mode == 0) { MGQ1_RELAY(0); }
+      else if (mode == 1) { MGQ1_RELAY(1); }
+      else if (mode == 2) { MGQ1_RELAY(2); }
+      else return hipErrorInvalidValue;
+      return hipGetLastError();
 #undef MGQ1_RELAY
 #undef MGQ1_RELAY4
+    }
   }
   // slot batch and column format are runtime properties of the operator
-#define MGQ1_SPMV4(MODE, NORM, KB, C16)                                                                     \
-  hipLaunchKernelGGL((k_spmv<B, K, XI, XO, T, MODE, NORM, KB, C16>), g, kThreads, 0, s, A, bb, xx, yy, mask, partials)
+#define MGQ1_SPMV4(MODE, NORM, KB, C16)                                                                               \
+  hipLaunchKernelGGL((k_spmv<B, K, XI, XO, T, MODE, NORM, KB, C16>), g, kThreads, dict_lds_bytes<K>(A), s, A, bb, xx, yy, mask, \
+                     partials)
 #define MGQ1_SPMV(MODE, NORM)                                                             \
   if (A.col16) {                                                                          \
     if (A.kb == kb_alt<B>()) MGQ1_SPMV4(MODE, NORM, kb_alt<B>(), true);                   \
@@ -262,6 +268,10 @@ hipError_t spmv_t(const SellDev& A, const void* b, const void* x, void* y, const
 template <int B>
 hipError_t spmv_block(const SellDev& A, const void* b, const void* x, void* y, const uint8_t* mask, int xk, int yk,
                   int mode, double* partials, hipStream_t s) {
+  if (A.kind == VK_DICT) {
+    if (xk == X_F64 && yk == X_F64) return spmv_t<B, VK_DICT, double, double, double>(A, b, x, y, mask, mode, partials, s);
+    return hipErrorInvalidValue;
+  }
   if (A.kind == VK_F64) {
     if (xk == X_F64 && yk == X_F64) return spmv_t<B, VK_F64, double, double, double>(A, b, x, y, mask, mode, partials, s);
     if (xk == X_F32 && yk == X_F64) return spmv_t<B, VK_F64, float, double, double>(A, b, x, y, mask, mode, partials, s);
@@ -291,22 +301,31 @@ hipError_t sweep_t(const SellDev& A, const void* S, const void* b, const void* x
 #define MGQ1_SWEEPR(KIND, C16) \
   hipLaunchKernelGGL((k_sweep_relay<B, KIND, X, T, C16>), unsigned(A.nslices), kThreads, 0, s, A, SS, bb, xx, oo, T(omega), T(beta), pmode)
 #define MGQ1_SWEEP4(KIND, KB, C16) \
-  hipLaunchKernelGGL((k_sweep<B, KIND, X, T, KB, C16>), g, kThreads, 0, s, A, SS, bb, xx, oo, T(omega), T(beta), pmode)
-#define MGQ1_SWEEP(KIND)                                                   \
-  if (relay) {                                                             \
-    if (A.col16) MGQ1_SWEEPR(KIND, true);                                  \
-    else MGQ1_SWEEPR(KIND, false);                                         \
-  } else if (A.col16) {                                                           \
+  hipLaunchKernelGGL((k_sweep<B, KIND, X, T, KB, C16>), g, kThreads, dict_lds_bytes<KIND>(A), s, A, SS, bb, xx, oo, T(omega), T(beta), pmode)
+#define MGQ1_SWEEP1(KIND)                                                  \
+  if (A.col16) {                                                           \
     if (A.kb == kb_alt<B>()) MGQ1_SWEEP4(KIND, kb_alt<B>(), true);         \
     else MGQ1_SWEEP4(KIND, kb_default<B>(), true);                         \
   } else {                                                                 \
     if (A.kb == kb_alt<B>()) MGQ1_SWEEP4(KIND, kb_alt<B>(), false);        \
     else MGQ1_SWEEP4(KIND, kb_default<B>(), false);                        \
   }
+#define MGQ1_SWEEP(KIND)                                                   \
+  if (relay) {                                                             \
+    if (A.col16) MGQ1_SWEEPR(KIND, true);                                  \
+    else MGQ1_SWEEPR(KIND, false);                                         \
+  } else {                                                                 \
+    MGQ1_SWEEP1(KIND)                                                      \
+  }
   // FP64 vectors go with FP64 values only; FP32 vectors with the reduced formats
   if constexpr (sizeof(X) == 8) {
-    if (A.kind != VK_F64) return hipErrorInvalidValue;
-    MGQ1_SWEEP(VK_F64);
+    if (A.kind == VK_DICT) {
+      MGQ1_SWEEP1(VK_DICT)
+    } else if (A.kind == VK_F64) {
+      MGQ1_SWEEP(VK_F64)
+    } else {
+      return hipErrorInvalidValue;
+    }
   } else {
     switch (A.kind) {
       case VK_F32: MGQ1_SWEEP(VK_F32); break;
@@ -316,6 +335,7 @@ hipError_t sweep_t(const SellDev& A, const void* S, const void* b, const void* x
     }
   }
 #undef MGQ1_SWEEP
+#undef MGQ1_SWEEP1
 #undef MGQ1_SWEEP4
 #undef MGQ1_SWEEPR
   return hipGetLastError();
@@ -351,7 +371,7 @@ hipError_t sweep2z_block(const SellDev& A, const void* S, const void* b, void* x
   const unsigned g = slice_grid(A.nslices);
   if (g == 0) return hipSuccess;
 #define MGQ1_S2Z4(KIND, X, T, KB, C16)                                                              \
-  hipLaunchKernelGGL((k_sweep2z<KIND, X, T, KB, C16>), g, kThreads, 0, s, A, static_cast<const X*>(S), \
+  hipLaunchKernelGGL((k_sweep2z<KIND, X, T, KB, C16>), g, kThreads, dict_lds_bytes<KIND>(A), s, A, static_cast<const X*>(S), \
                      static_cast<const X*>(b), static_cast<X*>(xo), T(omega))
 #define MGQ1_S2Z(KIND, X, T)                                                     \
   if (A.col16) {                                                                 \
@@ -362,8 +382,13 @@ hipError_t sweep2z_block(const SellDev& A, const void* S, const void* b, void* x
     else MGQ1_S2Z4(KIND, X, T, kb_default<1>(), false);                          \
   }
   if (xk == X_F64) {
-    if (A.kind != VK_F64) return hipErrorInvalidValue;
-    MGQ1_S2Z(VK_F64, double, double);
+    if (A.kind == VK_DICT) {
+      MGQ1_S2Z(VK_DICT, double, double);
+    } else if (A.kind == VK_F64) {
+      MGQ1_S2Z(VK_F64, double, double);
+    } else {
+      return hipErrorInvalidValue;
+    }
   } else {
     switch (A.kind) {
       case VK_F32: MGQ1_S2Z(VK_F32, float, float); break;

@@ -268,7 +268,7 @@ class Hierarchy:
         return pc.value, rc.value, wb.value
 
     def dictionary_blocks(self, l):
-        """Distinct blocks of level l's operator where its rows are stored once (0: other forms)."""
+        """Distinct blocks of level l's operator where they are stored once (0: other forms)."""
         n = C.c_int32()
         _check(lib().mg_level_dictionary(self.h, l, C.byref(n)))
         return n.value
