@@ -51,8 +51,8 @@ enum { MG_OUTER_IR = 0, MG_OUTER_FGMRES = 1 };
 enum { MG_SMOOTH_JACOBI = 0, MG_SMOOTH_CHEBYSHEV = 1 };
 /* precision of the V-cycle; the outer defect, the update and the coarse solve are FP64.
  * Every precision stores a level's distinct blocks once (lossless: the same bits in every
- * step, V-cycle and solve) where the level's FP64 blocks fill 16 MiB and more, at most 65,535 of
- * them are distinct and most rows repeat whole rows (single-problem handles).
+ * step, V-cycle and solve) where the level's values fill some 13 to 32 MiB and more, at most
+ * 65,535 of the blocks are distinct and most rows repeat whole rows (single-problem handles).
  * MG_PREC_FP64_DICT: FP64 throughout with the distinct blocks stored once on every level
  * of at most 65,535 of them, whatever its size and repetition (a 16-bit number per stored
  * block where rows do not repeat; not on levels that keep half of their blocks' values,

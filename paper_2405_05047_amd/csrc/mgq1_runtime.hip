@@ -785,22 +785,50 @@ int upload_dict(DevOwner* h, const HostSell& S, SellDev& D, hipStream_t s, bool*
   return MG_OK;
 }
 
-// Which levels take the node form: those whose FP64 blocks would fill kNodeFormBytes and more.
-// Smaller levels wait for memory latency, not bytes, and the node form's descriptor is one
-// more dependent load in their chain.  MGQ1_NODE_FORM=1 / =0: every level that can / none
-// (tests; the V-cycle's bits are the same).
-constexpr int64_t kNodeFormBytes = int64_t(16) << 20;
+int value_bytes(int vkind) { return vkind == VK_F64 ? 8 : vkind == VK_F32 ? 4 : 2; }
+constexpr int64_t kMiB = int64_t(1) << 20;
 
-bool want_node(const HostLevel& L, bool* must) {
-  if (const char* e = std::getenv("MGQ1_NODE_FORM")) {
-    *must = std::atoi(e) != 0;
-    return *must;
-  }
-  return L.nnzb * L.B * L.B * 8 >= kNodeFormBytes;
+// Which levels take the node form: those where the bytes that it saves cost more than the longer
+// chain of dependent reads (and, of the sliced form, the relay) gives.  A sweep in us, sliced ELL
+// and node form, on both sides of each line:
+//
+// One component: the operator streams 13 MiB and more (values in the cycle's type and 16-bit
+// columns), and 128 MiB more times the share of slices without uniform columns, which read
+// their columns per lane.  Uniform meshes: FP64 8.8 MiB 3.9 and 4.6, 17 MiB 5.3 and 4.9, 35 MiB 9.3
+// and 6.0; FP32 10 MiB 3.9 and 4.3, 13.4 MiB 3.8 and 3.8 (the FP64 product of the outer loop 5.9 and
+// 4.7), 21 MiB 5.4 and 4.2; 16-bit values 10 MiB 4.0 and 4.6, 14 MiB 4.7 and 4.8, 20 MiB 6.0 and 5.0.  Adaptive meshes, 7 to 15% of the slices not uniform: FP64 22 MiB 5.5 and 5.9, 32 MiB 8.6
+// and 6.4; FP32 19 MiB 4.6 and 5.3, 31 MiB 8.4 and 7.5; 16-bit values 21 MiB 6.6 and 8.0, 34 MiB 11.0
+// and 11.4, 82 MiB 22 and 19.
+//
+// Several components (measured with 3): values of 32 MiB in FP64, 28 in FP32 and 15 in 16 bits.
+// FP64 27 MiB 13.6 and 14.4, 41 MiB 11.3 and 8.9; FP32 26 MiB 8.0 and 8.4, 30 MiB 9.0 and 8.3; 16-bit
+// values 13 MiB 7.6 and 8.5, 15.2 MiB 7.3 and 8.5 (its solve 1.23 and 1.20 ms: the FP64 products
+// gain more), 15.6 MiB 11.4 and 10.6, 22 MiB 10.5 and 8.5.  At most an eighth of the slots in slices of
+// general values, whose block reads are scattered: 12% 28.6 and 25.3 (FP64, 90 MiB), 20% 15.1 and 25.2
+// (45 MiB).
+//
+// MGQ1_NODE_FORM=1 / =0: every level that can / none (tests; the V-cycle's bits are the same).
+// MGQ1_NODE_FORM, -1: not set
+int node_switch() {
+  const char* e = std::getenv("MGQ1_NODE_FORM");
+  return e ? std::atoi(e) != 0 : -1;
+}
+
+bool node_size(const HostLevel& L, int vkind) {
+  const int vb = value_bytes(vkind);
+  if (L.B == 1) return L.nnzb * (vb + 2) >= 13 * kMiB;
+  return L.nnzb * L.B * L.B * vb >= (vb == 8 ? 32 : vb == 4 ? 28 : 15) * kMiB;
+}
+
+bool node_pays(const HostLevel& L, const NodeHost& H, int vkind) {
+  if (L.B > 1) return H.general * 8 <= H.slots;
+  int64_t rest = 0;                 // slices without uniform columns
+  for (int64_t q = 0; q < H.nslices; ++q) rest += (H.desc[size_t(q) * 4 + 1] & kNodeColUniform) == 0;
+  return (L.nnzb * (value_bytes(vkind) + 2) - 13 * kMiB) * H.nslices >= 128 * kMiB * rest;
 }
 
 // The node form of level L (NodeDev): D.A64 and D.Ac with their smoother blocks.  *applied
-// tells whether the operator qualified; must: with any share of general slices.
+// tells whether the operator qualified; must: whatever it gives.
 int setup_node(DevOwner* h, const HostLevel& L, int vkind, int xk, bool must, int* flag, hipStream_t s, LevelDev& D,
                bool* applied) {
   *applied = false;
@@ -822,7 +850,7 @@ int setup_node(DevOwner* h, const HostLevel& L, int vkind, int xk, bool must, in
   auto H = std::make_unique<NodeHost>();
   const bool ok = build_node(L.n, B, L.rowptr.data(), L.col.data(), L.val.data(), coded ? rexp.data() : nullptr, must,
                              [](int64_t n, int64_t c, auto&& f) { parallel_for(n, c, f); }, *H);
-  if (!ok) return MG_OK;
+  if (!ok || (!must && !node_pays(L, *H, vkind))) return MG_OK;
   NodeDev N;
   N.n = L.n;
   N.B = B;
@@ -970,8 +998,8 @@ bool flow_shape(const HostLevel& L) {
 
 constexpr int kFlowEntry[8] = {0, 1, 2, 3, 4, 8, 12, 5};   // block entry of value v
 
-// The flow form is for levels that the node form's size rule names and its distinct rows refuse,
-// above the relay's limit: at 9,261 nodes (579 slices) a sweep is 8.4 us in the relay and 9.2 us
+// The flow form is for levels whose FP64 blocks fill 16 MiB and that the node form refuses, above
+// the relay's limit: at 9,261 nodes (579 slices) a sweep is 8.4 us in the relay and 9.2 us
 // in the flow form in FP64, 4.5 and 5.2 us in FP32; at 35,937 nodes 22.8 and 18.0, 12.2 and 7.8.
 // MGQ1_FLOW_FORM=0 / =1: off / on levels of any size, before the node form (tests; the bits
 // are the same); -1: not set.
@@ -1726,14 +1754,15 @@ int setup_level(DevOwner* h, const HostLevel& L, bool has_p, int NR, int vkind, 
   D.N = int64_t(L.n) * L.B;
   D.nnzb = L.nnzb;
   PhaseTimer pt;
-  bool node = false, must = any_size;
-  const int ff = flow_switch();
-  if (single && !sliced && ff != 1 && (want_node(L, &must) || any_size)) {
+  bool node = false;
+  const int ff = flow_switch(), nf = node_switch();
+  const bool must = any_size || nf == 1;
+  if (single && !sliced && ff != 1 && (must || (nf != 0 && node_size(L, vkind)))) {
     if ((rc = setup_node(h, L, vkind, xk, must, flag, s, D, &node))) return rc;
     pt.mark("  node form");
   }
   if (single && !sliced && !node && L.B == 4 && ff != 0 &&
-      (ff == 1 || (L.n > kRelaySlices * (kWave / 4) && want_node(L, &must)))) {
+      (ff == 1 || (nf != 0 && L.n > kRelaySlices * (kWave / 4) && L.nnzb * 128 >= 16 * kMiB))) {
     if ((rc = setup_flow(h, L, vkind, xk, flag, s, D, &node))) return rc;
     pt.mark("  flow form");
   }
