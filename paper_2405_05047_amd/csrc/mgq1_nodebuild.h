@@ -29,6 +29,12 @@ struct NodeHost {
   std::vector<int32_t> sblock;          // block number behind each smoother table entry
   int64_t slots = 0, general = 0;       // slot rows of 64, and those of slices with general values
 
+  // frees what only the device reads once it is there; the rest maps stored values back
+  void drop_uploaded() {
+    for (auto* v : {&opat, &rpat, &base, &col32, &sblock}) std::vector<int32_t>().swap(*v);
+    for (auto* v : {&col16, &sidx}) std::vector<uint16_t>().swap(*v);
+    std::vector<int8_t>().swap(dexp);
+  }
   int32_t nblocks() const { return int32_t(dict.size()) / (B * B); }
   int32_t node_at(int64_t pos) const { return perm.empty() ? int32_t(pos) : perm[size_t(pos)]; }
   // number of the block in slot k of slice s, lane r

@@ -968,7 +968,7 @@ int setup_node(DevOwner* h, const HostLevel& L, int vkind, int xk, bool must, in
   D.Ac.kind = vkind;
   D.A64.node = D.n64.get();
   D.Ac.node = D.nc.get();
-  D.hperm = H->perm;
+  H->drop_uploaded();
   D.nh = std::move(H);
   *applied = true;
   return MG_OK;
