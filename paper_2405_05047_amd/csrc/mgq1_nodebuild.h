@@ -93,16 +93,27 @@ struct BlockSet {
 
 constexpr int32_t kMaxBlocks = 65535;
 
+// chunks of a loop whose chunks each keep a set of their own: a small level is not worth the
+// threads
+inline int64_t set_chunks(int64_t items, int64_t least) {
+  return std::min<int64_t>(64, std::max<int64_t>(1, items / least));
+}
+
+struct Always {
+  bool operator()(const NodeHost&) const { return true; }
+};
+
 }  // namespace nodebuild
 
 // Builds the node form of a block CSR operator (n rows, B x B blocks, rows' exponents in
 // row_exp when given: blocks are then distinct with their rows' exponents).  false: more
 // than 65,535 distinct blocks, vectors of 4 GiB and more, or (must == false) more than a
 // quarter of the slots in slices of general values, where the sliced-ELL form moves fewer
-// instructions per block.  Throws std::bad_alloc.
-template <class ParallelFor>
+// instructions per block, or pays(H) false of the descriptors and counts.  Throws
+// std::bad_alloc.
+template <class ParallelFor, class Pays = nodebuild::Always>
 bool build_node(int32_t n, int B, const int32_t* rowptr, const int32_t* col, const double* val,
-                const int8_t* row_exp, bool must, ParallelFor&& parallel_for, NodeHost& H) {
+                const int8_t* row_exp, bool must, ParallelFor&& parallel_for, NodeHost& H, Pays pays = Pays()) {
   using namespace nodebuild;
   const int BB = B * B;
   if (B > 4 || n < 1 || int64_t(n) * B * 8 >= (int64_t(1) << 32)) return false;
@@ -113,7 +124,7 @@ bool build_node(int32_t n, int B, const int32_t* rowptr, const int32_t* col, con
   const int64_t nnz = rowptr[n];
   std::vector<uint16_t> id(size_t(nnz), 0);
   // ---- distinct blocks: per chunk of rows, then merged in chunk order
-  const int64_t nchunk = 64, per = (int64_t(n) + nchunk - 1) / nchunk;
+  const int64_t nchunk = set_chunks(n, 256), per = (int64_t(n) + nchunk - 1) / nchunk;
   std::vector<BlockSet> sets(static_cast<size_t>(nchunk), BlockSet(words));
   std::vector<int> bad(size_t(nchunk), 0);
   auto key_of = [&](int64_t i, int64_t k, uint64_t* key) {
@@ -439,7 +450,7 @@ bool build_node(int32_t n, int B, const int32_t* rowptr, const int32_t* col, con
       n16 += w;
     }
   }
-  if (!must && H.general * 4 > H.slots) return false;
+  if (!must && (H.general * 4 > H.slots || !pays(H))) return false;
   H.didx.assign(size_t(nd) * kWave, 0);
   H.col16.assign(size_t(n16) * kWave, 0);
   H.base.assign(size_t(n16), 0);

@@ -728,7 +728,7 @@ int upload_dict(DevOwner* h, const HostSell& S, SellDev& D, hipStream_t s, bool*
   using nodebuild::BlockSet;
   *applied = false;
   const int B = S.B, BB = B * B, W = S.W, R = S.R;
-  const int64_t nblk = S.slots * R, nchunk = 64, per = (nblk + nchunk - 1) / nchunk;
+  const int64_t nblk = S.slots * R, nchunk = nodebuild::set_chunks(nblk, 4096), per = (nblk + nchunk - 1) / nchunk;
   std::vector<BlockSet> sets(static_cast<size_t>(nchunk), BlockSet(BB));
   std::vector<int> bad(size_t(nchunk), 0);
   std::vector<uint16_t> idx(static_cast<size_t>(nblk));
@@ -849,8 +849,9 @@ int setup_node(DevOwner* h, const HostLevel& L, int vkind, int xk, bool must, in
   }
   auto H = std::make_unique<NodeHost>();
   const bool ok = build_node(L.n, B, L.rowptr.data(), L.col.data(), L.val.data(), coded ? rexp.data() : nullptr, must,
-                             [](int64_t n, int64_t c, auto&& f) { parallel_for(n, c, f); }, *H);
-  if (!ok || (!must && !node_pays(L, *H, vkind))) return MG_OK;
+                             [](int64_t n, int64_t c, auto&& f) { parallel_for(n, c, f); }, *H,
+                             [&](const NodeHost& N) { return node_pays(L, N, vkind); });
+  if (!ok) return MG_OK;
   NodeDev N;
   N.n = L.n;
   N.B = B;
@@ -3099,7 +3100,7 @@ bool distinct_lists(int64_t nnzb, const std::vector<uint32_t>& cptr, const std::
     return e;
   };
   constexpr int32_t kMax = 65535;
-  const int64_t nchunk = 64, per = (nnzb + nchunk - 1) / nchunk;
+  const int64_t nchunk = nodebuild::set_chunks(nnzb, 4096), per = (nnzb + nchunk - 1) / nchunk;
   std::vector<Set> sets(static_cast<size_t>(nchunk));
   std::vector<int> bad(size_t(nchunk), 0);
   lid.assign(size_t(nnzb), 0);
