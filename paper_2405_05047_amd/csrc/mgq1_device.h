@@ -107,6 +107,12 @@ __device__ __forceinline__ bool is_wide(const SellDev& A, int su) {
   return A.wide != nullptr && ((A.wide[su >> 5] >> (su & 31)) & 1u);
 }
 
+// bytes of LDS that hold a VK_DICT operator's blocks (0: they are read through the caches)
+__host__ __device__ __forceinline__ int dict_lds_size(const SellDev& A) {
+  const int64_t bytes = int64_t(A.ndict) * A.B * A.B * int64_t(sizeof(double));
+  return bytes <= kDictLdsBytes ? int(bytes) : 0;
+}
+
 template <int NB, int B, int NR, int K, class XI, class T, bool C16, bool NT>
 __device__ __forceinline__ void sell_batch(const SellDev& A, int k, int r, int node, int rl, int q,
                                            const XI* __restrict__ x, T& acc) {
@@ -130,7 +136,7 @@ __device__ __forceinline__ void sell_batch(const SellDev& A, int k, int r, int n
     for (int qq = 0; qq < NB; ++qq) di[qq] = stream_load<NT>(A.didx + int64_t(k + qq) * R + r);
     __builtin_amdgcn_sched_barrier(0);
     const int c = rl % B;
-    if (A.dlds) {
+    if (dict_lds_size(A) > 0) {
       extern __shared__ double dict_lds[];
 #pragma unroll
       for (int qq = 0; qq < NB; ++qq)
@@ -140,7 +146,8 @@ __device__ __forceinline__ void sell_batch(const SellDev& A, int k, int r, int n
 #pragma unroll
       for (int qq = 0; qq < NB; ++qq)
 #pragma unroll
-        for (int cc = 0; cc < B; ++cc) av[qq][cc] = A.dtab[(int64_t(di[qq]) * B + c) * B + cc];
+        for (int cc = 0; cc < B; ++cc)
+          av[qq][cc] = static_cast<const double*>(A.val)[(int64_t(di[qq]) * B + c) * B + cc];
     }
   } else {
 #pragma unroll
@@ -179,16 +186,15 @@ __device__ __forceinline__ void sell_batch(const SellDev& A, int k, int r, int n
     for (int cc = 0; cc < B; ++cc) acc += T(Val<K>::dec(av[qq][cc])) * T(xv[qq][cc]);
 }
 
-// dictionary form with dlds set: the workgroup copies the dictionary into LDS before any
-// slice work (all threads reach the barrier); launched with ndict * B * B doubles of
-// dynamic shared memory
+// small dictionaries: the workgroup copies them into LDS before any slice work (all threads
+// reach the barrier); launched with dict_lds_bytes of dynamic shared memory
 template <int K>
 __device__ __forceinline__ void dict_stage(const SellDev& A) {
   if constexpr (K == VK_DICT) {
-    if (A.dlds) {
+    const int n = dict_lds_size(A) / int(sizeof(double));
+    if (n > 0) {
       extern __shared__ double dict_lds[];
-      const int n = A.ndict * A.B * A.B;
-      for (int i = int(threadIdx.x); i < n; i += int(blockDim.x)) dict_lds[i] = A.dtab[i];
+      for (int i = int(threadIdx.x); i < n; i += int(blockDim.x)) dict_lds[i] = static_cast<const double*>(A.val)[i];
       __syncthreads();
     }
   }
@@ -196,7 +202,7 @@ __device__ __forceinline__ void dict_stage(const SellDev& A) {
 
 template <int K>
 inline size_t dict_lds_bytes(const SellDev& A) {
-  return (K == VK_DICT && A.dlds) ? size_t(A.ndict) * A.B * A.B * sizeof(double) : 0;
+  return K == VK_DICT ? size_t(dict_lds_size(A)) : 0;
 }
 
 // The same batch for the second of two sweeps from x = 0 with b = 1: the iterate after the
@@ -217,13 +223,13 @@ __device__ __forceinline__ void sell_batch_z(const SellDev& A, int k, int rl, in
 #pragma unroll
     for (int qq = 0; qq < NB; ++qq) di[qq] = stream_load<NT>(A.didx + int64_t(k + qq) * kWave + rl);
     __builtin_amdgcn_sched_barrier(0);
-    if (A.dlds) {
+    if (dict_lds_size(A) > 0) {
       extern __shared__ double dict_lds[];
 #pragma unroll
       for (int qq = 0; qq < NB; ++qq) av[qq] = dict_lds[di[qq]];
     } else {
 #pragma unroll
-      for (int qq = 0; qq < NB; ++qq) av[qq] = A.dtab[di[qq]];
+      for (int qq = 0; qq < NB; ++qq) av[qq] = static_cast<const double*>(A.val)[di[qq]];
     }
   } else {
 #pragma unroll

@@ -20,6 +20,9 @@ constexpr int kMaxRedBlocks = 2048;   // grid (= partial count) of the vector re
 struct NodeDev;
 struct FlowDev;
 
+// dictionaries (VK_DICT) up to this size are copied into LDS by every workgroup
+constexpr int kDictLdsBytes = 16384;
+
 // Sliced ELL of a block matrix: one slice = 64 lanes = R = 64/B nodes x B components;
 // lane = r*B + c handles scalar row (node slice*R + r, component c).  For block slot k of
 // the slice, the value of column component cc for lane `ln` sits at
@@ -32,8 +35,12 @@ struct SellDev {
   int64_t slots = 0;
   const int32_t* sptr = nullptr;    // nslices + 1
   const int32_t* col = nullptr;     // slots * R
-  const void* val = nullptr;        // slots * B * 64 values of `kind`
-  const int8_t* rexp = nullptr;     // nslices * 64 power-of-two row exponents (F16 / BF16)
+  // slots * B * 64 values of `kind`; VK_DICT: the ndict distinct B x B FP64 blocks, row-major
+  const void* val = nullptr;
+  union {
+    const int8_t* rexp = nullptr;   // F16 / BF16: nslices * 64 power-of-two row exponents
+    const uint16_t* didx;           // VK_DICT: number of the block of node row r in slot k at
+  };                                // k * R + r
   int kind = VK_F64;
   int kb = 0;                       // block slots per load batch (0: the default for B)
   const uint16_t* col16 = nullptr;  // col - colbase[slot] as 16 bits where the slot's columns
@@ -43,12 +50,7 @@ struct SellDev {
   const int32_t* perm = nullptr;    // node at row position slice*R + r (NULL: the position
                                     // itself); rows sorted by length inside windows of slices
   int nt = 1;                       // 1: values and indices read with non-temporal loads
-  // kind VK_DICT: the block of node row r in slot k is dtab[didx[k * R + r]] (ndict
-  // distinct B x B FP64 blocks, row-major); val is not read
-  const uint16_t* didx = nullptr;
-  const double* dtab = nullptr;
-  int32_t ndict = 0;
-  int dlds = 0;                     // VK_DICT: every workgroup first copies dtab into LDS
+  int32_t ndict = 0;                // VK_DICT: up to kDictLdsBytes every workgroup copies them into LDS
   const NodeDev* node = nullptr;    // host: the level is stored in the node form instead (the
                                     // sliced arrays above are then absent)
   const FlowDev* flow = nullptr;    // host: ... or in the flow form
