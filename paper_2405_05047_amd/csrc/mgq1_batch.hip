@@ -177,7 +177,11 @@ __device__ __forceinline__ void rows_rest(int rem, const SellDev& A, int k, cons
 template <int K, class XI, class T, int KB, bool C16>
 __device__ __forceinline__ void rows_loop(const SellDev& A, const RowLane& s, const XI* __restrict__ x,
                                           T (&acc)[kRowRhs]) {
-  constexpr int NB = KB / 2;               // two or more values per slot
+  // The lane holds kRowRhs values per slot.  The default slot batch takes half the slots at a
+  // time, for occupancy on large levels; the other one all 16, a 9-point row in one dependent
+  // read, for small levels (16,641 nodes and two of 1,000, 16-bit values: sweep 5.4 and 4.4 us,
+  // solve 3.86 and 3.64 ms); the setup times both.
+  constexpr int NB = KB == kb_alt<1>() ? KB : KB / 2;
   int k, k1;
   slot_range(A, s.slice, k, k1);
   for (; k + NB <= k1; k += NB) rows_batch<NB, K, XI, T, C16>(A, k, s, x, acc);
