@@ -269,6 +269,11 @@ struct HostSell {
   std::vector<int8_t> rexp;                         // nslices * W
 };
 
+// slices per chunk of a parallel loop: those of some 2^16 values, whatever a slice holds
+int64_t slice_chunk(const HostSell& S) {
+  return std::max<int64_t>(1, (int64_t(1) << 16) * S.nslices / std::max<int64_t>(1, S.slots * S.B * S.W));
+}
+
 // Uniform slice width (plain ELL) on levels of up to 2^18 scalar rows, whose kernels wait
 // on memory latency rather than bandwidth, when padding every slice to the widest one
 // adds at most 12.5% slots (on larger levels only when it adds none: there the extra
@@ -376,7 +381,7 @@ HostSell build_sell(const HostLevel& L, int NR = 1) {
   S.val.assign(size_t(S.slots) * B * W, 0.0);
   S.rexp.assign(size_t(S.nslices) * W, 0);
   // every slice fills its own slots and exponents (parallel over slices)
-  parallel_for(S.nslices, 1024, [&](int64_t s0, int64_t s1) {
+  parallel_for(S.nslices, slice_chunk(S), [&](int64_t s0, int64_t s1) {
   for (int64_t s = s0; s < s1; ++s) {
     const int32_t w = S.sptr[s + 1] - S.sptr[s];
     for (int r = 0; r < S.R; ++r) {
@@ -635,7 +640,7 @@ int upload_sell(DevOwner* h, const HostSell& S, int kind, SellDev& D, hipStream_
   std::vector<int32_t> base(size_t(S.slots), 0);
   std::vector<uint8_t> is_wide(size_t(S.nslices), 0);
   // per slice (parallel): offsets and bases, or the wide mark
-  parallel_for(S.nslices, 1024, [&](int64_t s0, int64_t s1) {
+  parallel_for(S.nslices, slice_chunk(S), [&](int64_t s0, int64_t s1) {
   for (int64_t sl = s0; sl < s1; ++sl) {
     bool fits = !(every > 0 && sl % every == 0);
     for (int64_t k = S.sptr[sl]; k < S.sptr[sl + 1] && fits; ++k) {
@@ -699,7 +704,7 @@ int upload_sell(DevOwner* h, const HostSell& S, int kind, SellDev& D, hipStream_
     D.val = v;
   } else {
     std::vector<uint16_t> q(nv);
-    parallel_for(S.nslices, 1024, [&](int64_t s0, int64_t s1) {
+    parallel_for(S.nslices, slice_chunk(S), [&](int64_t s0, int64_t s1) {
       for (int64_t sl = s0; sl < s1; ++sl)
         for (int32_t k = S.sptr[sl]; k < S.sptr[sl + 1]; ++k)
           for (int cc = 0; cc < S.B; ++cc)
