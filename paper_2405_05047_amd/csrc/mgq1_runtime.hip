@@ -3252,25 +3252,35 @@ int asm_setup(AsmDev* A, const mg_asm_in& in, hipStream_t s) {
   uint16_t* p16;
   double* pd;
   uint8_t* p8;
-  // Where the distinct lists are at most a quarter of the blocks (and at most 65,535), each is
-  // summed once and spread over its blocks; a mesh so irregular (or so small) that they are
-  // more is summed block by block.  MGQ1_ASM_LISTS=0 keeps that everywhere (tests; the values
-  // are the same bits).
-  std::vector<uint16_t> lid, bits(size_t(in.nnzb), 0);
+  // Each distinct list summed once and spread over its blocks takes a second launch.  Block by
+  // block and by lists: one component 4.7 MB of values 9.1 and 11.4 us, 10.5 MB 11.4 and 11.5, 18.8 MB
+  // 17.5 and 11.0; three components 8 MB 16.2 and 16.6, 27 MB 21.4 and 19.5.  Next to hanging nodes in
+  // 3D a block has up to 116 contributions, and the chain of the longest list sets the time:
+  // 4.6 MB 42.9 and 38.0, 16.5 MB 41.7 and 37.3.  So from 10 MiB of values or lists of more than 32,
+  // where the distinct lists are at most a quarter of the blocks (and at most 65,535).
+  // MGQ1_ASM_LISTS=0 / =1: block by block / by lists everywhere (tests; the values are the same
+  // bits).
+  const char* sw = std::getenv("MGQ1_ASM_LISTS");
+  const int force = sw ? std::atoi(sw) != 0 : -1;
+  uint32_t longest = 0;
+  for (int64_t k = 0; k < in.nnzb; ++k) longest = std::max(longest, cptr[size_t(k) + 1] - cptr[size_t(k)]);
+  bool lists = force == 1 || (force != 0 && (in.nnzb * B * B * 8 >= 10 * kMiB || longest > 32));
+  std::vector<uint16_t> lid, bits;
   std::vector<int64_t> rep;
-  parallel_for(in.nnzb, 1 << 16, [&](int64_t k0, int64_t k1) {
-    for (int64_t k = k0; k < k1; ++k) {
-      unsigned m = brow[size_t(k)] == bcol[size_t(k)] ? 256u : 0u;
-      for (int c = 0; c < B; ++c) {
-        if (mask[size_t(brow[size_t(k)]) * B + c]) m |= 1u << c;
-        if (mask[size_t(bcol[size_t(k)]) * B + c]) m |= 16u << c;
+  if (lists) {
+    bits.resize(size_t(in.nnzb));
+    parallel_for(in.nnzb, 1 << 16, [&](int64_t k0, int64_t k1) {
+      for (int64_t k = k0; k < k1; ++k) {
+        unsigned m = brow[size_t(k)] == bcol[size_t(k)] ? 256u : 0u;
+        for (int c = 0; c < B; ++c) {
+          if (mask[size_t(brow[size_t(k)]) * B + c]) m |= 1u << c;
+          if (mask[size_t(bcol[size_t(k)]) * B + c]) m |= 16u << c;
+        }
+        bits[size_t(k)] = uint16_t(m);
       }
-      bits[size_t(k)] = uint16_t(m);
-    }
-  });
-  const char* off = std::getenv("MGQ1_ASM_LISTS");
-  const bool lists = !(off && std::atoi(off) == 0) && distinct_lists(in.nnzb, cptr, code, bits, lid, rep) &&
-                     int64_t(rep.size()) * 4 <= in.nnzb;
+    });
+    lists = distinct_lists(in.nnzb, cptr, code, bits, lid, rep) && (force == 1 || int64_t(rep.size()) * 4 <= in.nnzb);
+  }
   if (lists) {
     std::vector<uint32_t> lptr(1, 0);
     std::vector<uint16_t> lcode, lmask;
