@@ -343,10 +343,10 @@ __global__ __launch_bounds__(kThreads) void k_bsell(const BEntry* __restrict__ E
       else if (KIND == BK_SWEEP) rows_sweep<K, X, T, KB, C16>(e.A, S, in0, in1, out, omega, slice);
       else rows_spmv<K, X, X, T, 2, KB, C16>(e.A, in0, in1, out, e.mask, slice);
     } else {
-      const SliceLane s = slice_lane<B, NR>(e.A, slice, threadIdx.x % kWave);
-      if (KIND == BK_SWEEP0) sweep0_slice<B, NR, X, T>(S, in0, out, omega, s);
-      else if (KIND == BK_SWEEP) sweep_slice<B, NR, K, X, T, KB, C16, 1>(e.A, S, in0, in1, out, omega, s);
-      else spmv_slice<B, NR, K, X, X, T, 2, KB, C16, 1>(e.A, in0, in1, out, e.mask, s);
+      const SliceLane s = slice_lane<B>(e.A, slice, threadIdx.x % kWave);
+      if (KIND == BK_SWEEP0) sweep0_slice<B, X, T>(S, in0, out, omega, s);
+      else if (KIND == BK_SWEEP) sweep_slice<B, K, X, T, KB, C16, 1>(e.A, S, in0, in1, out, omega, s);
+      else spmv_slice<B, K, X, X, T, 2, KB, C16, 1>(e.A, in0, in1, out, e.mask, s);
     }
   });
 }
@@ -399,8 +399,8 @@ __global__ __launch_bounds__(kThreads) void k_bsell64(const BEntry* __restrict__
         __syncthreads();
       }
     } else {
-      const SliceLane s = slice_lane<B, NR>(e.A, slice, threadIdx.x % kWave);
-      const double out = spmv_slice<B, NR, VK_F64, XI, double, double, MODE, KB, C16, 1>(e.A, b, x, y, nullptr, s);
+      const SliceLane s = slice_lane<B>(e.A, slice, threadIdx.x % kWave);
+      const double out = spmv_slice<B, VK_F64, XI, double, double, MODE, KB, C16, 1>(e.A, b, x, y, nullptr, s);
       if (KIND == BK_DEFECT64) {
         const double t = block_sum_rhs(out * out, NR, lds);
         if (threadIdx.x < NR) partials[int64_t(e.first + blk) * NR + threadIdx.x] = t;
@@ -439,11 +439,11 @@ __global__ __launch_bounds__(kThreads) void k_btsell(const BEntry* __restrict__ 
         else trows<X, T, double, true, 1>(e.Ts, slice, in, out, e.mask, e.mask_c);
       }
     } else if (KIND == BK_RESTRICT) {
-      if (e.Ts.f32) tsell_lane<B, NR, X, T, float, false, 0>(e.Ts, slice, lane, in, out, e.mask_c, nullptr);
-      else tsell_lane<B, NR, X, T, double, false, 0>(e.Ts, slice, lane, in, out, e.mask_c, nullptr);
+      if (e.Ts.f32) tsell_lane<B, X, T, float, false, 0>(e.Ts, slice, lane, in, out, e.mask_c, nullptr);
+      else tsell_lane<B, X, T, double, false, 0>(e.Ts, slice, lane, in, out, e.mask_c, nullptr);
     } else {
-      if (e.Ts.f32) tsell_lane<B, NR, X, T, float, true, 1>(e.Ts, slice, lane, in, out, e.mask, e.mask_c);
-      else tsell_lane<B, NR, X, T, double, true, 1>(e.Ts, slice, lane, in, out, e.mask, e.mask_c);
+      if (e.Ts.f32) tsell_lane<B, X, T, float, true, 1>(e.Ts, slice, lane, in, out, e.mask, e.mask_c);
+      else tsell_lane<B, X, T, double, true, 1>(e.Ts, slice, lane, in, out, e.mask, e.mask_c);
     }
   });
 }

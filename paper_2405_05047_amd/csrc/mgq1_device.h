@@ -113,11 +113,10 @@ __host__ __device__ __forceinline__ int dict_lds_size(const SellDev& A) {
   return bytes <= kDictLdsBytes ? int(bytes) : 0;
 }
 
-template <int NB, int B, int NR, int K, class XI, class T, bool C16, bool NT>
-__device__ __forceinline__ void sell_batch(const SellDev& A, int k, int r, int node, int rl, int q,
+template <int NB, int B, int K, class XI, class T, bool C16, bool NT>
+__device__ __forceinline__ void sell_batch(const SellDev& A, int k, int r, int node, int rl,
                                            const XI* __restrict__ x, T& acc) {
-  constexpr int R = kWave / (B * NR);
-  constexpr int W = kWave / NR;
+  constexpr int R = kWave / B;
   using VR = typename Val<K>::raw;
   // phase 1: column indices and values (independent of each other); phase 2: the x
   // gathers; phase 3: the FMAs.  Scheduling barriers keep the phases apart, otherwise the
@@ -130,7 +129,6 @@ __device__ __forceinline__ void sell_batch(const SellDev& A, int k, int r, int n
   if constexpr (K == VK_DICT) {
     // column and block numbers first, then the block's row from the (cached) dictionary together
     // with the x gathers
-    static_assert(NR == 1, "the dictionary form has one right-hand side");
     unsigned short di[NB];
 #pragma unroll
     for (int qq = 0; qq < NB; ++qq) di[qq] = stream_load<NT>(A.didx + int64_t(k + qq) * R + r);
@@ -152,13 +150,13 @@ __device__ __forceinline__ void sell_batch(const SellDev& A, int k, int r, int n
   } else {
 #pragma unroll
     for (int qq = 0; qq < NB; ++qq) {
-      const int64_t vb = int64_t(k + qq) * B * W + rl;
+      const int64_t vb = int64_t(k + qq) * B * kWave + rl;
 #pragma unroll
-      for (int cc = 0; cc < B; ++cc) av[qq][cc] = Val<K>::template load<NT>(A.val, vb + cc * W);
+      for (int cc = 0; cc < B; ++cc) av[qq][cc] = Val<K>::template load<NT>(A.val, vb + cc * kWave);
     }
     __builtin_amdgcn_sched_barrier(0);
   }
-  if constexpr (B > 1 && NR == 1) {
+  if constexpr (B > 1) {
     // each lane gathers only its own component of the neighbour node (the B lanes of a
     // node read one contiguous B-vector together) and takes the others from its node's
     // lanes by wave shuffles
@@ -173,11 +171,7 @@ __device__ __forceinline__ void sell_batch(const SellDev& A, int k, int r, int n
       for (int cc = 0; cc < B; ++cc) xv[qq][cc] = __shfl(xo[qq], base + cc, kWave);
   } else {
 #pragma unroll
-    for (int qq = 0; qq < NB; ++qq) {
-      const XI* xj = x + uint64_t(js[qq]) * (B * NR) + q;
-#pragma unroll
-      for (int cc = 0; cc < B; ++cc) xv[qq][cc] = xj[cc * NR];
-    }
+    for (int qq = 0; qq < NB; ++qq) xv[qq][0] = x[js[qq]];
   }
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -267,44 +261,39 @@ __device__ __forceinline__ void sell_loop_z(int k, int k1, const SellDev& A, int
 }
 
 // the remaining rem < KB slots of a slice as one batch of exactly rem slots
-template <int N, int B, int NR, int K, class XI, class T, bool C16, bool NT>
-__device__ __forceinline__ void sell_rest(int rem, const SellDev& A, int k, int r, int node, int rl, int q,
+template <int N, int B, int K, class XI, class T, bool C16, bool NT>
+__device__ __forceinline__ void sell_rest(int rem, const SellDev& A, int k, int r, int node, int rl,
                                           const XI* __restrict__ x, T& acc) {
   if constexpr (N >= 1) {
-    if (rem == N) sell_batch<N, B, NR, K, XI, T, C16, NT>(A, k, r, node, rl, q, x, acc);
-    else sell_rest<N - 1, B, NR, K, XI, T, C16, NT>(rem, A, k, r, node, rl, q, x, acc);
+    if (rem == N) sell_batch<N, B, K, XI, T, C16, NT>(A, k, r, node, rl, x, acc);
+    else sell_rest<N - 1, B, K, XI, T, C16, NT>(rem, A, k, r, node, rl, x, acc);
   }
 }
 
 // the slots [k, k1) of one slice: batches of KB, then the remainder as one batch
-template <int KB, int B, int NR, int K, class XI, class T, bool C16, bool NT>
-__device__ __forceinline__ void sell_loop(int k, int k1, const SellDev& A, int r, int node, int rl, int q,
+template <int KB, int B, int K, class XI, class T, bool C16, bool NT>
+__device__ __forceinline__ void sell_loop(int k, int k1, const SellDev& A, int r, int node, int rl,
                                           const XI* __restrict__ x, T& acc) {
-  for (; k + KB <= k1; k += KB) sell_batch<KB, B, NR, K, XI, T, C16, NT>(A, k, r, node, rl, q, x, acc);
-  sell_rest<KB - 1, B, NR, K, XI, T, C16, NT>(k1 - k, A, k, r, node, rl, q, x, acc);
+  for (; k + KB <= k1; k += KB) sell_batch<KB, B, K, XI, T, C16, NT>(A, k, r, node, rl, x, acc);
+  sell_rest<KB - 1, B, K, XI, T, C16, NT>(k1 - k, A, k, r, node, rl, x, acc);
 }
 
 template <int B> constexpr int kb_default() { return B <= 2 ? 8 : 4; }
 template <int B> constexpr int kb_alt() { return B <= 2 ? 16 : 8; }
 
-// per-lane row dot product of a slice: sum_k sum_cc a(k, cc) x[(col_k * B + cc) * NR + q].
-// NR right-hand sides share every matrix entry: lane = (r * B + c) * NR + q, the slice
-// holds R = 64 / (B * NR) nodes, and the values of row lane rl = lane / NR sit at
-// val[(k * B + cc) * W + rl] with the padded row-lane stride W = 64 / NR (R * B rounded up,
-// 64 for one right-hand side).  NR = 1 is the single right-hand-side layout.  Slots are
-// consumed in batches of KB, the remainder in one shorter batch (slice-uniform branch);
-// the FMAs run in slot order whatever KB is, so every KB gives the same bits.
+// per-lane row dot product of a slice: sum_k sum_cc a(k, cc) x[col_k * B + cc], lane = r * B + c,
+// values at val[(k * B + cc) * 64 + lane].  Slots are consumed in batches of KB, the remainder in
+// one shorter batch (slice-uniform branch); the FMAs run in slot order whatever KB is, so
+// every KB gives the same bits.
 // LK: load kind of the operator stream — 0 as the operator says (A.nt), 1 always
 // non-temporal (batched form), 2 always ordinary (single-workgroup tail)
-template <int B, int NR, int K, class XI, class T, int KB = kb_default<B>(), bool C16 = false, int LK = 0>
+template <int B, int K, class XI, class T, int KB = kb_default<B>(), bool C16 = false, int LK = 0>
 __device__ __forceinline__ T sell_dot(const SellDev& A, int slice, int lane, bool valid,
                                       const XI* __restrict__ x) {
-  constexpr int W = kWave / NR;
-  constexpr int R = kWave / (B * NR);
+  constexpr int R = kWave / B;
   T acc = T(0);
   if (!valid) return acc;
-  const int rl = lane / NR, q = lane % NR;
-  const int r = rl / B;
+  const int rl = lane, r = lane / B;
   // the slice is the same for the whole wave: keep it (and the slot range, the load bases)
   // in scalar registers
   slice = __builtin_amdgcn_readfirstlane(slice);
@@ -314,16 +303,16 @@ __device__ __forceinline__ T sell_dot(const SellDev& A, int slice, int lane, boo
   const bool wide = C16 && is_wide(A, slice);
   if (LK == 1 || (LK == 0 && A.nt)) {
     if constexpr (LK != 2) {
-      if (wide) sell_loop<KB, B, NR, K, XI, T, false, true>(k, k1, A, r, node, rl, q, x, acc);
-      else sell_loop<KB, B, NR, K, XI, T, C16, true>(k, k1, A, r, node, rl, q, x, acc);
+      if (wide) sell_loop<KB, B, K, XI, T, false, true>(k, k1, A, r, node, rl, x, acc);
+      else sell_loop<KB, B, K, XI, T, C16, true>(k, k1, A, r, node, rl, x, acc);
     }
   } else {
     if constexpr (LK != 1) {
-      if (wide) sell_loop<KB, B, NR, K, XI, T, false, false>(k, k1, A, r, node, rl, q, x, acc);
-      else sell_loop<KB, B, NR, K, XI, T, C16, false>(k, k1, A, r, node, rl, q, x, acc);
+      if (wide) sell_loop<KB, B, K, XI, T, false, false>(k, k1, A, r, node, rl, x, acc);
+      else sell_loop<KB, B, K, XI, T, C16, false>(k, k1, A, r, node, rl, x, acc);
     }
   }
-  if (K == VK_F16 || K == VK_BF16) acc *= T(ldexpf(1.0f, A.rexp[int64_t(slice) * W + rl]));
+  if (K == VK_F16 || K == VK_BF16) acc *= T(ldexpf(1.0f, A.rexp[int64_t(slice) * kWave + rl]));
   return acc;
 }
 
@@ -400,25 +389,25 @@ __device__ __forceinline__ double sum_partials(const double* __restrict__ p, int
 // geometry of one wave-slice
 struct SliceLane {
   int slice, lane, node;
-  int64_t dof;            // (node * B + c) * NR + q
+  int64_t dof;            // node * B + c
   bool valid;
 };
 
-template <int B, int NR>
+template <int B>
 __device__ __forceinline__ SliceLane slice_lane(const SellDev& A, int slice, int lane) {
-  constexpr int R = kWave / (B * NR);
+  constexpr int R = kWave / B;
   SliceLane s;
   s.slice = slice;
   s.lane = lane;
-  const int pos = slice * R + lane / (B * NR);   // row position of the lane's node
-  s.valid = slice < A.nslices && lane < R * B * NR && pos < A.n;
+  const int pos = slice * R + lane / B;   // row position of the lane's node
+  s.valid = slice < A.nslices && lane < R * B && pos < A.n;
   s.node = (A.perm != nullptr && s.valid) ? A.perm[pos] : pos;
-  s.dof = int64_t(s.node) * B * NR + lane % (B * NR);
+  s.dof = int64_t(s.node) * B + lane % B;
   return s;
 }
 
 // y = A x (MODE 0), b - A x (MODE 1), M (b - A x) (MODE 2); returns the written value
-template <int B, int NR, int K, class XI, class XO, class T, int MODE, int KB = kb_default<B>(), bool C16 = false,
+template <int B, int K, class XI, class XO, class T, int MODE, int KB = kb_default<B>(), bool C16 = false,
           int LK = 0>
 __device__ __forceinline__ T spmv_slice(const SellDev& A, const XO* __restrict__ b, const XI* __restrict__ x,
                                         XO* __restrict__ y, const uint8_t* __restrict__ mask, const SliceLane& s) {
@@ -426,9 +415,9 @@ __device__ __forceinline__ T spmv_slice(const SellDev& A, const XO* __restrict__
   uint8_t mk = 0;
   if (MODE != 0 && s.valid) {              // loaded before the row sum (latency overlap)
     bv = b[s.dof];
-    if (MODE == 2) mk = mask[s.dof / NR];
+    if (MODE == 2) mk = mask[s.dof];
   }
-  const T acc = sell_dot<B, NR, K, XI, T, KB, C16, LK>(A, s.slice, s.lane, s.valid, x);
+  const T acc = sell_dot<B, K, XI, T, KB, C16, LK>(A, s.slice, s.lane, s.valid, x);
   T out = T(0);
   if (s.valid) {
     if (MODE == 0) {
@@ -445,12 +434,10 @@ __device__ __forceinline__ T spmv_slice(const SellDev& A, const XO* __restrict__
 // x_out = x + omega S (b - A x), and with pmode != 0 the three-term (Chebyshev) form
 // x_out = x + omega S (b - A x) + beta (x - x_prev): pmode 1 reads x_prev from x_out
 // itself (each lane reads its own entry before it overwrites it), pmode 2 takes x_prev = 0
-template <int B, int NR, int K, class X, class T, int KB = kb_default<B>(), bool C16 = false, int LK = 0>
+template <int B, int K, class X, class T, int KB = kb_default<B>(), bool C16 = false, int LK = 0>
 __device__ __forceinline__ void sweep_slice(const SellDev& A, const X* __restrict__ S, const X* __restrict__ b,
                                             const X* __restrict__ x, X* __restrict__ xo, T omega,
                                             const SliceLane& s, T beta = T(0), int pmode = 0) {
-  constexpr int W = kWave / NR;
-  const int rl = s.lane / NR, q = s.lane % NR;
   // the lane's own b, x and smoother row are loaded before the row sum, so their latency
   // overlaps the slot batches
   X bv = X(0), xv = X(0), pv = X(0), sv[B];
@@ -463,15 +450,15 @@ __device__ __forceinline__ void sweep_slice(const SellDev& A, const X* __restric
     // with pmode != 1 it rereads x and the value is not used
     pv = (pmode == 1 ? static_cast<const X*>(xo) : x)[s.dof];
 #pragma unroll
-    for (int cc = 0; cc < B; ++cc) sv[cc] = S[(int64_t(s.slice) * B + cc) * W + rl];
+    for (int cc = 0; cc < B; ++cc) sv[cc] = S[(int64_t(s.slice) * B + cc) * kWave + s.lane];
   }
-  const T acc = sell_dot<B, NR, K, X, T, KB, C16, LK>(A, s.slice, s.lane, s.valid, x);
+  const T acc = sell_dot<B, K, X, T, KB, C16, LK>(A, s.slice, s.lane, s.valid, x);
   const T res = s.valid ? T(bv) - acc : T(0);
-  const int base = (rl / B) * B;
+  const int base = (s.lane / B) * B;
   T upd = T(0);
 #pragma unroll
   for (int cc = 0; cc < B; ++cc) {
-    const T rc = __shfl(res, ((base + cc) * NR + q) & (kWave - 1), kWave);
+    const T rc = __shfl(res, (base + cc) & (kWave - 1), kWave);
     if (s.valid) upd += T(sv[cc]) * rc;
   }
   if (s.valid) {
@@ -481,16 +468,14 @@ __device__ __forceinline__ void sweep_slice(const SellDev& A, const X* __restric
   }
 }
 
-template <int B, int NR, class X, class T>
+template <int B, class X, class T>
 __device__ __forceinline__ void sweep0_slice(const X* __restrict__ S, const X* __restrict__ b, X* __restrict__ xo,
                                              T omega, const SliceLane& s) {
-  constexpr int W = kWave / NR;
   if (!s.valid) return;
-  const int rl = s.lane / NR, q = s.lane % NR;
   T upd = T(0);
 #pragma unroll
   for (int cc = 0; cc < B; ++cc)
-    upd += T(S[(int64_t(s.slice) * B + cc) * W + rl]) * T(b[(int64_t(s.node) * B + cc) * NR + q]);
+    upd += T(S[(int64_t(s.slice) * B + cc) * kWave + s.lane]) * T(b[int64_t(s.node) * B + cc]);
   xo[s.dof] = X(omega * upd);
 }
 
@@ -498,46 +483,42 @@ __device__ __forceinline__ double weight(const CsrDev& M, int k) {
   return M.f32 ? double(static_cast<const float*>(M.val)[k]) : static_cast<const double*>(M.val)[k];
 }
 
-// d[t] = M_c sum_k R_jk (M_f r)[k], t = (j*B + c) * NR + q
-template <int B, int NR, class X, class T>
+// d[dof] = M_c sum_k R_jk (M_f r)[k], dof = j * B + c
+template <int B, class X, class T>
 __device__ __forceinline__ void restrict_dof(const CsrDev& R, const X* __restrict__ r, X* __restrict__ d,
                                              const uint8_t* __restrict__ mask_c, const uint8_t* __restrict__ mask_f,
-                                             int64_t t) {
-  const int64_t dof = t / NR;
-  const int q = int(t % NR);
+                                             int64_t dof) {
   const int j = int(dof / B), c = int(dof % B);
   T acc = T(0);
   if (!mask_c[dof]) {
     for (int k = R.rowptr[j]; k < R.rowptr[j + 1]; ++k) {
       const int64_t fd = int64_t(R.col[k]) * B + c;
-      if (mask_f == nullptr || !mask_f[fd]) acc += T(weight(R, k)) * T(r[fd * NR + q]);
+      if (mask_f == nullptr || !mask_f[fd]) acc += T(weight(R, k)) * T(r[fd]);
     }
   }
-  d[t] = X(acc);
+  d[dof] = X(acc);
 }
 
-// x[t] += M_f sum_k P_ik (M_c y)[k]
-template <int B, int NR, class X, class T>
+// x[dof] += M_f sum_k P_ik (M_c y)[k]
+template <int B, class X, class T>
 __device__ __forceinline__ void prolong_dof(const CsrDev& P, const X* __restrict__ y, X* __restrict__ x,
                                             const uint8_t* __restrict__ mask_f, const uint8_t* __restrict__ mask_c,
-                                            int64_t t) {
-  const int64_t dof = t / NR;
-  const int q = int(t % NR);
+                                            int64_t dof) {
   if (mask_f[dof]) return;
   const int i = int(dof / B), c = int(dof % B);
   T acc = T(0);
   for (int k = P.rowptr[i]; k < P.rowptr[i + 1]; ++k) {
     const int64_t cd = int64_t(P.col[k]) * B + c;
-    if (!mask_c[cd]) acc += T(weight(P, k)) * T(y[cd * NR + q]);
+    if (!mask_c[cd]) acc += T(weight(P, k)) * T(y[cd]);
   }
-  x[t] = X(T(x[t]) + acc);
+  x[dof] = X(T(x[dof]) + acc);
 }
 
 // ---- sliced transfers: NB slots of one node row, loads first (straight-line), then the
 // weighted sum in slot order.  MC: apply the column mask (entries whose column DoF is
 // masked contribute 0).
-template <int NB, int B, int NR, class X, class T, class WT, bool MC, bool NT>
-__device__ __forceinline__ void tsell_batch(const TSellDev& M, int k, int r, int c, int q,
+template <int NB, int B, class X, class T, class WT, bool MC, bool NT>
+__device__ __forceinline__ void tsell_batch(const TSellDev& M, int k, int r, int c,
                                             const X* __restrict__ in, const uint8_t* __restrict__ mcol,
                                             T& acc) {
   const int R = M.R;
@@ -554,7 +535,7 @@ __device__ __forceinline__ void tsell_batch(const TSellDev& M, int k, int r, int
 #pragma unroll
   for (int qq = 0; qq < NB; ++qq) {
     const uint64_t d = uint64_t(js[qq]) * B + c;
-    vs[qq] = in[d * NR + q];
+    vs[qq] = in[d];
     ms[qq] = MC ? mcol[d] : uint8_t(0);
   }
   __builtin_amdgcn_sched_barrier(0);
@@ -562,55 +543,54 @@ __device__ __forceinline__ void tsell_batch(const TSellDev& M, int k, int r, int
   for (int qq = 0; qq < NB; ++qq) acc += T(ws[qq]) * (ms[qq] ? T(0) : T(vs[qq]));
 }
 
-template <int N, int B, int NR, class X, class T, class WT, bool MC, bool NT>
-__device__ __forceinline__ void tsell_rest(int rem, const TSellDev& M, int k, int r, int c, int q,
+template <int N, int B, class X, class T, class WT, bool MC, bool NT>
+__device__ __forceinline__ void tsell_rest(int rem, const TSellDev& M, int k, int r, int c,
                                            const X* __restrict__ in, const uint8_t* __restrict__ mcol, T& acc) {
   if constexpr (N >= 1) {
-    if (rem == N) tsell_batch<N, B, NR, X, T, WT, MC, NT>(M, k, r, c, q, in, mcol, acc);
-    else tsell_rest<N - 1, B, NR, X, T, WT, MC, NT>(rem, M, k, r, c, q, in, mcol, acc);
+    if (rem == N) tsell_batch<N, B, X, T, WT, MC, NT>(M, k, r, c, in, mcol, acc);
+    else tsell_rest<N - 1, B, X, T, WT, MC, NT>(rem, M, k, r, c, in, mcol, acc);
   }
 }
 
 // one lane of a sliced transfer.  MODE 0: out = restriction sum (zero on masked rows);
 // MODE 1: out += prolongation sum (rows whose DoF is masked are left unchanged)
-template <int B, int NR, class X, class T, class WT, bool MC, int MODE>
+template <int B, class X, class T, class WT, bool MC, int MODE>
 __device__ __forceinline__ void tsell_lane(const TSellDev& M, int slice, int lane, const X* __restrict__ in,
                                            X* __restrict__ out, const uint8_t* __restrict__ mrow,
                                            const uint8_t* __restrict__ mcol) {
   constexpr int KB = 8;
   const int R = M.R;
-  const int r = lane / (B * NR), c = (lane / NR) % B, q = lane % NR;
+  const int r = lane / B, c = lane % B;
   const int node = slice * R + r;
-  if (slice >= M.nslices || lane >= R * B * NR || node >= M.nrows) return;
+  if (slice >= M.nslices || lane >= R * B || node >= M.nrows) return;
   const int64_t dof = int64_t(node) * B + c;
-  const int64_t t = dof * NR + q;
   // the row mask and (prolongation) the old value are loaded with the first slots; masked
   // rows run the sum too (their columns are valid indices) and drop it at the end, so no
   // branch waits for the mask before the slot loads are issued
   const uint8_t masked = mrow[dof];
   X old = X(0);
-  if (MODE == 1) old = out[t];
+  if (MODE == 1) old = out[dof];
   const int su = __builtin_amdgcn_readfirstlane(slice);
   int k, k1;
   slot_range(M, su, k, k1);
   T acc = T(0);
   if (M.nt) {
-    for (; k + KB <= k1; k += KB) tsell_batch<KB, B, NR, X, T, WT, MC, true>(M, k, r, c, q, in, mcol, acc);
-    tsell_rest<KB - 1, B, NR, X, T, WT, MC, true>(k1 - k, M, k, r, c, q, in, mcol, acc);
+    for (; k + KB <= k1; k += KB) tsell_batch<KB, B, X, T, WT, MC, true>(M, k, r, c, in, mcol, acc);
+    tsell_rest<KB - 1, B, X, T, WT, MC, true>(k1 - k, M, k, r, c, in, mcol, acc);
   } else {
-    for (; k + KB <= k1; k += KB) tsell_batch<KB, B, NR, X, T, WT, MC, false>(M, k, r, c, q, in, mcol, acc);
-    tsell_rest<KB - 1, B, NR, X, T, WT, MC, false>(k1 - k, M, k, r, c, q, in, mcol, acc);
+    for (; k + KB <= k1; k += KB) tsell_batch<KB, B, X, T, WT, MC, false>(M, k, r, c, in, mcol, acc);
+    tsell_rest<KB - 1, B, X, T, WT, MC, false>(k1 - k, M, k, r, c, in, mcol, acc);
   }
-  if (MODE == 0) out[t] = masked ? X(0) : X(acc);
-  else if (!masked) out[t] = X(T(old) + acc);
+  if (MODE == 0) out[dof] = masked ? X(0) : X(acc);
+  else if (!masked) out[dof] = X(T(old) + acc);
 }
 
-template <int B, int NR, class X, class T, class WT, bool MC, int MODE>
+template <int B, class X, class T, class WT, bool MC, int MODE>
 __global__ __launch_bounds__(kThreads) void k_tsell(TSellDev M, const X* __restrict__ in, X* __restrict__ out,
                                                     const uint8_t* __restrict__ mrow,
                                                     const uint8_t* __restrict__ mcol) {
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
-  tsell_lane<B, NR, X, T, WT, MC, MODE>(M, bid * kSliceWaves + threadIdx.x / kWave, threadIdx.x % kWave, in, out,
+  tsell_lane<B, X, T, WT, MC, MODE>(M, bid * kSliceWaves + threadIdx.x / kWave, threadIdx.x % kWave, in, out,
                                         mrow, mcol);
 }
 

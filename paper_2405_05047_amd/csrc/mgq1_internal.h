@@ -131,7 +131,8 @@ struct CsrDev {
 };
 
 // the same scalar transfer matrix as a sliced ELL over node rows (the layout the grid
-// kernels use): a slice holds R = 64 / (B * NR) rows, one lane per (row, component, rhs);
+// kernels use): a slice holds R = 64 / B rows, one lane per (row, component), or with 8
+// right-hand sides R = 64 / kRowLanes rows of kRowLanes lanes each;
 // slot k of row r of slice s sits at col / w[k * R + r] with k in [sptr[s], sptr[s+1]),
 // padded slots carry weight 0 and a column of their own row
 struct TSellDev {

@@ -96,8 +96,8 @@ template <int B, int K, class X, class T>
 __device__ void tail_sweep(const TailLevel& L, const X* b, const X* x, X* xo, T omega) {
   const int nw = blockDim.x / kWave, w = threadIdx.x / kWave, ln = threadIdx.x % kWave;
   for (int sl = w; sl < L.A.nslices; sl += nw)
-    sweep_slice<B, 1, K, X, T, kb_default<B>(), false, 2>(L.A, static_cast<const X*>(L.S), b, x, xo, omega,
-                                                          slice_lane<B, 1>(L.A, sl, ln));
+    sweep_slice<B, K, X, T, kb_default<B>(), false, 2>(L.A, static_cast<const X*>(L.S), b, x, xo, omega,
+                                                          slice_lane<B>(L.A, sl, ln));
   __syncthreads();
 }
 
@@ -123,7 +123,7 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(const TailLevel* __restri
     const X* b = column(L.b, L);
     if (p.nu1 >= 1) {
       for (int sl = w; sl < L.A.nslices; sl += nw)
-        sweep0_slice<B, 1, X, T>(static_cast<const X*>(L.S), b, cur, omega, slice_lane<B, 1>(L.A, sl, ln));
+        sweep0_slice<B, X, T>(static_cast<const X*>(L.S), b, cur, omega, slice_lane<B>(L.A, sl, ln));
       __syncthreads();
       for (int q = 1; q < p.nu1; ++q) {
         tail_sweep<B, K, X, T>(L, b, cur, oth, omega);
@@ -134,12 +134,12 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(const TailLevel* __restri
       __syncthreads();
     }
     for (int sl = w; sl < L.A.nslices; sl += nw)
-      spmv_slice<B, 1, K, X, X, T, 2, kb_default<B>(), false, 2>(L.A, b, cur, column(L.r, L), L.mask,
-                                                                 slice_lane<B, 1>(L.A, sl, ln));
+      spmv_slice<B, K, X, X, T, 2, kb_default<B>(), false, 2>(L.A, b, cur, column(L.r, L), L.mask,
+                                                                 slice_lane<B>(L.A, sl, ln));
     __syncthreads();
     const TailLevel& C = lv[l - 1];
     for (int64_t t = threadIdx.x; t < int64_t(C.A.n) * B; t += blockDim.x)
-      restrict_dof<B, 1, X, T>(L.R, column(L.r, L), column(C.b, C), C.mask, nullptr, t);
+      restrict_dof<B, X, T>(L.R, column(L.r, L), column(C.b, C), C.mask, nullptr, t);
     __syncthreads();
   }
   // coarse solve on level 0
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(const TailLevel* __restri
       X* cur = ((k - 1) % 2 == 0) ? x0 : tmp;
       X* oth = ((k - 1) % 2 == 0) ? tmp : x0;
       for (int sl = w; sl < C.A.nslices; sl += nw)
-        sweep0_slice<B, 1, X, T>(static_cast<const X*>(C.S), b0, cur, omega, slice_lane<B, 1>(C.A, sl, ln));
+        sweep0_slice<B, X, T>(static_cast<const X*>(C.S), b0, cur, omega, slice_lane<B>(C.A, sl, ln));
       __syncthreads();
       for (int q = 1; q < k; ++q) {
         tail_sweep<B, K, X, T>(C, b0, cur, oth, omega);
@@ -174,7 +174,7 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(const TailLevel* __restri
     X* oth = (pp % 2 == 0) ? tmp : own;
     if (pre_pp % 2 == 1) { X* t = cur; cur = oth; oth = t; }
     for (int64_t t = threadIdx.x; t < int64_t(L.A.n) * B; t += blockDim.x)
-      prolong_dof<B, 1, X, T>(L.P, column(C.x, C), cur, L.mask, C.mask, t);
+      prolong_dof<B, X, T>(L.P, column(C.x, C), cur, L.mask, C.mask, t);
     __syncthreads();
     for (int q = 0; q < p.nu2; ++q) {
       tail_sweep<B, K, X, T>(L, column(L.b, L), cur, oth, omega);
@@ -563,10 +563,10 @@ hipError_t tsell_w(int mode, const TSellDev& M, const void* in, void* out, const
   const X* ii = static_cast<const X*>(in);
   X* oo = static_cast<X*>(out);
   if (mode == 0) {
-    if (mcol) hipLaunchKernelGGL((k_tsell<B, 1, X, T, WT, true, 0>), g, kThreads, 0, s, M, ii, oo, mrow, mcol);
-    else hipLaunchKernelGGL((k_tsell<B, 1, X, T, WT, false, 0>), g, kThreads, 0, s, M, ii, oo, mrow, mcol);
+    if (mcol) hipLaunchKernelGGL((k_tsell<B, X, T, WT, true, 0>), g, kThreads, 0, s, M, ii, oo, mrow, mcol);
+    else hipLaunchKernelGGL((k_tsell<B, X, T, WT, false, 0>), g, kThreads, 0, s, M, ii, oo, mrow, mcol);
   } else {
-    hipLaunchKernelGGL((k_tsell<B, 1, X, T, WT, true, 1>), g, kThreads, 0, s, M, ii, oo, mrow, mcol);
+    hipLaunchKernelGGL((k_tsell<B, X, T, WT, true, 1>), g, kThreads, 0, s, M, ii, oo, mrow, mcol);
   }
   return hipGetLastError();
 }

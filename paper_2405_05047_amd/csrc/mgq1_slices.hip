@@ -14,8 +14,8 @@ __global__ __launch_bounds__(kThreads) void k_spmv(SellDev A, const XO* __restri
                                                    double* __restrict__ partials) {
   dict_stage<K>(A);
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
-  const SliceLane s = slice_lane<B, 1>(A, bid * kSliceWaves + threadIdx.x / kWave, threadIdx.x % kWave);
-  const T out = spmv_slice<B, 1, K, XI, XO, T, MODE, KB, C16>(A, b, x, y, mask, s);
+  const SliceLane s = slice_lane<B>(A, bid * kSliceWaves + threadIdx.x / kWave, threadIdx.x % kWave);
+  const T out = spmv_slice<B, K, XI, XO, T, MODE, KB, C16>(A, b, x, y, mask, s);
   if (NORM) {
     __shared__ double lds[kMaxWaves + 1];
     const double p = block_allsum(double(out) * double(out), lds);
@@ -29,8 +29,8 @@ __global__ __launch_bounds__(kThreads) void k_sweep(SellDev A, const X* __restri
                                                     T beta, int pmode) {
   dict_stage<K>(A);
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
-  const SliceLane s = slice_lane<B, 1>(A, bid * kSliceWaves + threadIdx.x / kWave, threadIdx.x % kWave);
-  sweep_slice<B, 1, K, X, T, KB, C16>(A, S, b, x, xo, omega, s, beta, pmode);
+  const SliceLane s = slice_lane<B>(A, bid * kSliceWaves + threadIdx.x / kWave, threadIdx.x % kWave);
+  sweep_slice<B, K, X, T, KB, C16>(A, S, b, x, xo, omega, s, beta, pmode);
 }
 
 // ------------------------------------------------------------------ relay form
@@ -113,7 +113,7 @@ template <int B, int K, class XI, class XO, class T, int MODE, bool C16>
 __global__ __launch_bounds__(kThreads) void k_spmv_relay(SellDev A, const XO* __restrict__ b, const XI* __restrict__ x,
                                                          XO* __restrict__ y, const uint8_t* __restrict__ mask) {
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
-  const SliceLane s = slice_lane<B, 1>(A, bid, int(threadIdx.x) % kWave);
+  const SliceLane s = slice_lane<B>(A, bid, int(threadIdx.x) % kWave);
   const bool last = int(threadIdx.x) / kWave == kSliceWaves - 1 && s.valid;
   XO bv = XO(0);
   uint8_t mk = 0;
@@ -134,7 +134,7 @@ __global__ __launch_bounds__(kThreads) void k_sweep_relay(SellDev A, const X* __
                                                           const X* __restrict__ x, X* __restrict__ xo, T omega,
                                                           T beta, int pmode) {
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
-  const SliceLane s = slice_lane<B, 1>(A, bid, int(threadIdx.x) % kWave);
+  const SliceLane s = slice_lane<B>(A, bid, int(threadIdx.x) % kWave);
   const bool mine = int(threadIdx.x) / kWave == kSliceWaves - 1;
   const bool last = mine && s.valid;
   X bv = X(0), xv = X(0), pv = X(0), sv[B];
@@ -199,8 +199,8 @@ __global__ __launch_bounds__(kThreads) void k_sweep2z(SellDev A, const X* __rest
 template <int B, class X, class T>
 __global__ __launch_bounds__(kThreads) void k_sweep0(SellDev A, const X* __restrict__ S, const X* __restrict__ b,
                                                      X* __restrict__ xo, T omega) {
-  const SliceLane s = slice_lane<B, 1>(A, blockIdx.x * kSliceWaves + threadIdx.x / kWave, threadIdx.x % kWave);
-  sweep0_slice<B, 1, X, T>(S, b, xo, omega, s);
+  const SliceLane s = slice_lane<B>(A, blockIdx.x * kSliceWaves + threadIdx.x / kWave, threadIdx.x % kWave);
+  sweep0_slice<B, X, T>(S, b, xo, omega, s);
 }
 
 
