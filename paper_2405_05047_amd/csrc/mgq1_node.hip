@@ -11,10 +11,9 @@
 //            general   a 16-bit block number per row and slot, the block read per lane
 //   columns  uniform   all rows have the same column offsets: nothing is stored per row, the
 //                      64 lanes read the neighbours' vector as one run.  With several
-//                      components the runs are staged in LDS: a lane's B values lie B apart, so
-//                      reading them slot by slot touches every cache line several times (64 tag
-//                      accesses per slot and wave on 129^3 elasticity, 87% of that sweep's
-//                      cycles), and the 3 slots of a mesh line read almost the same run
+//                      components the runs are staged in LDS: the lanes' B values lie B apart, so
+//                      reading them component by component and slot by slot touches every cache
+//                      line several times, and the 3 slots of a mesh line read almost the same run
 //            16-bit    offsets from the slot's smallest column (32-bit where they do not fit)
 //
 // The sliced-ELL form of the same operator streams 8 B^2 + 2 bytes per block; here a block
