@@ -3202,7 +3202,8 @@ int asm_setup(AsmDev* A, const mg_asm_in& in, hipStream_t s) {
       if (in.A_col[k] < 0 || in.A_col[k] >= n || (k > in.A_rowptr[i] && in.A_col[k] <= in.A_col[k - 1]))
         return fail(MG_EINVAL, "columns must be in range, sorted and unique");
   // contributions, cell by cell, counted per block then placed (stable)
-  std::vector<std::pair<int64_t, uint16_t>> contrib;
+  std::vector<std::pair<uint32_t, uint16_t>> contrib;        // block (nnzb < 2^31), code
+  contrib.reserve(size_t(in.n_cells) * nb * nb);
   for (int32_t e = 0; e < in.n_cells; ++e) {
     const int d = int(std::lower_bound(sizes.begin(), sizes.end(), in.cell_size[e]) - sizes.begin());
     for (int a = 0; a < nb; ++a) {
@@ -3227,7 +3228,7 @@ int asm_setup(AsmDev* A, const mg_asm_in& in, hipStream_t s) {
             if (it == r1 || *it != nbn[qb]) continue;   // a constrained column node
             const int ex = xa[qa] + xb[qb];
             if (ex > 7) return fail(MG_EUNSUPPORTED, "hanging weight product below 2^-7");
-            contrib.push_back({int64_t(it - in.A_col), uint16_t(d | a << 5 | b << 8 | ex << 11)});
+            contrib.push_back({uint32_t(it - in.A_col), uint16_t(d | a << 5 | b << 8 | ex << 11)});
           }
         }
       }
@@ -3242,10 +3243,6 @@ int asm_setup(AsmDev* A, const mg_asm_in& in, hipStream_t s) {
     std::vector<uint32_t> fill(cptr.begin(), cptr.end() - 1);
     for (const auto& c : contrib) code[fill[size_t(c.first)]++] = c.second;
   }
-  std::vector<int32_t> brow(size_t(in.nnzb)), bcol(in.A_col, in.A_col + in.nnzb);
-  for (int32_t i = 0; i < n; ++i)
-    for (int32_t k = in.A_rowptr[i]; k < in.A_rowptr[i + 1]; ++k) brow[size_t(k)] = i;
-  std::vector<uint8_t> mask(in.dof_mask, in.dof_mask + size_t(n) * B);
   int rc;
   int32_t *p32;
   uint32_t* pu;
@@ -3269,14 +3266,16 @@ int asm_setup(AsmDev* A, const mg_asm_in& in, hipStream_t s) {
   std::vector<int64_t> rep;
   if (lists) {
     bits.resize(size_t(in.nnzb));
-    parallel_for(in.nnzb, 1 << 16, [&](int64_t k0, int64_t k1) {
-      for (int64_t k = k0; k < k1; ++k) {
-        unsigned m = brow[size_t(k)] == bcol[size_t(k)] ? 256u : 0u;
-        for (int c = 0; c < B; ++c) {
-          if (mask[size_t(brow[size_t(k)]) * B + c]) m |= 1u << c;
-          if (mask[size_t(bcol[size_t(k)]) * B + c]) m |= 16u << c;
+    parallel_for(n, 1 << 13, [&](int64_t i0, int64_t i1) {
+      for (int64_t i = i0; i < i1; ++i) {
+        unsigned row = 0;
+        for (int c = 0; c < B; ++c) row |= in.dof_mask[size_t(i) * B + c] ? 1u << c : 0u;
+        for (int64_t k = in.A_rowptr[i]; k < in.A_rowptr[i + 1]; ++k) {
+          const int64_t j = in.A_col[k];
+          unsigned m = row | (i == j ? 256u : 0u);
+          for (int c = 0; c < B; ++c) m |= in.dof_mask[size_t(j) * B + c] ? 16u << c : 0u;
+          bits[size_t(k)] = uint16_t(m);
         }
-        bits[size_t(k)] = uint16_t(m);
       }
     });
     lists = distinct_lists(in.nnzb, cptr, code, bits, lid, rep) && (force == 1 || int64_t(rep.size()) * 4 <= in.nnzb);
@@ -3301,6 +3300,10 @@ int asm_setup(AsmDev* A, const mg_asm_in& in, hipStream_t s) {
     A->nl = int(rep.size());
     MG_HIP(hipStreamSynchronize(s));
   } else {
+    std::vector<int32_t> brow(size_t(in.nnzb)), bcol(in.A_col, in.A_col + in.nnzb);
+    for (int32_t i = 0; i < n; ++i)
+      for (int32_t k = in.A_rowptr[i]; k < in.A_rowptr[i + 1]; ++k) brow[size_t(k)] = i;
+    std::vector<uint8_t> mask(in.dof_mask, in.dof_mask + size_t(n) * B);
     if ((rc = upload(A, &p32, brow, s))) return rc;
     A->brow = p32;
     if ((rc = upload(A, &p32, bcol, s))) return rc;
@@ -3311,6 +3314,7 @@ int asm_setup(AsmDev* A, const mg_asm_in& in, hipStream_t s) {
     A->code = p16;
     if ((rc = upload(A, &p8, mask, s))) return rc;
     A->mask = p8;
+    MG_HIP(hipStreamSynchronize(s));
   }
   if ((rc = upload(A, &pd, sizes, s))) return rc;
   A->sizes = pd;
