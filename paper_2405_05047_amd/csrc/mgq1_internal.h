@@ -263,6 +263,9 @@ int reduction_grid(int64_t n);
 hipError_t launch_dot_partials(int64_t n, const double* a, const double* b, double* partials, hipStream_t s);
 hipError_t launch_finish(const double* partials, int g, double* out, int sqrt_out, hipStream_t s,
                          double* host = nullptr);
+// ||a|| to *out and *host by the two above, in one launch where one block takes the vector (4,096
+// elements: solves of a cycle or two notice the launches); partials: reduction_grid(n) doubles
+hipError_t launch_norm(int64_t n, const double* a, double* partials, double* out, double* host, hipStream_t s);
 // Gram-Schmidt of FGMRES step j (modified Gram-Schmidt with its dot products formed in one
 // pass): w -= sum_{i<=j} h_i v_i, v_i = V + i * n, h stored in h[0..j]; gram: kWave * kWave
 // doubles that hold the basis's Gram entries from step to step (row 0 first, any content

@@ -326,10 +326,9 @@ __global__ void k_scale_div(int64_t n, double* __restrict__ y, const double* __r
   }
 }
 
-// partial sums of a.b (b == nullptr: a.a), one per block
-__global__ __launch_bounds__(kRedThreads) void k_dot_partials(int64_t n, const double* __restrict__ a,
-                                                              const double* __restrict__ b, double* __restrict__ out) {
-  __shared__ double lds[kMaxWaves + 1];
+// this block's part of a.b (b == nullptr: a.a), on every thread
+__device__ __forceinline__ double dot_block(int64_t n, const double* __restrict__ a, const double* __restrict__ b,
+                                            double* lds) {
   constexpr int U = 4;                     // elements per thread and round, loads first
   double t = 0.0;
   const int64_t stride = int64_t(gridDim.x) * blockDim.x;
@@ -344,24 +343,40 @@ __global__ __launch_bounds__(kRedThreads) void k_dot_partials(int64_t n, const d
 #pragma unroll
     for (int u = 0; u < U; ++u) t += av[u] * bv[u];
   }
-  const double s = block_allsum(t, lds);
+  return block_allsum(t, lds);
+}
+
+// partial sums of a.b (b == nullptr: a.a), one per block
+__global__ __launch_bounds__(kRedThreads) void k_dot_partials(int64_t n, const double* __restrict__ a,
+                                                              const double* __restrict__ b, double* __restrict__ out) {
+  __shared__ double lds[kMaxWaves + 1];
+  const double s = dot_block(n, a, b, lds);
   if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
-// out = sum (or sqrt of the sum) of partials, one workgroup; host: the same to memory that the
-// host reads after the stream has been waited for
+// v to *out and to memory that the host reads after the stream has been waited for
+__device__ __forceinline__ void store_scalar(double v, double* out, double* host) {
+  *out = v;
+  if (host) {
+    *host = v;
+    __threadfence_system();
+  }
+}
+
+// ||a|| of a vector that one block takes: k_dot_partials and k_finish in one launch, same bits
+__global__ __launch_bounds__(kRedThreads) void k_norm_block(int64_t n, const double* __restrict__ a, double* out,
+                                                            double* host) {
+  __shared__ double lds[kMaxWaves + 1];
+  const double s = dot_block(n, a, nullptr, lds);
+  if (threadIdx.x == 0) store_scalar(sqrt(s), out, host);
+}
+
+// out = sum (or sqrt of the sum) of partials, one workgroup; host as in store_scalar
 __global__ __launch_bounds__(1024) void k_finish(const double* __restrict__ p, int g, double* out, int sq,
                                                  double* host) {
   __shared__ double lds[kMaxWaves + 1];
   const double s = sum_partials(p, g, lds);
-  if (threadIdx.x == 0) {
-    const double v = sq ? sqrt(s) : s;
-    *out = v;
-    if (host) {
-      *host = v;
-      __threadfence_system();
-    }
-  }
+  if (threadIdx.x == 0) store_scalar(sq ? sqrt(s) : s, out, host);
 }
 
 // Givens rotation j of the Hessenberg column j (applies the previous rotations, forms the
@@ -756,6 +771,15 @@ hipError_t launch_scale_div(int64_t n, double* y, const double* x, const double*
 hipError_t launch_dot_partials(int64_t n, const double* a, const double* b, double* partials, hipStream_t s) {
   hipLaunchKernelGGL(k_dot_partials, vec_grid(n), kRedThreads, 0, s, n, a, b, partials);
   return hipGetLastError();
+}
+
+hipError_t launch_norm(int64_t n, const double* a, double* partials, double* out, double* host, hipStream_t s) {
+  if (vec_grid(n) == 1) {
+    hipLaunchKernelGGL(k_norm_block, 1, kRedThreads, 0, s, n, a, out, host);
+    return hipGetLastError();
+  }
+  const hipError_t e = launch_dot_partials(n, a, nullptr, partials, s);
+  return e != hipSuccess ? e : launch_finish(partials, reduction_grid(n), out, 1, s, host);
 }
 
 hipError_t launch_finish(const double* partials, int g, double* out, int sqrt_out, hipStream_t s, double* host) {

@@ -1436,8 +1436,7 @@ int enqueue_defect(mg_handle* h, const double* b, const double* x, hipStream_t s
   LevelDev& T = h->lv[h->L];
   if (h->cfg.outer == MG_OUTER_FGMRES) {
     MG_HIP(launch_spmv(T.A64, b, x, h->rout, nullptr, X_F64, X_F64, 1, nullptr, s));
-    MG_HIP(launch_dot_partials(T.N, h->rout, nullptr, h->pv, s));
-    MG_HIP(launch_finish(h->pv, reduction_grid(T.N), h->dsc + 0, 1, s, h->norm_dev));
+    MG_HIP(launch_norm(T.N, h->rout, h->pv, h->dsc + 0, h->norm_dev, s));
   } else {
     MG_HIP(launch_spmv(T.A64, b, x, h->rout, nullptr, X_F64, X_F64, 1, h->pbig, s));
     MG_HIP(launch_finish(h->pbig, spmv_grid(T.A64), h->dsc + 0, 1, s, h->norm_dev));
@@ -1518,8 +1517,7 @@ int solve_impl(mg_handle* h, const double* b, double* x, mg_solve_stats* st, voi
   int rc;
   // ||b|| (to dsc[4]) and the initial defect r = b - A x with ||r|| (to dsc[0]), read
   // back with one synchronisation
-  MG_HIP(launch_dot_partials(N, b, nullptr, h->pv, s));
-  MG_HIP(launch_finish(h->pv, reduction_grid(N), h->dsc + 4, 1, s, h->norm_dev + 1));
+  MG_HIP(launch_norm(N, b, h->pv, h->dsc + 4, h->norm_dev + 1, s));
   if ((rc = outer_defect(h, b, x, s))) return rc;
   const double bn = h->norm[1];
   const double tol = c.rtol * bn;
